@@ -79,11 +79,22 @@ __global__ __launch_bounds__(256) void batch_prep(BatchArgs B, int jprec) {
                 woff += (w < wave) ? wave_tot[w] : 0;
                 tot += wave_tot[w];
             }
-            if (f) B.perm[E.row_off + base + woff + below] = i;
+            if (f) {
+                B.perm[E.row_off + base + woff + below] = i;
+                B.rank[E.row_off + i] = base + woff + below;
+            }
             base += tot;
             __syncthreads();
         }
     }
+    // columns as ranks, for the step kernel's LDS addresses
+    if (E.n <= kBatchSlots)
+        for (int i = t; i < E.n; i += 256)
+            for (int p = B.row_ptr[E.rp_off + i]; p < B.row_ptr[E.rp_off + i + 1]; ++p) {
+                const int c = B.col[E.nz_off + p];
+                B.colr[E.nz_off + p] =
+                    static_cast<uint16_t>(B.rank[E.row_off + c] | (c > i ? 0x8000 : 0));
+            }
 }
 
 __global__ void batch_reset(int *counters, int n) {

@@ -77,7 +77,8 @@ constexpr int kRegStride = kRegMaxN + 64;  // LDS position buffer: n words, then
 constexpr int kBatchTPB = 1024;                     // threads per workgroup, large shape
 constexpr int kBatchTPBSmall = 512;                 // small shape (two workgroups per CU)
 constexpr int kBatchSPT = 9;                        // slots per thread (both shapes)
-constexpr int kBatchSlots = kBatchTPB * kBatchSPT;  // largest n * agents per item
+constexpr int kBatchAgents = 2;                     // agents per slot
+constexpr int kBatchSlots = kBatchTPB * kBatchSPT;  // largest n * agents / 2 per item
 constexpr int kBatchSlotsSmall = kBatchTPBSmall * kBatchSPT;
 constexpr int kBatchTailCap = 8192;                 // default LDS words for couplings past the
                                                     //   slots' register capacity (32 KB)
@@ -86,21 +87,11 @@ constexpr int kBatchTailCap = 8192;                 // default LDS words for cou
 // BF16 hi + lo pairs (streaming kernels, sb_stream_kernels.hpp)
 enum : int { kJFp16 = 0, kJBf16 = 1, kJFp32 = 2, kJFp8 = 3, kJFp8Blk = 4, kJBf16x2 = 5 };
 
-// LDS bytes of one batch workgroup of `tpb` threads with `tail_words` of
-// staged couplings: two position buffers (slots plus one pad word per lane
-// of a wave), the per-wave reduction area, the item word, the tails.
-constexpr size_t batch_lds_bytes(int tpb, int tail_words) {
-    return sizeof(float) * 2 * (static_cast<size_t>(tpb) * kBatchSPT + 64) +
-           sizeof(double) * static_cast<size_t>(tpb / 64) * 64 + 16 +
-           sizeof(uint32_t) * static_cast<size_t>(tail_words);
-}
-
 struct BatchEvent {
     int n, nnz;
     int row_off;                 // offset into per-spin arrays (a, h, perm, best_T, T rows)
     int rp_off;                  // offset into row_ptr (row_off + event index)
     int nz_off;                  // offset into col, b, J16
-    int lg_agents;               // log2 of the agents one work item holds
     int event_id;                // Philox counter word 2
     float c0_scale;              // c0 of the event = (fixed or auto c0) * c0_scale
 };
@@ -115,16 +106,22 @@ struct BatchArgs {
     const BatchEvent *ev;        // [E]
     const int *item_event;       // [n_items], decreasing cost
     const int *item_agent0;      // [n_items]
+    const int *item_lg;          // [n_items] log2 of the agents an item holds
     const int *row_ptr;          // [sum (n + 1)] per-event row pointers (local)
     const int *col;              // [sum nnz] per-event spin ids (local)
     const double *a;             // [sum n]
     const double *b;             // [sum nnz]
     uint16_t *J16;               // [sum nnz] 16-bit couplings (prep output)
+    uint16_t *colr;              // [sum nnz] rank of each column in the spin order, bit 15:
+                                 //   the column is above its row (prep output; events of
+                                 //   at most kBatchSlots spins)
     float *h;                    // [sum n]
     float *c0;                   // [E]
     double *offset;              // [E] Ising offset C
     int *perm;                   // [sum n] spin order per event
+    int *rank;                   // [sum n] its inverse
     const float *sched;          // [K]
+    void *trash;                 // 64 bytes that absorb stores of lanes without work
     int *counter;                // this launch's work queue counter
     double *etrace;              // [E * n_ckpt * M]
     double *energy;              // [E * M] final O(T)
@@ -136,6 +133,11 @@ struct BatchArgs {
     int8_t *best_T;              // [sum n]
     long long *ckpt_clock;       // [E * (n_ckpt + 1) * M] device wall clock at each
                                  //   agent's item start and checkpoints, or null
+    // a single event solved by the same step loop (FP32 couplings)
+    const float *J32;            // [nnz]
+    const double *scal;          // [0] = c0
+    float *y_out;                // [n * M] final momenta, or null
+    BatchEvent one;              // the event
     const double *target;        // [E] or null: stop an event's work at the first
                                  //   checkpoint where an agent reaches O(T) <= target
     int *done;                   // [E] events whose target was reached (target mode)

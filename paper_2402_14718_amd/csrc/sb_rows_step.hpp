@@ -1,0 +1,703 @@
+// The step loop of solves whose whole state stays on chip (gfx950): one
+// workgroup holds every spin of a few agents from the start draw to the
+// last step.  The batched kernel (sb_batch_step.hpp) and the resident
+// single-event kernel (sb_resident_rows.hpp) are this body.
+//
+// Paper section "Simulated Bifurcation": bSB (Eq. 5-8), dSB (Eq. 9-12), aSB
+// (Eq. 1-4).
+//
+// Layout.  An item is one event with G groups of W agents (G a power of
+// two).  Its spins are ranked by decreasing row length, and position
+// j = rank * G + group is one LDS word of W shared values (x, or sgn x for
+// dSB).  Thread t's slot s is position s * T + t, so a wave's stores are
+// consecutive words and need no address of their own (odd slots hand their
+// positions to the waves in reverse order, so that no wave holds the longest
+// rows of every slot); x and y of the W
+// agents, the field and the row's couplings live in VGPRs.  A coupling is
+// read once from LDS for all W agents, and held once.  For dSB a word holds
+// the W = 2 signs as two halves +-1.0, which the fused multiply-add takes
+// as they are (v_fma_mix), so a gather moves half the bytes of FP32 values.
+//
+// Why W = 2 and no branches per coupling but per pair: this loop is bound
+// by VALU issue and by the LDS.  Rows of 64 consecutive ranks have nearly
+// the same length, so each wave keeps its longest row per slot in an SGPR
+// and skips whole groups of couplings past it: gathers and multiply-adds
+// come to 1.03-1.1 times the couplings on events of 100 to 1000 particles,
+// where fixed counts per slot came to 1.4 times.
+//
+// Couplings past a slot's register capacity are packed into an LDS array
+// once per item and summed from there, in CSR order after the held ones; an
+// item whose tails do not fit reads them from global memory.  Absent
+// couplings of a group are a zero coupling to the spin itself: they add an
+// exact zero.
+//
+// No branch around the state is divergent: lanes without work read another
+// lane's data and select, and write to a dump word.  With the registers all
+// in use, the register allocator places copies at the joins of divergent
+// branches, ahead of the instruction that switches the lanes back on
+// (seen in the ISA of an earlier form of this loop: lanes lost an address).
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <hip/hip_fp16.h>
+
+#include <cstdint>
+#include <type_traits>
+
+#include "sb_device.hpp"
+#include "sb_kernels.hpp"
+
+namespace sbt {
+
+namespace {
+
+// Couplings held per slot, by slot: slot 0 holds the longest rows.  On the
+// 1000-particle event (n = 8484, 9 slots of 1024) the longest rows by slot
+// are 19-26, 6-7, 4, 3, 2, 2, 2, 2, 1.
+constexpr int kCap[kBatchSPT] = {16, 8, 5, 4, 3, 2, 2, 2, 1};
+__host__ __device__ constexpr int cap_before(int s) {
+    int o = 0;
+    for (int i = 0; i < s; ++i) o += kCap[i];
+    return o;
+}
+// Couplings of every slot that are gathered while the slot before is summed.
+constexpr int kAhead = 2;
+__host__ __device__ constexpr int ahead(int s) { return kCap[s] < kAhead ? kCap[s] : kAhead; }
+constexpr uint16_t kColUpper = 0x8000;  // colr: the column is above the row (j > i)
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// Hides a loop-invariant register from the optimiser (an empty asm that
+// "modifies" it), so that values derived from it are recomputed where used
+// instead of being hoisted out of the step loop and kept live.
+__device__ __forceinline__ void launder(uint32_t &v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void launder_uniform(int &v) { asm volatile("" : "+s"(v)); }
+
+// Calls f(integral_constant<int, I>) for I = 0 .. N-1.
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void unrolled(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        unrolled<N, I + 1>(f);
+    }
+}
+
+// What one LDS word holds: the shared values of W agents.
+template <int MODE, int W>
+struct Shared {
+    static_assert(W == 1 || W == 2, "one or two agents per word");
+    static constexpr bool kSigns = MODE == kDSB && W == 2;  // two halves +-1.0
+    using type = std::conditional_t<kSigns, uint32_t, std::conditional_t<W == 2, f32x2, float>>;
+    static constexpr uint32_t kBytes = sizeof(type);
+
+    static __device__ __forceinline__ type pack(const float (&x)[W]) {
+        if constexpr (kSigns) {
+            // upper halves of both, their sign bits onto 1.0 (0x3C00)
+            const uint32_t u = __builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]),
+                                                     0x07060302u);
+            uint32_t r;  // (one bitfield insert; as C++ it becomes an and and an or)
+            asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(0x7FFF7FFFu), "v"(0x3C003C00u), "v"(u));
+            return r;
+        } else if constexpr (W == 2) {
+            return f32x2{shared_value<MODE>(x[0]), shared_value<MODE>(x[1])};
+        } else {
+            return shared_value<MODE>(x[0]);
+        }
+    }
+    template <int A>
+    static __device__ __forceinline__ float get(type v) {
+        if constexpr (kSigns)
+            return static_cast<float>(__ushort_as_half(static_cast<uint16_t>(A == 0 ? v : v >> 16)));
+        else if constexpr (W == 2)
+            return v[A];
+        else
+            return v;
+    }
+};
+
+// sb_step with the position's multiply-add in a register of its own: in
+// place it costs a copy, because the wall test and the clamp both read it.
+template <int MODE>
+__device__ __forceinline__ void rows_step(float &x, float &y, float F, float c0, float g, float dt,
+                                          float dta0) {
+    if constexpr (MODE == kASB) {
+        sb_update_asb(x, y, F, c0, g, dt, dta0);
+    } else {
+        const float force = __builtin_fmaf(c0, F, -(g * x));
+        const float yn = __builtin_fmaf(dt, force, y);
+        float xn;
+        asm("v_fma_f32 %0, %1, %2, %3" : "=v"(xn) : "s"(dta0), "v"(yn), "v"(x));
+        y = __builtin_fabsf(xn) > 1.0f ? 0.0f : yn;
+        x = __builtin_amdgcn_fmed3f(xn, -1.0f, 1.0f);
+    }
+    asm volatile("" : "+v"(y));  // the select stays here
+}
+
+__device__ __forceinline__ float uniform(float v) {
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+}
+
+// *p = v where `mine`, into the trash words elsewhere: a store with no
+// branch around it.
+template <class T>
+__device__ __forceinline__ void put(bool mine, T *p, T v, void *trash) {
+    *(mine ? p : static_cast<T *>(trash)) = v;
+}
+
+template <class T>
+__device__ __forceinline__ T lds_read(uint32_t addr) {
+    typedef __attribute__((address_space(3))) T lds_t;
+    return *(const lds_t *)(static_cast<uintptr_t>(addr));
+}
+
+template <class T>
+__device__ __forceinline__ void lds_write(uint32_t addr, T v) {
+    typedef __attribute__((address_space(3))) T lds_t;
+    *(lds_t *)(static_cast<uintptr_t>(addr)) = v;
+}
+
+}  // namespace
+
+// LDS of one workgroup: two position buffers of S * TPB words, the
+// reduction area where the idle position buffer is too small for it, the
+// item word, the tails.
+template <int MODE, int TPB, int S, int W>
+struct RowsLds {
+    static constexpr uint32_t kBuf = static_cast<uint32_t>(S) * TPB * Shared<MODE, W>::kBytes;
+    static constexpr uint32_t kRed = sizeof(double) * TPB * W;
+    static constexpr bool kRedInBuf = kRed <= kBuf;  // energies reduce in the buffer not read
+    static constexpr uint32_t kItem = 2 * kBuf + (kRedInBuf ? 0 : kRed);
+    static constexpr uint32_t kDump = kItem + 32;  // two words that absorb writes of no one
+    static constexpr uint32_t kTails = kItem + 64;
+    static constexpr uint32_t kMax = TPB <= 512 && S == kBatchSPT ? 81920 : 163840;
+    static constexpr int kTailWords = static_cast<int>((kMax - kTails) / 4);
+    static int tail_words(int asked) { return asked < kTailWords ? asked : kTailWords; }
+    static size_t bytes(int tails) { return kTails + sizeof(uint32_t) * static_cast<size_t>(tails); }
+};
+
+// SINGLE: one event, workgroup b takes agents b * W ..; otherwise items from
+// a queue.  T: threads of the workgroup (TPB except for single events).
+template <int MODE, int JP, int TPB, int S, int W, bool SINGLE>
+__device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *smem) {
+    using V = Shared<MODE, W>;
+    using word = typename V::type;
+    using L = RowsLds<MODE, TPB, S, W>;
+    constexpr bool kWide = JP == kJFp32;            // coupling and address in words of their own
+    constexpr uint32_t kB = V::kBytes;
+    // a held address is 16 bits: the byte address where every word of the
+    // first buffer has one, else the position
+    constexpr bool kBytesHeld = L::kBuf <= 65536;
+    constexpr uint32_t kScale = kBytesHeld ? kB : 1;
+    constexpr int kHeld = cap_before(S);
+    static_assert(S <= kBatchSPT && (kBytesHeld || L::kBuf <= 8 * 65536), "positions fit 16 bits");
+
+    double *red_own = reinterpret_cast<double *>(smem + 2 * L::kBuf);
+    int *item_s = reinterpret_cast<int *>(smem + L::kItem);
+    const int t = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int T = SINGLE ? static_cast<int>(blockDim.x) : TPB;
+    const int nwaves = T >> 6;
+    auto sync = [&]() __attribute__((always_inline)) {
+        if constexpr (TPB == 64) {
+            // one wave: the LDS executes its accesses in order
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        } else {
+            __syncthreads();
+        }
+    };
+
+    for (bool first = true;; first = false) {
+        int e = 0, agent0, lgG = 0;
+        if constexpr (SINGLE) {
+            if (!first) return;
+            agent0 = static_cast<int>(blockIdx.x) * W;
+        } else {
+            if (t == 0) *item_s = atomicAdd(B.counter, 1);
+            __syncthreads();
+            const int local = __builtin_amdgcn_readfirstlane(*item_s);
+            __syncthreads();
+            if (local >= B.n_items) return;
+            const int item = B.item_begin + local;
+            e = B.item_event[item];
+            agent0 = B.item_agent0[item];
+            lgG = max(0, B.item_lg[item] - (W - 1));
+        }
+        const BatchEvent E = SINGLE ? B.one : B.ev[e];
+        const int n = E.n;
+        const int G = 1 << lgG;
+        const int g = t & (G - 1);
+        const int agent = agent0 + g * W;  // the first of this thread's agents
+        // this thread's position within an odd slot (a wave keeps its lanes'
+        // groups as long as a group fits a wave), and the position of slot s
+        const int t_odd = G <= 64 ? (nwaves - 1 - wave) * 64 + (t & 63) : t;
+        auto place = [&](int s) -> int { return s * T + (s & 1 ? t_odd : t); };
+        // the agents that thread `t` (t < G) reports energies and stamps of
+        auto reports = [&](int w) -> bool { return (t < G) & (agent0 + t * W + w < B.M); };
+        const bool wave_reports = wave * 64 < G;
+        // when each agent's work starts and reaches each checkpoint (the
+        // device's constant-rate wall clock), for time-to-target
+        auto stamp = [&](int slot) {
+            if (!SINGLE && B.ckpt_clock && wave_reports)
+                for (int w = 0; w < W; ++w)
+                    put(reports(w),
+                        B.ckpt_clock + (static_cast<size_t>(e) * (B.n_ckpt + 1) + slot) * B.M + agent0 + t * W + w,
+                        static_cast<long long>(wall_clock64()), B.trash);
+        };
+        stamp(0);
+
+        float xr[S][W], yr[S][W], hr[S];
+        // held couplings: 16-bit forms are one word (address low, coupling
+        // high); FP32 a word each and two addresses per word
+        uint32_t cw[kHeld], ca[kWide ? (kHeld + 1) / 2 : 1];
+        int cnt[S];  // longest row of this wave per slot, up to the capacity
+        // tail lengths of the slots, 5 bits each: slots 0-5 in tp_lo, 6-8 in
+        // the low 15 bits of tp_hi, the tails' first entry above; the wave's
+        // longest per slot likewise in tm_lo, tm_hi
+        uint32_t tp_lo = 0, tp_hi = 0, tm_lo = 0, tm_hi = 0;
+        int tsum = 0, tbig = 0, act = 0;
+        // (the workgroup's LDS starts at address 0; launchers check it)
+        auto five = [](uint32_t lo, uint32_t hi, auto sc) -> int {
+            constexpr int s = decltype(sc)::value;
+            return static_cast<int>((s < 6 ? lo >> (5 * (s < 6 ? s : 0)) : hi >> (5 * (s < 6 ? 0 : s - 6))) & 31u);
+        };
+        // the spin of slot s and whether there is one (otherwise another's)
+        auto spin_at = [&](int s, bool &there) -> int {
+            const int q = place(s) >> lgG;
+            there = q < n;
+            return B.perm[E.row_off + min(q, n - 1)];
+        };
+        auto row_of = [&](int i, bool there, int &p0) -> int {  // length of the row, 0 without a spin
+            p0 = B.row_ptr[E.rp_off + i];
+            const int p1 = B.row_ptr[E.rp_off + i + 1];
+            return there ? p1 - p0 : 0;
+        };
+        auto address = [&](uint32_t colr) -> uint32_t {
+            return ((colr & (kColUpper - 1)) * G + g) * kScale;
+        };
+        auto coupling = [&](int p) -> uint32_t {
+            if constexpr (kWide)
+                return __float_as_uint(B.J32[p]);
+            else
+                return static_cast<uint32_t>(B.J16[p]) << 16;
+        };
+        auto self_of = [&](int s) -> uint32_t { return static_cast<uint32_t>(place(s)) * kScale; };
+        if constexpr (kWide) {
+#pragma unroll
+            for (int c = 0; c < (kHeld + 1) / 2; ++c) ca[c] = 0;
+        }
+        unrolled<S>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            constexpr int CAP = kCap[s], O = cap_before(s);
+            bool there;
+            int p0;
+            const int i = spin_at(s, there);
+            const int len = row_of(i, there, p0);
+            const float h = B.h[E.row_off + i];
+            hr[s] = there ? h : 0.0f;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const Philox4 r = philox4x32_10(static_cast<uint32_t>(i), static_cast<uint32_t>(agent + w),
+                                                static_cast<uint32_t>(E.event_id), 0u, B.seed_lo, B.seed_hi);
+                xr[s][w] = there ? philox_word_to_unit(r.v[0]) : 0.0f;
+                yr[s][w] = there ? philox_word_to_unit(r.v[1]) : 0.0f;
+            }
+            cnt[s] = wave_max_int(len < CAP ? len : CAP);
+#pragma unroll
+            for (int c = 0; c < CAP; ++c) {
+                uint32_t a = self_of(s), v = 0u;
+                if (c < cnt[s]) {
+                    const int p = c < len ? E.nz_off + p0 + c : 0;
+                    const uint32_t al = address(B.colr[p]), vl = coupling(p);
+                    a = c < len ? al : a;
+                    v = c < len ? vl : v;
+                }
+                if constexpr (kWide) {
+                    cw[O + c] = v;
+                    ca[(O + c) / 2] |= a << (16 * ((O + c) & 1));
+                } else {
+                    cw[O + c] = v | a;
+                }
+            }
+            const int tl = max(0, len - CAP);
+            tbig |= tl > 31 ? 1 : 0;
+            const uint32_t tl5 = static_cast<uint32_t>(min(tl, 31)), tm5 = static_cast<uint32_t>(wave_max_int(min(tl, 31)));
+            if constexpr (s < 6) {
+                tp_lo |= tl5 << (5 * s);
+                tm_lo |= tm5 << (5 * s);
+            } else {
+                tp_hi |= tl5 << (5 * (s - 6));
+                tm_hi |= tm5 << (5 * (s - 6));
+            }
+            tsum += tl;
+            act |= there ? 1 << s : 0;
+            lds_write<word>(static_cast<uint32_t>(place(s)) * kB, V::pack(xr[s]));
+        });
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) act |= __shfl_xor(act, off, 64);
+        int n_act = 32 - __builtin_clz(__builtin_amdgcn_readfirstlane(act) | 1);  // a prefix
+        int any_tail = wave_max_int(tsum);
+        // offsets of the tails by a block scan; an item whose tails do not
+        // fit, or that has more than 31 for one row, reads them from global
+        // memory.  The scan's scratch is the buffer no wave reads yet.
+        int *scan = reinterpret_cast<int *>(L::kRedInBuf ? smem + L::kBuf : smem + 2 * L::kBuf);
+        int t_total = 0, big_total = 0;
+        const int t_base = block_exclusive_scan(tsum, scan, t_total);
+        (void)block_exclusive_scan(tbig, scan, big_total);
+        constexpr int kTW = kWide ? 2 : 1;  // words per tail entry
+        const bool lds_tails = __builtin_amdgcn_readfirstlane(t_total) * kTW <= B.tail_cap &&
+                               __builtin_amdgcn_readfirstlane(big_total) == 0;
+        if (lds_tails && any_tail > 0) {
+            int o = t_base;
+            unrolled<S>([&](auto sc) {
+                constexpr int s = decltype(sc)::value;
+                const int most = five(tm_lo, tm_hi, sc), len = five(tp_lo, tp_hi, sc);
+                if (most > 0) {
+                    bool there;
+                    int p0;
+                    const int i = spin_at(s, there);
+                    (void)row_of(i, there, p0);
+                    for (int u = 0; u < most; ++u) {
+                        const bool mine = u < len;
+                        const int p = mine ? E.nz_off + p0 + kCap[s] + u : 0;
+                        const uint32_t a = address(B.colr[p]), v = coupling(p);
+                        const uint32_t at = mine ? L::kTails + 4u * kTW * (o + u) : L::kDump;
+                        if constexpr (kWide) {
+                            lds_write<uint32_t>(at, v);
+                            lds_write<uint32_t>(at + 4, a);
+                        } else {
+                            lds_write<uint32_t>(at, v | a);
+                        }
+                    }
+                    o += len;
+                }
+            });
+        }
+        tp_hi |= lds_tails ? static_cast<uint32_t>(t_base) << 15 : 0u;
+        __syncthreads();
+
+        const float c0 = uniform(SINGLE ? static_cast<float>(B.scal[0]) : B.c0[e]);
+        const float dt = B.dt, dta0 = B.dta0;
+        // the schedule a step ahead, as a vector load: a scalar one would
+        // make every wait for LDS values a wait for all of them
+        float gap_next = B.sched[0];
+        // LDS addresses of slots 0 and 1 in the first buffer, less whole slots
+        uint32_t own = static_cast<uint32_t>(t) * kB, own_odd = static_cast<uint32_t>(t_odd) * kB;
+        launder(own);
+        launder(own_odd);
+        int ck = 0;
+
+        // FP64 energy of the current state per agent (Eq. 13): out[w] is
+        // agent (agent0 + t * W + w)'s in threads t < G.  The sums run
+        // through the buffer that this step does not read.
+        auto agent_energy = [&](int buf, double (&out)[W]) {
+            double *red = L::kRedInBuf ? reinterpret_cast<double *>(smem + (buf ^ 1) * L::kBuf) : red_own;
+            double v[W] = {};
+            unrolled<S>([&](auto sc) {
+                constexpr int s = decltype(sc)::value;
+                if (s >= n_act) return;
+                bool there;
+                int p0;
+                const int i = spin_at(s, there);
+                const int len = row_of(i, there, p0);
+                const int most = wave_max_int(len);
+                const double a = B.a[E.row_off + i];
+                double er[W];
+                for (int w = 0; w < W; ++w) er[w] = a;
+                for (int u = 0; u < most; ++u) {
+                    const int p = u < len ? E.nz_off + p0 + u : 0;
+                    const int c = B.colr[p];
+                    const double b = B.b[p];
+                    const bool pair = (u < len) & ((c & kColUpper) != 0);
+                    const word x = lds_read<word>(static_cast<uint32_t>(buf) * L::kBuf +
+                                                  (pair ? (c & (kColUpper - 1)) * G + g : 0) * kB);
+                    unrolled<W>([&](auto wc) {
+                        constexpr int w = decltype(wc)::value;
+                        er[w] += (pair & (V::template get<w>(x) >= 0.0f)) ? b : 0.0;
+                    });
+                }
+                for (int w = 0; w < W; ++w) v[w] += (there & (xr[s][w] >= 0.0f)) ? er[w] : 0.0;
+            });
+            for (int w = 0; w < W; ++w) {
+                // lanes with equal t % G hold the same agents
+                for (int off = 32; off >= G; off >>= 1) v[w] += __shfl_xor(v[w], off, 64);
+                red[w * T + t] = v[w];
+            }
+            __syncthreads();
+            for (int w = 0; w < W; ++w) {
+                // group t: lane t of every wave when G <= 64; otherwise lane
+                // t % 64 of the waves whose first group is t rounded down to 64
+                double tot = 0.0;
+                if (wave_reports)
+                    for (int v2 = 0; v2 < nwaves; ++v2)
+                        if (G <= 64 || ((v2 * 64) & (G - 1)) == wave * 64)
+                            tot += red[w * T + v2 * 64 + (t & 63)];
+                out[w] = tot;
+            }
+            __syncthreads();
+        };
+
+        // One step reading buffer BUF and writing the other.
+        auto step = [&](auto bufc, int k) __attribute__((always_inline)) {
+            constexpr int BUF = decltype(bufc)::value;
+            constexpr uint32_t XO = BUF * L::kBuf, XN = (BUF ^ 1) * L::kBuf;
+            const float gap = gap_next;
+            gap_next = B.sched[min(k + 1, B.K - 1)];
+#pragma unroll
+            for (int c = 0; c < (kWide ? (kHeld + 1) / 2 : kHeld); ++c) launder(kWide ? ca[c] : cw[c]);
+            // (comparisons with the counts belong in the step, not in masks kept for it)
+#pragma unroll
+            for (int s = 0; s < S; ++s) launder_uniform(cnt[s]);
+            launder_uniform(n_act);
+            auto read = [&](uint32_t a16) __attribute__((always_inline)) -> word {
+                return lds_read<word>(kBytesHeld ? a16 + XO : a16);
+            };
+            // the 16-bit address of held coupling o as a byte address
+            auto addr_of = [&](auto oc) __attribute__((always_inline)) -> uint32_t {
+                constexpr int o = decltype(oc)::value;
+                const uint32_t wv = kWide ? ca[o / 2] : cw[o];
+                if constexpr (kBytesHeld) {
+                    return kWide && (o & 1) ? wv >> 16 : wv & 0xFFFFu;
+                } else {
+                    // position * bytes + buffer in one instruction
+                    uint32_t a;
+                    if constexpr (kWide && (o & 1))
+                        a = (wv >> 16) * kB + XO;
+                    else if constexpr (XO == 0)
+                        asm("v_mad_u32_u16 %0, %1, %2, 0" : "=v"(a) : "v"(wv), "n"(kB));
+                    else
+                        asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(a) : "v"(wv), "n"(kB), "s"(XO));
+                    return a;
+                }
+            };
+            auto value_of = [&](auto oc) __attribute__((always_inline)) -> float {
+                constexpr int o = decltype(oc)::value;
+                if constexpr (kWide)
+                    return __uint_as_float(cw[o]);
+                else if constexpr (JP == kJFp16)
+                    return static_cast<float>(__ushort_as_half(static_cast<uint16_t>(cw[o] >> 16)));
+                else
+                    return __uint_as_float(cw[o] & 0xFFFF0000u);
+            };
+            // couplings [C0, C1) of slot s, all gathers in flight at once
+            auto load = [&](auto sc, auto c0c, auto c1c, word *v) __attribute__((always_inline)) {
+                constexpr int O = cap_before(decltype(sc)::value), C0 = decltype(c0c)::value;
+                unrolled<decltype(c1c)::value - C0>([&](auto uc) __attribute__((always_inline)) {
+                    constexpr int u = decltype(uc)::value;
+                    v[u] = read(addr_of(std::integral_constant<int, O + C0 + u>{}));
+                });
+            };
+            auto add = [&](auto sc, auto c0c, auto c1c, const word *v, float (&acc)[W])
+                           __attribute__((always_inline)) {
+                constexpr int O = cap_before(decltype(sc)::value), C0 = decltype(c0c)::value;
+                unrolled<decltype(c1c)::value - C0>([&](auto uc) __attribute__((always_inline)) {
+                    constexpr int u = decltype(uc)::value;
+                    const float jv = value_of(std::integral_constant<int, O + C0 + u>{});
+                    unrolled<W>([&](auto wc) __attribute__((always_inline)) {
+                        constexpr int w = decltype(wc)::value;
+                        acc[w] = __builtin_fmaf(jv, V::template get<w>(v[u]), acc[w]);
+                    });
+                });
+            };
+            using std::integral_constant;
+            // the first couplings of a slot are gathered while the slot
+            // before it is summed
+            word base[2][kAhead];
+            load(integral_constant<int, 0>{}, integral_constant<int, 0>{}, integral_constant<int, ahead(0)>{},
+                 base[0]);
+            unrolled<S>([&](auto sc) __attribute__((always_inline)) {
+                constexpr int s = decltype(sc)::value;
+                if (s >= n_act) return;
+                constexpr int CAP = kCap[s];
+                float acc[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) acc[w] = hr[s];
+                // couplings [kAhead, C) of this slot and the next slot's
+                // first, in flight together; one straight run per length class
+                auto row = [&](auto cc) __attribute__((always_inline)) {
+                    constexpr int C = decltype(cc)::value;
+                    word v[C > ahead(s) ? C - ahead(s) : 1];
+                    if constexpr (C > ahead(s)) load(sc, integral_constant<int, ahead(s)>{}, cc, v);
+                    if constexpr (s + 1 < S)
+                        load(integral_constant<int, s + 1>{}, integral_constant<int, 0>{},
+                             integral_constant<int, ahead(s + 1)>{}, base[(s + 1) & 1]);
+                    add(sc, integral_constant<int, 0>{}, integral_constant<int, ahead(s)>{}, base[s & 1], acc);
+                    if constexpr (C > ahead(s)) add(sc, integral_constant<int, ahead(s)>{}, cc, v, acc);
+                    // (distinct per class, or the classes' ends are merged
+                    // at the price of a copy per operand)
+#pragma unroll
+                    for (int w = 0; w < W; ++w) asm volatile("; slot %1 class %2" : "+v"(acc[w]) : "n"(s), "n"(C));
+                };
+                if constexpr (CAP <= 2) {
+                    row(integral_constant<int, CAP>{});
+                } else if constexpr (CAP <= 4) {
+                    if (cnt[s] <= 2)
+                        row(integral_constant<int, 2>{});
+                    else
+                        row(integral_constant<int, CAP>{});
+                } else if constexpr (CAP <= 8) {
+                    if (cnt[s] <= 2)
+                        row(integral_constant<int, 2>{});
+                    else if (cnt[s] <= 4)
+                        row(integral_constant<int, 4>{});
+                    else
+                        row(integral_constant<int, CAP>{});
+                } else {
+                    if (cnt[s] <= 2)
+                        row(integral_constant<int, 2>{});
+                    else if (cnt[s] <= 4)
+                        row(integral_constant<int, 4>{});
+                    else if (cnt[s] <= 8)
+                        row(integral_constant<int, 8>{});
+                    else
+                        row(integral_constant<int, CAP>{});
+                }
+                launder_uniform(any_tail);
+                if (__builtin_expect(any_tail, 0)) {
+                    // CSR order within the row, after the held couplings;
+                    // lanes past their row's end add a zero coupling
+                    const uint32_t self = self_of(s);
+                    auto tail_word = [&](uint32_t a16) __attribute__((always_inline)) -> word {
+                        return lds_read<word>((kBytesHeld ? a16 : a16 * kB) + XO);
+                    };
+                    auto tail_add = [&](uint32_t v, word x) __attribute__((always_inline)) {
+                        float jv;
+                        if constexpr (JP == kJFp16)
+                            jv = static_cast<float>(__ushort_as_half(static_cast<uint16_t>(v >> 16)));
+                        else
+                            jv = __uint_as_float(kWide ? v : v & 0xFFFF0000u);
+                        unrolled<W>([&](auto wc) {
+                            constexpr int w = decltype(wc)::value;
+                            acc[w] = __builtin_fmaf(jv, V::template get<w>(x), acc[w]);
+                        });
+                    };
+                    if (lds_tails) {
+                        int o = static_cast<int>(tp_hi >> 15);
+                        unrolled<s>([&](auto bc) { o += five(tp_lo, tp_hi, bc); });
+                        const int len = five(tp_lo, tp_hi, sc), most = five(tm_lo, tm_hi, sc);
+                        // four at a time, so that a wave with long rows waits
+                        // twice for the LDS per four couplings
+                        constexpr int U = 4;
+                        for (int u0 = 0; u0 < most; u0 += U) {
+                            uint32_t tw[U], a16[U];
+                            word x[U];
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const uint32_t at = u0 + u < len ? L::kTails + 4u * kTW * (o + u0 + u) : L::kDump;
+                                tw[u] = lds_read<uint32_t>(at);
+                                if constexpr (kWide) a16[u] = lds_read<uint32_t>(at + 4);
+                            }
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const bool mine = u0 + u < len;
+                                if constexpr (kWide) {
+                                    tw[u] = mine ? tw[u] : 0u;
+                                    a16[u] = mine ? a16[u] : self;
+                                } else {
+                                    tw[u] = mine ? tw[u] : self;
+                                    a16[u] = tw[u] & 0xFFFFu;
+                                }
+                                x[u] = tail_word(a16[u]);
+                            }
+#pragma unroll
+                            for (int u = 0; u < U; ++u) tail_add(tw[u], x[u]);
+                        }
+                    } else {
+                        bool there;
+                        int p0;
+                        const int i = spin_at(s, there);
+                        const int len = row_of(i, there, p0), most = wave_max_int(len);
+                        for (int u = CAP; u < most; ++u) {
+                            const bool mine = u < len;
+                            const int p = mine ? E.nz_off + p0 + u : 0;
+                            const uint32_t v = coupling(p), a = address(B.colr[p]);
+                            tail_add(mine ? v : 0u, tail_word(mine ? a : self));
+                        }
+                    }
+                }
+#pragma unroll
+                for (int w = 0; w < W; ++w) rows_step<MODE>(xr[s][w], yr[s][w], acc[w], c0, gap, dt, dta0);
+                lds_write<word>((s & 1 ? own_odd : own) + (XN + static_cast<uint32_t>(s * T) * kB), V::pack(xr[s]));
+            });
+            sync();
+        };
+        // steps in runs between checkpoints; the buffer read at step k is k & 1
+        int k = 0;
+        while (k < B.K) {
+            const int kend = B.ckpt_every > 0 ? min(B.K, k - k % B.ckpt_every + B.ckpt_every) : B.K;
+            if (k & 1) step(std::integral_constant<int, 1>{}, k++);
+            for (; k + 1 < kend; k += 2) {
+                step(std::integral_constant<int, 0>{}, k);
+                step(std::integral_constant<int, 1>{}, k + 1);
+            }
+            if (k < kend) step(std::integral_constant<int, 0>{}, k++);
+            if (B.ckpt_every > 0 && k % B.ckpt_every == 0) {
+                double en[W];
+                agent_energy(k & 1, en);
+                if (wave_reports)
+                    for (int w = 0; w < W; ++w)
+                        put(reports(w), B.etrace + (static_cast<size_t>(e) * B.n_ckpt + ck) * B.M + agent0 + t * W + w,
+                            en[w], B.trash);
+                stamp(ck + 1);
+                ++ck;
+                // target mode: the event's work stops at the first
+                // checkpoint where one of its agents (of this item or,
+                // through the event's flag, of another) reaches the target
+                if (!SINGLE && B.target) {
+                    // (an OR over the workgroup through the item word)
+                    bool hit = false;
+                    for (int w = 0; w < W; ++w) hit |= reports(w) & (en[w] <= B.target[e]);
+                    if (wave == 0) *item_s = 0;
+                    __syncthreads();
+                    if (__ballot(hit)) *item_s = 1;
+                    __syncthreads();
+                    if (wave == 0) {
+                        const int any = __builtin_amdgcn_readfirstlane(*item_s);
+                        if (any)
+                            __hip_atomic_store(B.done + e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        *item_s = any | __hip_atomic_load(B.done + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    __syncthreads();
+                    const bool stop = __builtin_amdgcn_readfirstlane(*item_s) != 0;
+                    __syncthreads();
+                    if (stop) break;
+                }
+            }
+        }
+        // checkpoints a target stop skipped read NaN (no state was reached)
+        if (wave_reports)
+            for (int c = ck; c < B.n_ckpt; ++c)
+                for (int w = 0; w < W; ++w) {
+                    put(reports(w), B.etrace + (static_cast<size_t>(e) * B.n_ckpt + c) * B.M + agent0 + t * W + w,
+                        static_cast<double>(NAN), B.trash);
+                    if (B.ckpt_clock)
+                        put(reports(w),
+                            B.ckpt_clock + (static_cast<size_t>(e) * (B.n_ckpt + 1) + c + 1) * B.M + agent0 + t * W + w,
+                            0ll, B.trash);
+                }
+        {
+            double en[W];
+            agent_energy(k & 1, en);
+            if (wave_reports)
+                for (int w = 0; w < W; ++w)
+                    put(reports(w), B.energy + static_cast<size_t>(e) * B.M + agent0 + t * W + w, en[w], B.trash);
+        }
+        unrolled<S>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            if (s >= n_act) return;
+            bool there;
+            const int i = spin_at(s, there);
+            const size_t o = (static_cast<size_t>(E.row_off) + i) * B.M + agent;
+            for (int w = 0; w < W; ++w) {
+                const bool mine = there & (agent + w < B.M);
+                put(mine, B.T + o + w, static_cast<int8_t>(xr[s][w] >= 0.0f ? 1 : 0), B.trash);
+                if (B.x_out) put(mine, B.x_out + o + w, xr[s][w], B.trash);
+                if (SINGLE && B.y_out) put(mine, B.y_out + o + w, yr[s][w], B.trash);
+            }
+        });
+        __syncthreads();
+    }
+}
+
+}  // namespace sbt

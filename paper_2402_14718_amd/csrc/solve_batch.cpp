@@ -24,7 +24,7 @@ struct Schedule {
     std::vector<sbt::BatchEvent> ev;
     // items of the 1024-thread launch first, then those of the 512-thread
     // launch, each group in decreasing-cost order
-    std::vector<int32_t> item_event, item_agent0;
+    std::vector<int32_t> item_event, item_agent0, item_lg;
     int n_large = 0, n_small = 0;  // items per launch
     int64_t sum_n = 0, sum_nnz = 0;
     // events above the band limit: one gang of row bands per agent
@@ -37,15 +37,26 @@ struct Schedule {
 
 int tpb_of(bool small) { return small ? sbt::kBatchTPBSmall : sbt::kBatchTPB; }
 
-// Agents per work item: the largest power of two A with n * A within
-// `fill` of the shape's slots (and A <= agents, A <= its threads); at least
-// one agent.
+// Agents per work item: the largest power of two A with n * A / 2 (two
+// agents share a slot) within `fill` of the shape's slots (and A <= agents,
+// A / 2 <= its threads); at least one agent, two where the event has them.
 int lg_agents_for(int32_t n, int32_t M, int tpb, double fill) {
-    const double cap = fill * tpb * sbt::kBatchSPT;
-    int lg = 0;
-    while ((2 << lg) <= M && (2 << lg) <= tpb && static_cast<double>(n) * (2 << lg) <= cap) ++lg;
+    const double cap = fill * tpb * sbt::kBatchSPT * sbt::kBatchAgents;
+    int lg = M >= sbt::kBatchAgents ? 1 : 0;
+    static_assert(sbt::kBatchAgents == 2, "lg counts pairs");
+    while ((2 << lg) <= M && (1 << lg) <= tpb && static_cast<double>(n) * (2 << lg) <= cap) ++lg;
     return lg;
 }
+
+// A shape's workgroups run side by side (one per CU, or two of the small
+// shape), so few large items leave some of them idle at the end: an item is
+// kept to a sixth of a workgroup's share of the launch, but no smaller than
+// a quarter of the slots, below which a step's fixed cost (its barrier and
+// one LDS round trip) outweighs the work.  Measured, 96 events of 20-400
+// particles x 100 agents (bSB): full items 7.3 ms, half 6.0, quarter 6.2.
+constexpr double kCUs = 256;  // (a constant: plan and run must agree)
+constexpr int kItemsPerGroup = 6;
+constexpr double kLeastFill = 0.25;
 
 int check_tuning(const sbt_batch_tuning &t, const char *who) {
     if (t.split_n < 0) return fail(SBT_EINVAL, "%s: tuning split_n must be >= 0", who);
@@ -73,9 +84,20 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
     S.ev.resize(E);
     struct Item {
         int64_t cost;
-        int32_t e, a0;
+        int32_t e, a0, lg;
     };
     std::vector<Item> items[2];  // [0]: 1024-thread shape, [1]: 512-thread shape
+    // split_n = 0: every event that fits it on the 512-thread shape, whose
+    // two workgroups per CU hide each other's barriers (512 events x 128
+    // agents, dSB BF16: VALU busy 0.79 against 0.66 on the 1024-thread shape)
+    const int32_t split = tu.split_n > 0 ? tu.split_n : sbt::kBatchSlotsSmall;
+    double share[2] = {0.0, 0.0};  // largest cost of an item
+    for (int32_t e = 0; e < E; ++e)
+        if (n[e] > 0 && nnz[e] >= 0)
+            share[n[e] <= split && n[e] <= sbt::kBatchSlotsSmall ? 1 : 0] +=
+                (static_cast<double>(n[e]) + static_cast<double>(nnz[e])) * p.agents;
+    share[0] /= kItemsPerGroup * kCUs;
+    share[1] /= kItemsPerGroup * 2.0 * kCUs;
     const int band_limit = tu.band_rows > 0 ? tu.band_rows : sbt::kBatchSlots;
     const int n_ckpt = p.energy_every > 0 ? p.steps / p.energy_every : 0;
     S.gangs.clear();
@@ -86,14 +108,13 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
     for (int32_t e = 0; e < E; ++e) {
         if (n[e] < 1) return fail(SBT_EINVAL, "%s: event %d has n = %d", who, e, n[e]);
         if (nnz[e] < 0) return fail(SBT_EINVAL, "%s: event %d has nnz < 0", who, e);
-        const bool small = n[e] <= tu.split_n && n[e] <= sbt::kBatchSlotsSmall;
+        const bool small = n[e] <= split && n[e] <= sbt::kBatchSlotsSmall;
         sbt::BatchEvent &d = S.ev[e];
         d.n = n[e];
         d.nnz = static_cast<int>(nnz[e]);
         d.row_off = static_cast<int>(row_off);
         d.rp_off = static_cast<int>(row_off + e);
         d.nz_off = static_cast<int>(nz_off);
-        d.lg_agents = lg_agents_for(n[e], p.agents, tpb_of(small), tu.fill);
         d.event_id = same_start ? p.event : p.event + e;
         d.c0_scale = c0_scale ? static_cast<float>(c0_scale[e]) : 1.0f;
         if (n[e] > band_limit) {
@@ -117,10 +138,18 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
             if (S.part_entries > INT32_MAX / 2)
                 return fail(SBT_EINVAL, "%s: too many row bands for 32-bit offsets", who);
         } else {
-            const int A = 1 << d.lg_agents;
-            for (int a0 = 0; a0 < p.agents; a0 += A) {
-                const int used = std::min(A, p.agents - a0);
-                items[small ? 1 : 0].push_back({(static_cast<int64_t>(n[e]) + nnz[e]) * used, e, a0});
+            const int64_t cost = static_cast<int64_t>(n[e]) + nnz[e];
+            int lg = lg_agents_for(n[e], p.agents, tpb_of(small), tu.fill);
+            while (lg > 1 && static_cast<double>(cost) * (1 << lg) > share[small ? 1 : 0] &&
+                   static_cast<double>(n[e]) * (1 << (lg - 1)) >
+                       kLeastFill * tpb_of(small) * sbt::kBatchSPT * sbt::kBatchAgents)
+                --lg;
+            for (int a0 = 0; a0 < p.agents;) {
+                // (the last items of an odd number of agents are smaller)
+                while (lg > 1 && (1 << lg) > p.agents - a0) --lg;
+                const int used = std::min(1 << lg, p.agents - a0);
+                items[small ? 1 : 0].push_back({cost * used, e, a0, lg});
+                a0 += used;
             }
         }
         row_off += n[e];
@@ -130,6 +159,7 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
     }
     S.item_event.clear();
     S.item_agent0.clear();
+    S.item_lg.clear();
     for (auto &v : items) {
         // longest items first (ties: event, then agent order)
         std::stable_sort(v.begin(), v.end(),
@@ -137,6 +167,7 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
         for (const Item &it : v) {
             S.item_event.push_back(it.e);
             S.item_agent0.push_back(it.a0);
+            S.item_lg.push_back(it.lg);
         }
     }
     S.n_large = static_cast<int>(items[0].size());
@@ -163,7 +194,7 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
 }
 
 struct BatchLayout {
-    size_t ev, item_e, item_a, J16, h, c0, offset, perm, sched, counter, etrace, energy, T;
+    size_t ev, item_e, item_a, item_lg, J16, colr, h, c0, offset, perm, rank, sched, counter, trash, etrace, energy, T;
     size_t gangs, gitem_g, gitem_b, xg, gints, gpart, gclock, done;
     size_t total;
     int n_ckpt;
@@ -182,13 +213,17 @@ BatchLayout make_layout(const Schedule &S, const sbt_solve_params &p) {
     L.ev = take(sizeof(sbt::BatchEvent) * E);
     L.item_e = take(sizeof(int32_t) * I);
     L.item_a = take(sizeof(int32_t) * I);
+    L.item_lg = take(sizeof(int32_t) * I);
     L.J16 = take(sizeof(uint16_t) * static_cast<size_t>(S.sum_nnz));
+    L.colr = take(sizeof(uint16_t) * static_cast<size_t>(S.sum_nnz));
     L.h = take(sizeof(float) * static_cast<size_t>(S.sum_n));
     L.c0 = take(sizeof(float) * E);
     L.offset = take(sizeof(double) * E);
     L.perm = take(sizeof(int32_t) * static_cast<size_t>(S.sum_n));
+    L.rank = take(sizeof(int32_t) * static_cast<size_t>(S.sum_n));
     L.sched = take(sizeof(float) * static_cast<size_t>(p.steps));
     L.counter = take(2 * sizeof(int32_t));  // one per launch
+    L.trash = take(64);
     L.etrace = take(sizeof(double) * E * static_cast<size_t>(L.n_ckpt) * M);
     L.energy = take(sizeof(double) * E * M);
     L.T = take(static_cast<size_t>(S.sum_n) * M);
@@ -295,6 +330,8 @@ extern "C" int sbt_batch_plan_tuned(const int32_t *n, const int64_t *nnz, int32_
                            hipMemcpyHostToDevice, st));
     SBT_HIP(hipMemcpyAsync(ws + L.item_a, S.item_agent0.data(),
                            sizeof(int32_t) * S.item_agent0.size(), hipMemcpyHostToDevice, st));
+    SBT_HIP(hipMemcpyAsync(ws + L.item_lg, S.item_lg.data(), sizeof(int32_t) * S.item_lg.size(),
+                           hipMemcpyHostToDevice, st));
     if (!S.gangs.empty()) {
         if (S.max_bands > cu_count())
             return fail(SBT_EUNSUPPORTED, "%s: an event needs %d row bands at once, more than the "
@@ -363,6 +400,7 @@ extern "C" int sbt_batch_run_tuned(const sbt_dev_batch *batch, sbt_mode mode, sb
     B.ev = reinterpret_cast<const sbt::BatchEvent *>(ws + L.ev);
     B.item_event = reinterpret_cast<const int *>(ws + L.item_e);
     B.item_agent0 = reinterpret_cast<const int *>(ws + L.item_a);
+    B.item_lg = reinterpret_cast<const int *>(ws + L.item_lg);
     B.row_ptr = batch->row_ptr;
     B.col = batch->col;
     B.a = batch->a;
@@ -372,7 +410,10 @@ extern "C" int sbt_batch_run_tuned(const sbt_dev_batch *batch, sbt_mode mode, sb
     B.c0 = reinterpret_cast<float *>(ws + L.c0);
     B.offset = out->offset ? out->offset : reinterpret_cast<double *>(ws + L.offset);
     B.perm = reinterpret_cast<int *>(ws + L.perm);
+    B.rank = reinterpret_cast<int *>(ws + L.rank);
+    B.colr = reinterpret_cast<uint16_t *>(ws + L.colr);
     B.sched = reinterpret_cast<const float *>(ws + L.sched);
+    B.trash = ws + L.trash;
     B.etrace = reinterpret_cast<double *>(ws + L.etrace);
     B.energy = out->agent_energy ? out->agent_energy : reinterpret_cast<double *>(ws + L.energy);
     B.trace = out->trace;
