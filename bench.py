@@ -725,9 +725,9 @@ def plain_form(sbt, tg, torch, q, kernel_choice, warmup, steps, with_ttt=True):
                 "unit": "TFLOP/s", "frac": achieved / MI355X_FP32_VECTOR_TFLOPS,
                 "peak_without_packed_fp32": MI355X_FP32_UNPACKED_TFLOPS,
                 "frac_without_packed_fp32": achieved / MI355X_FP32_UNPACKED_TFLOPS,
-                "traffic": measured_traffic("sb_resident_reg_plain.md"),
-                "lds": measured_lds("sb_resident_reg_plain.md"),
-                "kernel": "sb_resident_reg", "launch_ms": launch_s * 1e3,
+                "traffic": measured_traffic("sb_resident_rows_plain.md"),
+                "lds": measured_lds("sb_resident_rows_plain.md"),
+                "kernel": "sb_resident_rows", "launch_ms": launch_s * 1e3,
                 "state_bytes_if_streamed_GBs": bytes_ / launch_s / 1e9}
     else:
         achieved = bytes_ / launch_s / 1e9

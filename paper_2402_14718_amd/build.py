@@ -27,17 +27,17 @@ ARCH = "gfx950"
 HOST_SOURCES = ["status.cpp", "validate.cpp", "build_qubo.cpp", "order.cpp", "anneal.cpp",
                 "batch_tuning.cpp"]
 RUNTIME_SOURCES = ["solve.cpp", "solve_batch.cpp"]
-HIP_SOURCES = ["sb_kernels.hip", "sb_resident_reg.hip", "sb_resident_reg_bsb.hip",
-               "sb_resident_reg_dsb.hip", "sb_resident_reg_asb.hip", "sb_batch.hip",
-               "sb_stream.hip", "build_qubo_gpu.hip", "solve_noalloc.hip", "sb_batch_gang.hip",
+HIP_SOURCES = ["sb_kernels.hip", "sb_batch.hip", "sb_stream.hip", "build_qubo_gpu.hip", "solve_noalloc.hip", "sb_batch_gang.hip",
                "sb_stream_tile.hip", "topk.hip", "sb_stream_quad.hip", "sb_stream_mfma.hip"]
 # one source built several times: (source, object tag, extra flags) -- the
-# batched step kernel once per (mode, coupling format, workgroup shape), in
-# parallel
+# batched step kernel once per (mode, coupling format, workgroup shape), the
+# resident kernel once per mode, in parallel
 HIP_VARIANTS = [("sb_batch_mode.hip", f"{m}_{j}_{tpb}",
                  [f"-DSBT_BATCH_MODE={mi}", f"-DSBT_BATCH_JP={ji}", f"-DSBT_BATCH_TPB={tpb}"])
                 for mi, m in enumerate(("bsb", "dsb", "asb")) for ji, j in enumerate(("fp16", "bf16"))
                 for tpb in (1024, 512)]
+HIP_VARIANTS += [("sb_resident_mode.hip", m, [f"-DSBT_RESIDENT_MODE={mi}"])
+                 for mi, m in enumerate(("bsb", "dsb", "asb"))]
 # the GPU QUBO builder evaluates the host builder's cut expressions: no
 # floating-point contraction, like the host file
 HIP_EXTRA_FLAGS = {"build_qubo_gpu.hip": ["-ffp-contract=off"]}

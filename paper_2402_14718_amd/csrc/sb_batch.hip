@@ -12,12 +12,74 @@
 
 namespace sbt {
 
+constexpr int kLenBins = 64;  // row lengths 0..62 and "63 or more"
+
+// perm[0..n) = spins by decreasing min(row length, 63), ascending id within a
+// length; rank its inverse.  One workgroup (whole waves); bins: kLenBins
+// ints per wave.  Each wave counts and then places one run of consecutive
+// spins, so the order does not depend on timing.
+__device__ __forceinline__ void rank_rows(int n, const int *row_ptr, int *perm, int *rank, int *bins) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, nw = static_cast<int>(blockDim.x) >> 6;
+    const int run = ((n + nw - 1) / nw + 63) / 64 * 64;  // spins per wave
+    const int i0 = min(n, wave * run), i1 = min(n, i0 + run);
+    int *mine = bins + wave * kLenBins;
+    mine[lane] = 0;
+    auto bin_of = [&](int i) { return kLenBins - 1 - min(row_ptr[i + 1] - row_ptr[i], kLenBins - 1); };
+    __syncthreads();
+    for (int i = i0 + lane; i < i1; i += 64) atomicAdd(mine + bin_of(i), 1);
+    __syncthreads();
+    // exclusive prefix sums over (bin, wave); lane b of wave 0 takes bin b
+    if (wave == 0) {
+        int tot = 0;
+        for (int w = 0; w < nw; ++w) tot += bins[w * kLenBins + lane];
+        int at = tot;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __shfl_up(at, off, 64);
+            if (lane >= off) at += v;
+        }
+        at -= tot;
+        for (int w = 0; w < nw; ++w) {
+            const int c = bins[w * kLenBins + lane];
+            bins[w * kLenBins + lane] = at;
+            at += c;
+        }
+    }
+    __syncthreads();
+    for (int g = i0; g < i1; g += 64) {
+        const int i = g + lane;
+        const bool in = i < i1;
+        const int b = in ? bin_of(i) : 0;
+        uint64_t same = __ballot(in);  // this group's spins of the same length
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const uint64_t has = __ballot(in && ((b >> k) & 1));
+            same &= ((b >> k) & 1) ? has : ~has;
+        }
+        const int below = __popcll(same & ((uint64_t(1) << lane) - 1));
+        const int base = in ? mine[b] : 0;
+        __builtin_amdgcn_wave_barrier();
+        if (in) {
+            if (below == 0) mine[b] = base + __popcll(same);
+            perm[base + below] = i;
+            rank[i] = base + below;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+}
+
+// A column as its rank, bit 15: it is above the row.
+__device__ __forceinline__ uint16_t column_rank(const int *rank, int row, int col) {
+    return static_cast<uint16_t>(rank[col] | (col > row ? 0x8000 : 0));
+}
+
 // Per-event preparation, one workgroup per event: FP32 field h, 16-bit
 // couplings J = -b/4, c0 and the Ising offset C (FP64, fixed order), and
 // the spin order by decreasing row length.
 __global__ __launch_bounds__(256) void batch_prep(BatchArgs B, int jprec) {
     __shared__ double red[4];
-    __shared__ int wave_tot[4];
+    __shared__ int bins[4 * kLenBins];
     const int e = blockIdx.x;
     const BatchEvent E = B.ev[e];
     const int t = threadIdx.x;
@@ -59,58 +121,106 @@ __global__ __launch_bounds__(256) void batch_prep(BatchArgs B, int jprec) {
         B.c0[e] = static_cast<float>(c0 * static_cast<double>(E.c0_scale));
         B.offset[e] = 0.5 * t3 + 0.25 * t2;
     }
-    // spin order: decreasing min(row length, 63), ascending id within a length
-    const int lane = t & 63, wave = t >> 6;
-    int base = 0;
-    for (int cls = 63; cls >= 0; --cls) {
-        for (int c0i = 0; c0i < E.n; c0i += 256) {
-            const int i = c0i + t;
-            bool f = false;
-            if (i < E.n) {
-                const int len = B.row_ptr[E.rp_off + i + 1] - B.row_ptr[E.rp_off + i];
-                f = min(len, 63) == cls;
-            }
-            const uint64_t bal = __ballot(f);
-            const int below = __popcll(bal & ((uint64_t(1) << lane) - 1));
-            if (lane == 0) wave_tot[wave] = __popcll(bal);
-            __syncthreads();
-            int woff = 0, tot = 0;
-            for (int w = 0; w < 4; ++w) {
-                woff += (w < wave) ? wave_tot[w] : 0;
-                tot += wave_tot[w];
-            }
-            if (f) {
-                B.perm[E.row_off + base + woff + below] = i;
-                B.rank[E.row_off + i] = base + woff + below;
-            }
-            base += tot;
-            __syncthreads();
-        }
-    }
+    if (E.n > kBatchSlots) return;  // (a gang: it needs no spin order)
+    rank_rows(E.n, B.row_ptr + E.rp_off, B.perm + E.row_off, B.rank + E.row_off, bins);
     // columns as ranks, for the step kernel's LDS addresses
-    if (E.n <= kBatchSlots)
-        for (int i = t; i < E.n; i += 256)
-            for (int p = B.row_ptr[E.rp_off + i]; p < B.row_ptr[E.rp_off + i + 1]; ++p) {
-                const int c = B.col[E.nz_off + p];
-                B.colr[E.nz_off + p] =
-                    static_cast<uint16_t>(B.rank[E.row_off + c] | (c > i ? 0x8000 : 0));
-            }
+    for (int i = t; i < E.n; i += 256)
+        for (int p = B.row_ptr[E.rp_off + i]; p < B.row_ptr[E.rp_off + i + 1]; ++p)
+            B.colr[E.nz_off + p] = column_rank(B.rank + E.row_off, i, B.col[E.nz_off + p]);
+}
+
+__global__ __launch_bounds__(1024) void rank_spins(int n, const int *__restrict__ row_ptr,
+                                                   int *__restrict__ perm, int *__restrict__ rank) {
+    __shared__ int bins[16 * kLenBins];
+    rank_rows(n, row_ptr, perm, rank, bins);
+}
+
+__global__ __launch_bounds__(256) void rank_columns(int n, const int *__restrict__ row_ptr,
+                                                    const int *__restrict__ col,
+                                                    const int *__restrict__ rank,
+                                                    uint16_t *__restrict__ colr) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    for (int p = row_ptr[i]; p < row_ptr[i + 1]; ++p) colr[p] = column_rank(rank, i, col[p]);
 }
 
 __global__ void batch_reset(int *counters, int n) {
     if (static_cast<int>(threadIdx.x) < n) counters[threadIdx.x] = 0;
 }
 
+// Final FP64 O(T) of every agent (Eq. 13), from the assignments: a workgroup
+// sums kEnergyChunk rows of one event for 64 agents, one lane each.  Its order
+// depends on nothing but the event, so agents with the same T have the same
+// energy under every schedule (the best agent is the lowest of a tie).
+// Four rows of a wave are in flight together: each is a chain of loads.
+__global__ __launch_bounds__(1024) void batch_energy(BatchArgs B) {
+    constexpr int kWaves = 16, kPer = kEnergyChunk / kWaves, R = 4;
+    __shared__ double sum[kWaves][64];
+    const int e = blockIdx.z;
+    const BatchEvent E = B.ev[e];
+    const int lo = blockIdx.x * kEnergyChunk;
+    if (E.gang || lo >= E.n) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int m = blockIdx.y * 64 + lane, mc = min(m, B.M - 1);
+    const int8_t *T = B.T + static_cast<size_t>(E.row_off) * B.M + mc;
+    const int *rp = B.row_ptr + E.rp_off, *col = B.col + E.nz_off;
+    const double *a = B.a + E.row_off, *b = B.b + E.nz_off;
+    double tot = 0.0;
+    for (int u = 0; u < kPer; u += R) {
+        double er[R];
+        int p[R], q[R];
+        bool on[R];
+        int most = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = lo + wave * kPer + u + r, ic = min(i, E.n - 1);
+            p[r] = rp[ic];
+            q[r] = i < E.n ? rp[ic + 1] : p[r];
+            er[r] = a[ic];
+            on[r] = i < E.n && T[static_cast<size_t>(ic) * B.M] != 0;
+            most = max(most, q[r] - p[r]);
+        }
+        for (int k = 0; k < most; ++k) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (k >= q[r] - p[r]) continue;  // (uniform: a row is a wave's)
+                const int i = lo + wave * kPer + u + r, c = col[p[r] + k];
+                const double bv = b[p[r] + k];
+                if (c > i && T[static_cast<size_t>(c) * B.M] != 0) er[r] += bv;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) tot += on[r] ? er[r] : 0.0;
+    }
+    sum[wave][lane] = tot;
+    __syncthreads();
+    if (wave == 0 && m < B.M) {
+        double v = 0.0;
+        for (int w = 0; w < kWaves; ++w) v += sum[w][lane];
+        B.epart[(static_cast<size_t>(e) * B.n_chunks + blockIdx.x) * B.M + m] = v;
+    }
+}
+
+// The parts of an agent's energy, in order.
+__device__ __forceinline__ double agent_total(const BatchArgs &B, const BatchEvent &E, int e, int m) {
+    double v = 0.0;
+    for (int c = 0; c * kEnergyChunk < E.n; ++c) v += B.epart[(static_cast<size_t>(e) * B.n_chunks + c) * B.M + m];
+    return v;
+}
+
+constexpr int kSelect = 256;
+
 // Per event: best agent (minimum energy, lowest index on ties), its T,
 // and the best-so-far trace over checkpoints.
-__global__ __launch_bounds__(256) void batch_select(BatchArgs B) {
-    __shared__ double se[256];
-    __shared__ int sm[256];
+__global__ __launch_bounds__(kSelect) void batch_select(BatchArgs B) {
+    __shared__ double se[kSelect];
+    __shared__ int sm[kSelect];
     const int e = blockIdx.x, t = threadIdx.x;
     const BatchEvent E = B.ev[e];
     double be = INFINITY;
     int bm = 0x7fffffff;
-    for (int m = t; m < B.M; m += 256) {
+    for (int m = t; m < B.M; m += kSelect) {
+        if (!E.gang) B.energy[static_cast<size_t>(e) * B.M + m] = agent_total(B, E, e, m);
         const double v = B.energy[static_cast<size_t>(e) * B.M + m];
         if (v < be || (v == be && m < bm)) {
             be = v;
@@ -120,7 +230,7 @@ __global__ __launch_bounds__(256) void batch_select(BatchArgs B) {
     se[t] = be;
     sm[t] = bm;
     __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
+    for (int w = kSelect / 2; w >= 1; w >>= 1) {
         if (t < w && (se[t + w] < se[t] || (se[t + w] == se[t] && sm[t + w] < sm[t]))) {
             se[t] = se[t + w];
             sm[t] = sm[t + w];
@@ -133,17 +243,17 @@ __global__ __launch_bounds__(256) void batch_select(BatchArgs B) {
         B.best_agent[e] = best;
     }
     if (best >= 0 && best < B.M)
-        for (int i = t; i < E.n; i += 256)
+        for (int i = t; i < E.n; i += kSelect)
             B.best_T[E.row_off + i] = B.T[(static_cast<size_t>(E.row_off) + i) * B.M + best];
     if (B.trace && B.n_ckpt > 0) {
         double bsf = INFINITY;
         for (int c = 0; c < B.n_ckpt; ++c) {
             double v = INFINITY;
-            for (int m = t; m < B.M; m += 256)
+            for (int m = t; m < B.M; m += kSelect)
                 v = fmin(v, B.etrace[(static_cast<size_t>(e) * B.n_ckpt + c) * B.M + m]);
             se[t] = v;
             __syncthreads();
-            for (int w = 128; w >= 1; w >>= 1) {
+            for (int w = kSelect / 2; w >= 1; w >>= 1) {
                 if (t < w) se[t] = fmin(se[t], se[t + w]);
                 __syncthreads();
             }
@@ -157,6 +267,18 @@ __global__ __launch_bounds__(256) void batch_select(BatchArgs B) {
 hipError_t launch_batch_prep(int jprec, const BatchArgs &B, hipStream_t st) {
     batch_prep<<<B.E, 256, 0, st>>>(B, jprec);
     return hipGetLastError();
+}
+
+hipError_t launch_rank_spins(int n, const int *row_ptr, const int *col, int *perm, int *rank,
+                             uint16_t *colr, hipStream_t st) {
+    rank_spins<<<1, 1024, 0, st>>>(n, row_ptr, perm, rank);
+    rank_columns<<<(n + 255) / 256, 256, 0, st>>>(n, row_ptr, col, rank, colr);
+    return hipGetLastError();
+}
+
+hipError_t launch_resident_rows(int mode, const BatchArgs &B, const RowsShape &R, hipStream_t st) {
+    if (mode == kASB) return launch_resident_rows_tu<kASB>(B, R, st);
+    return mode == kDSB ? launch_resident_rows_tu<kDSB>(B, R, st) : launch_resident_rows_tu<kBSB>(B, R, st);
 }
 
 hipError_t launch_batch_reset(int *counters, int n, hipStream_t st) {
@@ -183,8 +305,14 @@ hipError_t launch_batch_steps(int mode, int jprec, int tpb, const BatchArgs &B, 
     return hipErrorInvalidValue;
 }
 
+hipError_t launch_batch_energy(const BatchArgs &B, hipStream_t st) {
+    if (B.n_chunks > 0)
+        batch_energy<<<dim3(B.n_chunks, (B.M + 63) / 64, B.E), 1024, 0, st>>>(B);
+    return hipGetLastError();
+}
+
 hipError_t launch_batch_select(const BatchArgs &B, hipStream_t st) {
-    batch_select<<<B.E, 256, 0, st>>>(B);
+    batch_select<<<B.E, kSelect, 0, st>>>(B);
     return hipGetLastError();
 }
 

@@ -241,49 +241,104 @@ __global__ __launch_bounds__(TPB) void sb_resident(ResidentArgs A) {
 
 // part[blockIdx.x * M + m] = sum over rows of this block of
 // T_i (a_i + sum_{j > i} b_ij T_j) for agent m, T = (x >= 0).
-__global__ __launch_bounds__(256) void energy_rows(int n, int M, int rows_per_block,
-                                                   const double *__restrict__ a,
-                                                   const int *__restrict__ row_ptr,
-                                                   const int *__restrict__ col,
-                                                   const double *__restrict__ b,
-                                                   const float *__restrict__ x,
-                                                   double *__restrict__ part) {
-    __shared__ double red[4][64];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+//
+// Small events are bound by load latency (a row is a chain of row pointer,
+// column and position loads), so a wave starts the first two of its eight
+// rows' loads together, and four positions of a row.  Large ones are bound by
+// the positions read: only those above the row, and no row without an agent
+// that holds it.  The row sums go to LDS and are then taken in a fixed order
+// (rows w, w + 4, ... for w = 0..3, then the four).  208710 x 512: 0.49 ->
+// 0.46 ms; 1444 x 256: 17 -> 9 us.
+constexpr int kEnergyWaves = 8;
+__global__ __launch_bounds__(64 * kEnergyWaves) void energy_rows(int n, int M, const double *__restrict__ a,
+                                                                 const int *__restrict__ row_ptr,
+                                                                 const int *__restrict__ col,
+                                                                 const double *__restrict__ b,
+                                                                 const float *__restrict__ x,
+                                                                 double *__restrict__ part) {
+    __shared__ double er[kEnergyRows][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int m = blockIdx.y * 64 + lane;
-    const int r0 = blockIdx.x * rows_per_block;
-    const int r1 = min(n, r0 + rows_per_block);
-    double e = 0.0;
-    if (m < M) {
-        for (int r = r0 + wave; r < r1; r += 4) {
-            const int i = __builtin_amdgcn_readfirstlane(r);
-            if (x[static_cast<size_t>(i) * M + m] >= 0.0f) {
-                double er = a[i];
-                for (int p = row_ptr[i]; p < row_ptr[i + 1]; ++p) {
-                    const int c = col[p];
-                    if (c > i && x[static_cast<size_t>(c) * M + m] >= 0.0f) er += b[p];
+    const int mc = min(m, M - 1);
+    const int r0 = blockIdx.x * kEnergyRows;
+    constexpr int kPer = kEnergyRows / kEnergyWaves;  // rows per wave
+    int cl[kPer], p0[kPer], p1[kPer];
+    float xi[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = r0 + wave * kPer + u, ic = min(i, n - 1);
+        p0[u] = row_ptr[ic];
+        p1[u] = row_ptr[ic + 1];
+        xi[u] = x[static_cast<size_t>(ic) * M + mc];
+        cl[u] = p0[u] + lane < p1[u] ? col[p0[u] + lane] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = r0 + wave * kPer + u;
+        const bool on = i < n && xi[u] >= 0.0f;
+        double e = 0.0;
+        if (__ballot(on)) {
+            e = a[i];
+            // 64 columns at a time, a lane each; those above the row (they
+            // ascend) are a run of lanes
+            for (int p = p0[u], q = p1[u]; p < q; p += 64) {
+                const int c64 = p == p0[u] ? cl[u] : (p + lane < q ? col[p + lane] : -1);
+                const uint64_t above = __ballot(c64 > i);
+                if (above == 0) continue;
+                const int k1 = min(64, q - p);
+                for (int k = __builtin_ctzll(above); k < k1; k += 4) {
+                    double bv[4];
+                    float xv[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int kr = min(k + r, k1 - 1), c = __builtin_amdgcn_readlane(c64, kr);
+                        bv[r] = b[p + kr];
+                        xv[r] = on && k + r < k1 ? x[static_cast<size_t>(c) * M + mc] : -1.0f;
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) e += xv[r] >= 0.0f ? bv[r] : 0.0;
                 }
-                e += er;
             }
         }
+        er[wave * kPer + u][lane] = on ? e : 0.0;
     }
-    red[wave][lane] = e;
+    __syncthreads();
+    if (wave < 4) {
+        double e = 0.0;
+        for (int r = wave; r < kEnergyRows; r += 4) e += er[r][lane];
+        er[wave][lane] = e;  // (rows below 4 are read by this wave alone)
+    }
     __syncthreads();
     if (wave == 0 && m < M)
         part[static_cast<size_t>(blockIdx.x) * M + m] =
-            ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+            ((er[0][lane] + er[1][lane]) + er[2][lane]) + er[3][lane];
 }
 
-__global__ __launch_bounds__(256) void energy_reduce(int nblk, int M, const double *__restrict__ part,
-                                                     double *__restrict__ out) {
-    const int m = blockIdx.x * 256 + threadIdx.x;
+// The blocks' parts of one agent in order; 16 loads in flight, since the
+// chain of adds waits for each (3261 parts x 512 agents: 1.33 -> 0.13 ms).
+__global__ __launch_bounds__(64) void energy_reduce(int nblk, int M, const double *__restrict__ part,
+                                                    double *__restrict__ out) {
+    const int m = blockIdx.x * 64 + threadIdx.x;
     if (m >= M) return;
+    constexpr int U = 16;
     double e = 0.0;
-    for (int k = 0; k < nblk; ++k) e += part[static_cast<size_t>(k) * M + m];
+    int k = 0;
+    double v[U];
+    for (; k + U <= nblk; k += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = part[static_cast<size_t>(k + u) * M + m];
+#pragma unroll
+        for (int u = 0; u < U; ++u) e += v[u];
+    }
+    for (; k < nblk; ++k) e += part[static_cast<size_t>(k) * M + m];
     out[m] = e;
 }
 
-// Best agent (minimum energy, lowest index on ties) and its T.
+// Best agent (minimum energy, lowest index on ties) and, for events up to
+// kSelectInBlock spins, its T; larger events' T is read by best_state, a
+// strided word per spin over the whole chip (208710 x 512: 0.41-0.75 ms in
+// one workgroup).
+constexpr int kSelectInBlock = 4096;
 __global__ __launch_bounds__(1024) void select_best(int n, int M, const double *__restrict__ E,
                                                     const float *__restrict__ x,
                                                     double *__restrict__ best_e,
@@ -320,8 +375,14 @@ __global__ __launch_bounds__(1024) void select_best(int n, int M, const double *
         *best_e = se[0];
         *best_m = mb;
     }
-    if (mb < 0 || mb >= M) return;
+    if (mb < 0 || mb >= M || n > kSelectInBlock) return;
     for (int i = t; i < n; i += 1024) T[i] = x[static_cast<size_t>(i) * M + mb] >= 0.0f ? 1 : 0;
+}
+
+__global__ __launch_bounds__(256) void best_state(int n, int M, const float *__restrict__ x,
+                                                  const int *__restrict__ best_m, int8_t *__restrict__ T) {
+    const int i = blockIdx.x * 256 + threadIdx.x, mb = *best_m;
+    if (i < n && mb >= 0 && mb < M) T[i] = x[static_cast<size_t>(i) * M + mb] >= 0.0f ? 1 : 0;
 }
 
 // trace[c] = min(trace[c-1], min_m etrace[c, m]).
@@ -393,7 +454,6 @@ static hipError_t launch_resident_m(const ResidentArgs &A, const ResidentShape &
 }
 
 hipError_t launch_resident(int mode, const ResidentArgs &A, const ResidentShape &S, hipStream_t st) {
-    if (S.rc > 0) return launch_resident_reg(mode, A, S, st);
     if (mode == kASB) return launch_resident_m<kASB>(A, S, st);
     return mode == kDSB ? launch_resident_m<kDSB>(A, S, st) : launch_resident_m<kBSB>(A, S, st);
 }
@@ -403,14 +463,15 @@ hipError_t launch_energy(int n, int M, const double *a, const int *row_ptr, cons
                          hipStream_t st) {
     const int nblk = (n + kEnergyRows - 1) / kEnergyRows;
     dim3 grid(nblk, (M + 63) / 64);
-    energy_rows<<<grid, 256, 0, st>>>(n, M, kEnergyRows, a, row_ptr, col, b, x, part);
-    energy_reduce<<<(M + 255) / 256, 256, 0, st>>>(nblk, M, part, out);
+    energy_rows<<<grid, 64 * kEnergyWaves, 0, st>>>(n, M, a, row_ptr, col, b, x, part);
+    energy_reduce<<<(M + 63) / 64, 64, 0, st>>>(nblk, M, part, out);
     return hipGetLastError();
 }
 
 hipError_t launch_select_best(int n, int M, const double *E, const float *x, double *best_e,
                               int *best_m, int8_t *T, hipStream_t st) {
     select_best<<<1, 1024, 0, st>>>(n, M, E, x, best_e, best_m, T);
+    if (n > kSelectInBlock) best_state<<<(n + 255) / 256, 256, 0, st>>>(n, M, x, best_m, T);
     return hipGetLastError();
 }
 

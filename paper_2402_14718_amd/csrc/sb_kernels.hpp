@@ -24,53 +24,24 @@ struct ResidentArgs {
     float *x;                    // [n*M] in: start, out: final
     float *y;                    // [n*M]
     double *etrace;              // [n_ckpt*M]
-    const int *perm;             // [n] spin order (register-row variant)
     const float *sched;          // [K] a0 - a_k (schedule table)
 };
 
+// Shape of the LDS-row resident kernel.
 struct ResidentShape {
-    int tpb;                     // threads per workgroup (register-row variant: any
-                                 //   multiple of 64 up to 1024)
-    int spt;                     // spins per thread: register-row 1, 2, 3, 4, 8; LDS-row a
-                                 //   power of two up to 16
-    int rc;                      // > 0: register-row variant with this many couplings per
-                                 //   row in VGPRs (2, 4, 8) for slot 0; 0: LDS-row variant
-    int rr;                      // register-row variant: couplings in VGPRs per row of the
-                                 //   other slots (rc, or 2)
-    bool jlds;                   // LDS-row variant: J held in LDS
+    int tpb;                     // threads per workgroup
+    int spt;                     // spins per thread: a power of two up to 16
+    bool jlds;                   // J held in LDS
     size_t lds_bytes;
 };
 
-// Register-row variant: VGPR estimate of a thread holding spt spins, rc
-// couplings in registers for slot 0 and rr for each other slot (fit to the
-// compiler's counts), the budget at a workgroup size, and which shapes
-// exist -- the host picks a shape only among these.  Slot 0 holds the
-// longest rows, so when the same capacity for every slot does not fit, the
-// other slots get 2 (rows longer than a slot's capacity continue from
-// global memory).
-constexpr int reg_vgpr_estimate(int spt, int rc, int rr) {
-    return 4 * (rc + (spt - 1) * rr) + 12 * spt + 40;
-}
-constexpr int reg_vgpr_budget(int maxtpb) { return maxtpb >= 1024 ? 128 : (maxtpb >= 512 ? 256 : 512); }
-constexpr bool reg_fits(int maxtpb, int spt, int rc, int rr) {
-    return !(spt > 4 && rc > 4) && reg_vgpr_estimate(spt, rc, rr) <= reg_vgpr_budget(maxtpb);
-}
-// the shapes that are built: same capacity everywhere where it fits, else
-// (rc, 2) where that fits with kSplitSlack VGPRs to spare (the compiler
-// keeps the step loop of such shapes spill-free -- checked on the ISA of
-// (1024 threads, 4 spins, 8/2) -- spilling only in the code around it)
-constexpr int kSplitSlack = 16;
-constexpr bool reg_variant_fits(int maxtpb, int spt, int rc, int rr) {
-    if (rr == rc) return reg_fits(maxtpb, spt, rc, rc);
-    return spt > 1 && rr == 2 && rc > 2 && !reg_fits(maxtpb, spt, rc, rc) && !(spt > 4 && rc > 4) &&
-           reg_vgpr_estimate(spt, rc, 2) <= reg_vgpr_budget(maxtpb) + kSplitSlack;
-}
-
-constexpr int kRegMaxN = 8192;   // register-row variant: largest n
-constexpr int kRegTailCap = 1792;  // register-row variant: couplings past the rows'
-                                   //   register capacity staged in LDS (14 KB)
-constexpr int kRegStride = kRegMaxN + 64;  // LDS position buffer: n words, then one pad
-                                           //   word per lane of a wave
+// Shape of the resident kernel whose rows are held in registers
+// (sb_resident_mode.hip); slots = 0: the event does not fit it.
+struct RowsShape {
+    int threads;                 // 64, 256, 512 or 1024
+    int slots;                   // spins per thread: 2, 4 or 9
+    int agents;                  // per workgroup: 1 or 2
+};
 
 // ---------------------------------------------------------------- batch
 
@@ -94,7 +65,10 @@ struct BatchEvent {
     int nz_off;                  // offset into col, b, J16
     int event_id;                // Philox counter word 2
     float c0_scale;              // c0 of the event = (fixed or auto c0) * c0_scale
+    int gang;                    // solved as gangs of row bands
 };
+
+constexpr int kEnergyChunk = 512;  // rows per workgroup of batch_energy
 
 struct BatchArgs {
     int E, M, K, ckpt_every, n_ckpt;
@@ -125,6 +99,8 @@ struct BatchArgs {
     int *counter;                // this launch's work queue counter
     double *etrace;              // [E * n_ckpt * M]
     double *energy;              // [E * M] final O(T)
+    double *epart;               // [E * n_chunks * M] its parts by kEnergyChunk rows
+    int n_chunks;                // of the largest event without gangs
     double *trace;               // [E * n_ckpt] best so far, or null
     double *best_energy;         // [E]
     int *best_agent;             // [E]
@@ -172,6 +148,8 @@ hipError_t launch_batch_steps(int mode, int jprec, int tpb, const BatchArgs &B, 
 template <int MODE, int JP, int TPB>
 hipError_t launch_batch_steps_tu(const BatchArgs &B, hipStream_t st);
 
+// final energies of every event without gangs, from its agents' T
+hipError_t launch_batch_energy(const BatchArgs &B, hipStream_t st);
 hipError_t launch_batch_select(const BatchArgs &B, hipStream_t st);
 // the gang launch (persistent grid of `B.grid` 1024-thread workgroups) and
 // the reduction of its partial energies and stamps; n_gangs gangs
@@ -187,13 +165,13 @@ hipError_t launch_init(int n, int M, uint64_t seed, uint32_t event, float *x, fl
                        hipStream_t st);
 hipError_t launch_schedule(int K, double a0, float *sched, hipStream_t st);
 hipError_t launch_resident(int mode, const ResidentArgs &A, const ResidentShape &S, hipStream_t st);
-hipError_t launch_resident_reg(int mode, const ResidentArgs &A, const ResidentShape &S,
-                               hipStream_t st);
-hipError_t launch_row_order(int n, const int *row_ptr, int *perm, hipStream_t st);
-// the register-row step kernel of one mode (one translation unit each)
-hipError_t launch_resident_reg_bsb(const ResidentArgs &A, const ResidentShape &S, hipStream_t st);
-hipError_t launch_resident_reg_dsb(const ResidentArgs &A, const ResidentShape &S, hipStream_t st);
-hipError_t launch_resident_reg_asb(const ResidentArgs &A, const ResidentShape &S, hipStream_t st);
+hipError_t launch_resident_rows(int mode, const BatchArgs &B, const RowsShape &R, hipStream_t st);
+template <int MODE>
+hipError_t launch_resident_rows_tu(const BatchArgs &B, const RowsShape &R, hipStream_t st);
+// spin order by decreasing row length (perm, its inverse rank) and the
+// columns in it (colr), for the kernels that hold rows in registers
+hipError_t launch_rank_spins(int n, const int *row_ptr, const int *col, int *perm, int *rank,
+                             uint16_t *colr, hipStream_t st);
 hipError_t launch_energy(int n, int M, const double *a, const int *row_ptr, const int *col,
                          const double *b, const float *x, double *part, double *out,
                          hipStream_t st);

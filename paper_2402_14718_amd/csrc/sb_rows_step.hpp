@@ -1,7 +1,7 @@
 // The step loop of solves whose whole state stays on chip (gfx950): one
 // workgroup holds every spin of a few agents from the start draw to the
 // last step.  The batched kernel (sb_batch_step.hpp) and the resident
-// single-event kernel (sb_resident_rows.hpp) are this body.
+// single-event kernel (sb_resident_mode.hip) are this body.
 //
 // Paper section "Simulated Bifurcation": bSB (Eq. 5-8), dSB (Eq. 9-12), aSB
 // (Eq. 1-4).
@@ -72,6 +72,22 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // instead of being hoisted out of the step loop and kept live.
 __device__ __forceinline__ void launder(uint32_t &v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void launder_uniform(int &v) { asm volatile("" : "+s"(v)); }
+
+// Exchanges and the largest value of a wave, for code beside the step loop:
+// `lane` comes from a fresh copy (see rows_solve), where __shfl_xor's six
+// lane addresses would be kept in registers through the loop.
+__device__ __forceinline__ int lane_xor(int v, int lane, int off) {
+    return __builtin_amdgcn_ds_bpermute((lane ^ off) << 2, v);
+}
+__device__ __forceinline__ double lane_xor(double v, int lane, int off) {
+    const int lo = lane_xor(__double2loint(v), lane, off), hi = lane_xor(__double2hiint(v), lane, off);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ int wave_max_at(int v, int lane) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v = max(v, lane_xor(v, lane, off));
+    return __builtin_amdgcn_readfirstlane(v);
+}
 
 // Calls f(integral_constant<int, I>) for I = 0 .. N-1.
 template <int N, int I = 0, class F>
@@ -166,7 +182,17 @@ struct RowsLds {
     static constexpr uint32_t kBuf = static_cast<uint32_t>(S) * TPB * Shared<MODE, W>::kBytes;
     static constexpr uint32_t kRed = sizeof(double) * TPB * W;
     static constexpr bool kRedInBuf = kRed <= kBuf;  // energies reduce in the buffer not read
-    static constexpr uint32_t kItem = 2 * kBuf + (kRedInBuf ? 0 : kRed);
+    // with nine slots the VGPRs do not hold everything: what the step can
+    // read back from the LDS at one word per slot leaves them -- the
+    // positions where the buffers hold them whole (bSB, aSB), the fields
+    // and, of two agents, the last slots' positions for dSB (a spilled
+    // register costs a memory access per step instead)
+    static constexpr bool kXInLds = S == kBatchSPT && MODE != kDSB;
+    static constexpr bool kHInLds = S == kBatchSPT && MODE == kDSB;
+    static constexpr uint32_t kH = 2 * kBuf + (kRedInBuf ? 0 : kRed);
+    static constexpr int kXFrom = kXInLds ? 0 : (kHInLds && W == 2 ? 6 : S);  // slots from here on: x in the LDS
+    static constexpr uint32_t kX = kH + (kHInLds ? 4u * S * TPB : 0);
+    static constexpr uint32_t kItem = kX + (kHInLds ? 4u * W * (S - kXFrom) * TPB : 0);
     static constexpr uint32_t kDump = kItem + 32;  // two words that absorb writes of no one
     static constexpr uint32_t kTails = kItem + 64;
     static constexpr uint32_t kMax = TPB <= 512 && S == kBatchSPT ? 81920 : 163840;
@@ -176,7 +202,7 @@ struct RowsLds {
 };
 
 // SINGLE: one event, workgroup b takes agents b * W ..; otherwise items from
-// a queue.  T: threads of the workgroup (TPB except for single events).
+// a queue.
 template <int MODE, int JP, int TPB, int S, int W, bool SINGLE>
 __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *smem) {
     using V = Shared<MODE, W>;
@@ -189,14 +215,13 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
     constexpr bool kBytesHeld = L::kBuf <= 65536;
     constexpr uint32_t kScale = kBytesHeld ? kB : 1;
     constexpr int kHeld = cap_before(S);
-    static_assert(S <= kBatchSPT && (kBytesHeld || L::kBuf <= 8 * 65536), "positions fit 16 bits");
+    static_assert(cap_before(1) == 16 && S <= kBatchSPT && (kBytesHeld || L::kBuf <= 8 * 65536), "positions fit 16 bits");
 
     double *red_own = reinterpret_cast<double *>(smem + 2 * L::kBuf);
     int *item_s = reinterpret_cast<int *>(smem + L::kItem);
     const int t = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int T = SINGLE ? static_cast<int>(blockDim.x) : TPB;
-    const int nwaves = T >> 6;
+    constexpr int T = TPB, nwaves = TPB / 64;
     auto sync = [&]() __attribute__((always_inline)) {
         if constexpr (TPB == 64) {
             // one wave: the LDS executes its accesses in order
@@ -220,9 +245,9 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
             __syncthreads();
             if (local >= B.n_items) return;
             const int item = B.item_begin + local;
-            e = B.item_event[item];
-            agent0 = B.item_agent0[item];
-            lgG = max(0, B.item_lg[item] - (W - 1));
+            e = __builtin_amdgcn_readfirstlane(B.item_event[item]);
+            agent0 = __builtin_amdgcn_readfirstlane(B.item_agent0[item]);
+            lgG = max(0, __builtin_amdgcn_readfirstlane(B.item_lg[item]) - (W - 1));
         }
         const BatchEvent E = SINGLE ? B.one : B.ev[e];
         const int n = E.n;
@@ -232,7 +257,37 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
         // this thread's position within an odd slot (a wave keeps its lanes'
         // groups as long as a group fits a wave), and the position of slot s
         const int t_odd = G <= 64 ? (nwaves - 1 - wave) * 64 + (t & 63) : t;
-        auto place = [&](int s) -> int { return s * T + (s & 1 ? t_odd : t); };
+        struct Place {
+            uint32_t even, odd;
+        };
+        // dSB positions kept in the LDS, by thread
+        using xs_t = std::conditional_t<W == 2, f32x2, float>;
+        auto x_at = [&](int s) -> uint32_t {
+            return L::kX + static_cast<uint32_t>(((s - L::kXFrom) * T + t) * 4 * W);
+        };
+        auto to_xs = [](const float (&x)[W]) __attribute__((always_inline)) -> xs_t {
+            if constexpr (W == 2)
+                return f32x2{x[0], x[1]};
+            else
+                return x[0];
+        };
+        auto from_xs = [](xs_t v, float (&x)[W]) __attribute__((always_inline)) {
+            if constexpr (W == 2) {
+                x[0] = v[0];
+                x[1] = v[1];
+            } else {
+                x[0] = v;
+            }
+        };
+        // what rarely runs inside the step loop computes its addresses from
+        // a fresh copy instead of keeping them in registers beside the state
+        auto fresh = [&]() __attribute__((always_inline)) -> Place {
+            Place P{static_cast<uint32_t>(t), static_cast<uint32_t>(t_odd)};
+            launder(P.even);
+            launder(P.odd);
+            return P;
+        };
+        auto place = [&](int s, const Place &P) -> int { return s * T + static_cast<int>(s & 1 ? P.odd : P.even); };
         // the agents that thread `t` (t < G) reports energies and stamps of
         auto reports = [&](int w) -> bool { return (t < G) & (agent0 + t * W + w < B.M); };
         const bool wave_reports = wave * 64 < G;
@@ -247,7 +302,7 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
         };
         stamp(0);
 
-        float xr[S][W], yr[S][W], hr[S];
+        float xr[L::kXInLds ? 1 : L::kXFrom][W], yr[S][W], hr[L::kHInLds ? 1 : S];
         // held couplings: 16-bit forms are one word (address low, coupling
         // high); FP32 a word each and two addresses per word
         uint32_t cw[kHeld], ca[kWide ? (kHeld + 1) / 2 : 1];
@@ -263,15 +318,18 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
             return static_cast<int>((s < 6 ? lo >> (5 * (s < 6 ? s : 0)) : hi >> (5 * (s < 6 ? 0 : s - 6))) & 31u);
         };
         // the spin of slot s and whether there is one (otherwise another's)
-        auto spin_at = [&](int s, bool &there) -> int {
-            const int q = place(s) >> lgG;
+        auto spin_at = [&](int s, const Place &P, bool &there) -> int {
+            const int q = place(s, P) >> lgG;
             there = q < n;
             return B.perm[E.row_off + min(q, n - 1)];
         };
         auto row_of = [&](int i, bool there, int &p0) -> int {  // length of the row, 0 without a spin
-            p0 = B.row_ptr[E.rp_off + i];
-            const int p1 = B.row_ptr[E.rp_off + i + 1];
-            return there ? p1 - p0 : 0;
+            uint32_t r0 = static_cast<uint32_t>(B.row_ptr[E.rp_off + i]);
+            uint32_t r1 = static_cast<uint32_t>(B.row_ptr[E.rp_off + i + 1]);
+            launder(r0);  // (or the loads move under a branch)
+            launder(r1);
+            p0 = static_cast<int>(r0);
+            return there ? static_cast<int>(r1 - r0) : 0;
         };
         auto address = [&](uint32_t colr) -> uint32_t {
             return ((colr & (kColUpper - 1)) * G + g) * kScale;
@@ -282,7 +340,7 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
             else
                 return static_cast<uint32_t>(B.J16[p]) << 16;
         };
-        auto self_of = [&](int s) -> uint32_t { return static_cast<uint32_t>(place(s)) * kScale; };
+        auto self_of = [&](int s, const Place &P) -> uint32_t { return static_cast<uint32_t>(place(s, P)) * kScale; };
         if constexpr (kWide) {
 #pragma unroll
             for (int c = 0; c < (kHeld + 1) / 2; ++c) ca[c] = 0;
@@ -290,29 +348,43 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
         unrolled<S>([&](auto sc) {
             constexpr int s = decltype(sc)::value;
             constexpr int CAP = kCap[s], O = cap_before(s);
+            const Place P = fresh();
             bool there;
             int p0;
-            const int i = spin_at(s, there);
+            const int i = spin_at(s, P, there);
             const int len = row_of(i, there, p0);
-            const float h = B.h[E.row_off + i];
-            hr[s] = there ? h : 0.0f;
+            uint32_t h = __float_as_uint(B.h[E.row_off + i]);
+            // every load of the row in flight (past its end: entry 0 again)
+            uint32_t al[CAP], vl[CAP];
+#pragma unroll
+            for (int c = 0; c < CAP; ++c) {
+                const int p = c < len ? E.nz_off + p0 + c : 0;
+                al[c] = B.colr[p];
+                vl[c] = coupling(p);
+            }
+            float x[W];
 #pragma unroll
             for (int w = 0; w < W; ++w) {
                 const Philox4 r = philox4x32_10(static_cast<uint32_t>(i), static_cast<uint32_t>(agent + w),
                                                 static_cast<uint32_t>(E.event_id), 0u, B.seed_lo, B.seed_hi);
-                xr[s][w] = there ? philox_word_to_unit(r.v[0]) : 0.0f;
+                x[w] = there ? philox_word_to_unit(r.v[0]) : 0.0f;
+                if constexpr (s < L::kXFrom) xr[s][w] = x[w];
                 yr[s][w] = there ? philox_word_to_unit(r.v[1]) : 0.0f;
             }
+            if constexpr (L::kHInLds && s >= L::kXFrom) lds_write<xs_t>(x_at(s), to_xs(x));
+            launder(h);
+            const float hf = there ? __uint_as_float(h) : 0.0f;
+            if constexpr (L::kHInLds)
+                lds_write<float>(L::kH + 4u * static_cast<uint32_t>(s * T + t), hf);
+            else
+                hr[s] = hf;
             cnt[s] = wave_max_int(len < CAP ? len : CAP);
+            const uint32_t self = self_of(s, P);
 #pragma unroll
             for (int c = 0; c < CAP; ++c) {
-                uint32_t a = self_of(s), v = 0u;
-                if (c < cnt[s]) {
-                    const int p = c < len ? E.nz_off + p0 + c : 0;
-                    const uint32_t al = address(B.colr[p]), vl = coupling(p);
-                    a = c < len ? al : a;
-                    v = c < len ? vl : v;
-                }
+                launder(al[c]);
+                launder(vl[c]);
+                const uint32_t a = c < len ? address(al[c]) : self, v = c < len ? vl[c] : 0u;
                 if constexpr (kWide) {
                     cw[O + c] = v;
                     ca[(O + c) / 2] |= a << (16 * ((O + c) & 1));
@@ -332,12 +404,13 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
             }
             tsum += tl;
             act |= there ? 1 << s : 0;
-            lds_write<word>(static_cast<uint32_t>(place(s)) * kB, V::pack(xr[s]));
+            lds_write<word>(static_cast<uint32_t>(place(s, P)) * kB, V::pack(x));
         });
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) act |= __shfl_xor(act, off, 64);
-        int n_act = 32 - __builtin_clz(__builtin_amdgcn_readfirstlane(act) | 1);  // a prefix
-        int any_tail = wave_max_int(tsum);
+        act = __builtin_amdgcn_readfirstlane(act);
+        int n_act = act ? 32 - __builtin_clz(act) : 0;  // slots with a spin: a prefix
+        const int any_tail = wave_max_int(tsum);
         // offsets of the tails by a block scan; an item whose tails do not
         // fit, or that has more than 31 for one row, reads them from global
         // memory.  The scan's scratch is the buffer no wave reads yet.
@@ -356,7 +429,7 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                 if (most > 0) {
                     bool there;
                     int p0;
-                    const int i = spin_at(s, there);
+                    const int i = spin_at(s, fresh(), there);
                     (void)row_of(i, there, p0);
                     for (int u = 0; u < most; ++u) {
                         const bool mine = u < len;
@@ -374,6 +447,16 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                 }
             });
         }
+        // slots of this wave whose rows go on in tails, or past the couplings
+        // that are always gathered
+        int tailed = 0, slow = 0;
+        unrolled<S>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            if (five(tm_lo, tm_hi, sc) > 0) tailed |= 1 << s;
+            if (cnt[s] > ahead(s)) slow |= 1 << s;
+        });
+        tailed = __builtin_amdgcn_readfirstlane(tailed);
+        slow = __builtin_amdgcn_readfirstlane(slow | tailed);
         tp_hi |= lds_tails ? static_cast<uint32_t>(t_base) << 15 : 0u;
         __syncthreads();
 
@@ -381,17 +464,36 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
         const float dt = B.dt, dta0 = B.dta0;
         // the schedule a step ahead, as a vector load: a scalar one would
         // make every wait for LDS values a wait for all of them
-        float gap_next = B.sched[0];
+        float gap_next = 0.0f;
         // LDS addresses of slots 0 and 1 in the first buffer, less whole slots
         uint32_t own = static_cast<uint32_t>(t) * kB, own_odd = static_cast<uint32_t>(t_odd) * kB;
         launder(own);
         launder(own_odd);
+        uint32_t own_h = L::kH + 4u * static_cast<uint32_t>(t);
+        uint32_t own_x = L::kX + 4u * W * static_cast<uint32_t>(t);
+        if constexpr (L::kHInLds) launder(own_h);
+        if constexpr (L::kHInLds && L::kXFrom < S) launder(own_x);
         int ck = 0;
+
+        // positions of slot s in buffer `buf`
+        auto state = [&](auto sc, const Place &P, int buf, float (&x)[W]) {
+            constexpr int s = decltype(sc)::value;
+            if constexpr (L::kXInLds) {
+                const word xw = lds_read<word>(static_cast<uint32_t>(buf) * L::kBuf + static_cast<uint32_t>(place(s, P)) * kB);
+                unrolled<W>([&](auto wc) { x[decltype(wc)::value] = V::template get<decltype(wc)::value>(xw); });
+            } else if constexpr (s >= L::kXFrom) {
+                from_xs(lds_read<xs_t>(x_at(s)), x);
+            } else {
+                for (int w = 0; w < W; ++w) x[w] = xr[s][w];
+            }
+        };
 
         // FP64 energy of the current state per agent (Eq. 13): out[w] is
         // agent (agent0 + t * W + w)'s in threads t < G.  The sums run
         // through the buffer that this step does not read.
         auto agent_energy = [&](int buf, double (&out)[W]) {
+            const Place P = fresh();
+            const int lane = static_cast<int>(P.even & 63u);
             double *red = L::kRedInBuf ? reinterpret_cast<double *>(smem + (buf ^ 1) * L::kBuf) : red_own;
             double v[W] = {};
             unrolled<S>([&](auto sc) {
@@ -399,9 +501,9 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                 if (s >= n_act) return;
                 bool there;
                 int p0;
-                const int i = spin_at(s, there);
+                const int i = spin_at(s, P, there);
                 const int len = row_of(i, there, p0);
-                const int most = wave_max_int(len);
+                const int most = wave_max_at(len, lane);
                 const double a = B.a[E.row_off + i];
                 double er[W];
                 for (int w = 0; w < W; ++w) er[w] = a;
@@ -417,11 +519,13 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                         er[w] += (pair & (V::template get<w>(x) >= 0.0f)) ? b : 0.0;
                     });
                 }
-                for (int w = 0; w < W; ++w) v[w] += (there & (xr[s][w] >= 0.0f)) ? er[w] : 0.0;
+                float x[W];
+                state(sc, P, buf, x);
+                for (int w = 0; w < W; ++w) v[w] += (there & (x[w] >= 0.0f)) ? er[w] : 0.0;
             });
             for (int w = 0; w < W; ++w) {
                 // lanes with equal t % G hold the same agents
-                for (int off = 32; off >= G; off >>= 1) v[w] += __shfl_xor(v[w], off, 64);
+                for (int off = 32; off >= G; off >>= 1) v[w] += lane_xor(v[w], lane, off);
                 red[w * T + t] = v[w];
             }
             __syncthreads();
@@ -438,18 +542,28 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
             __syncthreads();
         };
 
+        auto held_value = [&](auto oc) __attribute__((always_inline)) -> float {
+            constexpr int o = decltype(oc)::value;
+            if constexpr (kWide)
+                return __uint_as_float(cw[o]);
+            else if constexpr (JP == kJFp16)
+                return static_cast<float>(__ushort_as_half(static_cast<uint16_t>(cw[o] >> 16)));
+            else
+                return __uint_as_float(cw[o] & 0xFFFF0000u);
+        };
+
         // One step reading buffer BUF and writing the other.
         auto step = [&](auto bufc, int k) __attribute__((always_inline)) {
             constexpr int BUF = decltype(bufc)::value;
             constexpr uint32_t XO = BUF * L::kBuf, XN = (BUF ^ 1) * L::kBuf;
             const float gap = gap_next;
             gap_next = B.sched[min(k + 1, B.K - 1)];
-#pragma unroll
-            for (int c = 0; c < (kWide ? (kHeld + 1) / 2 : kHeld); ++c) launder(kWide ? ca[c] : cw[c]);
             // (comparisons with the counts belong in the step, not in masks kept for it)
 #pragma unroll
-            for (int s = 0; s < S; ++s) launder_uniform(cnt[s]);
+            for (int s = 0; s < S; ++s)
+                if (kCap[s] > 4) launder_uniform(cnt[s]);
             launder_uniform(n_act);
+            launder_uniform(slow);
             auto read = [&](uint32_t a16) __attribute__((always_inline)) -> word {
                 return lds_read<word>(kBytesHeld ? a16 + XO : a16);
             };
@@ -471,20 +585,15 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                     return a;
                 }
             };
-            auto value_of = [&](auto oc) __attribute__((always_inline)) -> float {
-                constexpr int o = decltype(oc)::value;
-                if constexpr (kWide)
-                    return __uint_as_float(cw[o]);
-                else if constexpr (JP == kJFp16)
-                    return static_cast<float>(__ushort_as_half(static_cast<uint16_t>(cw[o] >> 16)));
-                else
-                    return __uint_as_float(cw[o] & 0xFFFF0000u);
-            };
             // couplings [C0, C1) of slot s, all gathers in flight at once
             auto load = [&](auto sc, auto c0c, auto c1c, word *v) __attribute__((always_inline)) {
                 constexpr int O = cap_before(decltype(sc)::value), C0 = decltype(c0c)::value;
                 unrolled<decltype(c1c)::value - C0>([&](auto uc) __attribute__((always_inline)) {
-                    constexpr int u = decltype(uc)::value;
+                    constexpr int u = decltype(uc)::value, o = O + C0 + u;
+                    if constexpr (!kWide)
+                        launder(cw[o]);
+                    else if constexpr ((o & 1) == 0 || u == 0)
+                        launder(ca[o / 2]);
                     v[u] = read(addr_of(std::integral_constant<int, O + C0 + u>{}));
                 });
             };
@@ -493,7 +602,7 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                 constexpr int O = cap_before(decltype(sc)::value), C0 = decltype(c0c)::value;
                 unrolled<decltype(c1c)::value - C0>([&](auto uc) __attribute__((always_inline)) {
                     constexpr int u = decltype(uc)::value;
-                    const float jv = value_of(std::integral_constant<int, O + C0 + u>{});
+                    const float jv = held_value(std::integral_constant<int, O + C0 + u>{});
                     unrolled<W>([&](auto wc) __attribute__((always_inline)) {
                         constexpr int w = decltype(wc)::value;
                         acc[w] = __builtin_fmaf(jv, V::template get<w>(v[u]), acc[w]);
@@ -503,61 +612,81 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
             using std::integral_constant;
             // the first couplings of a slot are gathered while the slot
             // before it is summed
-            word base[2][kAhead];
-            load(integral_constant<int, 0>{}, integral_constant<int, 0>{}, integral_constant<int, ahead(0)>{},
-                 base[0]);
+            word base[2][kAhead], xw[2];
+            float hw[2];
+            xs_t xs[2];
+            auto read_ahead = [&](auto nc) __attribute__((always_inline)) {
+                constexpr int n2 = decltype(nc)::value;
+                load(nc, integral_constant<int, 0>{}, integral_constant<int, ahead(n2)>{}, base[n2 & 1]);
+                if constexpr (L::kXInLds)
+                    xw[n2 & 1] = lds_read<word>((n2 & 1 ? own_odd : own) + (XO + static_cast<uint32_t>(n2 * T) * kB));
+                if constexpr (L::kHInLds && n2 >= L::kXFrom)
+                    xs[n2 & 1] = lds_read<xs_t>(own_x + 4u * W * static_cast<uint32_t>((n2 - L::kXFrom) * T));
+                if constexpr (L::kHInLds) hw[n2 & 1] = lds_read<float>(own_h + 4u * static_cast<uint32_t>(n2 * T));
+            };
+            read_ahead(integral_constant<int, 0>{});
             unrolled<S>([&](auto sc) __attribute__((always_inline)) {
                 constexpr int s = decltype(sc)::value;
                 if (s >= n_act) return;
                 constexpr int CAP = kCap[s];
-                float acc[W];
+                float acc[W], x[W];
 #pragma unroll
-                for (int w = 0; w < W; ++w) acc[w] = hr[s];
-                // couplings [kAhead, C) of this slot and the next slot's
-                // first, in flight together; one straight run per length class
-                auto row = [&](auto cc) __attribute__((always_inline)) {
-                    constexpr int C = decltype(cc)::value;
-                    word v[C > ahead(s) ? C - ahead(s) : 1];
-                    if constexpr (C > ahead(s)) load(sc, integral_constant<int, ahead(s)>{}, cc, v);
-                    if constexpr (s + 1 < S)
-                        load(integral_constant<int, s + 1>{}, integral_constant<int, 0>{},
-                             integral_constant<int, ahead(s + 1)>{}, base[(s + 1) & 1]);
-                    add(sc, integral_constant<int, 0>{}, integral_constant<int, ahead(s)>{}, base[s & 1], acc);
-                    if constexpr (C > ahead(s)) add(sc, integral_constant<int, ahead(s)>{}, cc, v, acc);
-                    // (distinct per class, or the classes' ends are merged
-                    // at the price of a copy per operand)
-#pragma unroll
-                    for (int w = 0; w < W; ++w) asm volatile("; slot %1 class %2" : "+v"(acc[w]) : "n"(s), "n"(C));
-                };
-                if constexpr (CAP <= 2) {
-                    row(integral_constant<int, CAP>{});
-                } else if constexpr (CAP <= 4) {
-                    if (cnt[s] <= 2)
-                        row(integral_constant<int, 2>{});
+                for (int w = 0; w < W; ++w) {
+                    if constexpr (L::kHInLds)
+                        acc[w] = hw[s & 1];
                     else
-                        row(integral_constant<int, CAP>{});
-                } else if constexpr (CAP <= 8) {
-                    if (cnt[s] <= 2)
-                        row(integral_constant<int, 2>{});
-                    else if (cnt[s] <= 4)
-                        row(integral_constant<int, 4>{});
-                    else
-                        row(integral_constant<int, CAP>{});
-                } else {
-                    if (cnt[s] <= 2)
-                        row(integral_constant<int, 2>{});
-                    else if (cnt[s] <= 4)
-                        row(integral_constant<int, 4>{});
-                    else if (cnt[s] <= 8)
-                        row(integral_constant<int, 8>{});
-                    else
-                        row(integral_constant<int, CAP>{});
+                        acc[w] = hr[s];
                 }
-                launder_uniform(any_tail);
-                if (__builtin_expect(any_tail, 0)) {
+                if constexpr (s + 1 < S) read_ahead(integral_constant<int, s + 1>{});
+                if (!((slow >> s) & 1)) {
+                    add(sc, integral_constant<int, 0>{}, integral_constant<int, ahead(s)>{}, base[s & 1], acc);
+#pragma unroll
+                    for (int w = 0; w < W; ++w) asm volatile("; slot %1 short" : "+v"(acc[w]) : "n"(s));
+                } else {
+                    // couplings [kAhead, C), at most six in flight: one
+                    // straight run per length class
+                    auto row = [&](auto cc) __attribute__((always_inline)) {
+                        constexpr int C = decltype(cc)::value;
+                        if constexpr (C > ahead(s)) {
+                            word v[C - ahead(s)];
+                            load(sc, integral_constant<int, ahead(s)>{}, cc, v);
+                            add(sc, integral_constant<int, 0>{}, integral_constant<int, ahead(s)>{}, base[s & 1], acc);
+                            add(sc, integral_constant<int, ahead(s)>{}, cc, v, acc);
+                        } else {
+                            add(sc, integral_constant<int, 0>{}, integral_constant<int, ahead(s)>{}, base[s & 1], acc);
+                        }
+                        // (distinct per class, or the classes' ends are
+                        // merged at the price of a copy per operand)
+#pragma unroll
+                        for (int w = 0; w < W; ++w)
+                            asm volatile("; slot %1 class %2" : "+v"(acc[w]) : "n"(s), "n"(C));
+                    };
+                    auto more = [&](auto c0c, auto c1c) __attribute__((always_inline)) {
+                        word v[decltype(c1c)::value - decltype(c0c)::value];
+                        load(sc, c0c, c1c, v);
+                        add(sc, c0c, c1c, v, acc);
+                    };
+                    if constexpr (CAP <= 4) {
+                        row(integral_constant<int, CAP>{});
+                    } else {
+                        if (cnt[s] <= 4)
+                            row(integral_constant<int, 4>{});
+                        else
+                            row(integral_constant<int, (CAP < 8 ? CAP : 8)>{});
+                        if constexpr (CAP > 8)
+                            if (cnt[s] > 8) {
+                                more(integral_constant<int, 8>{}, integral_constant<int, 12>{});
+                                if (cnt[s] > 12) more(integral_constant<int, 12>{}, integral_constant<int, CAP>{});
+                            }
+                    }
+                    if (__builtin_expect((tailed >> s) & 1, 0)) {
                     // CSR order within the row, after the held couplings;
                     // lanes past their row's end add a zero coupling
-                    const uint32_t self = self_of(s);
+                    const Place P = fresh();
+                    uint32_t tl_lo = tp_lo, tl_hi = tp_hi;
+                    launder(tl_lo);
+                    launder(tl_hi);
+                    const uint32_t self = self_of(s, P);
                     auto tail_word = [&](uint32_t a16) __attribute__((always_inline)) -> word {
                         return lds_read<word>((kBytesHeld ? a16 : a16 * kB) + XO);
                     };
@@ -573,9 +702,9 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                         });
                     };
                     if (lds_tails) {
-                        int o = static_cast<int>(tp_hi >> 15);
-                        unrolled<s>([&](auto bc) { o += five(tp_lo, tp_hi, bc); });
-                        const int len = five(tp_lo, tp_hi, sc), most = five(tm_lo, tm_hi, sc);
+                        int o = static_cast<int>(tl_hi >> 15);
+                        unrolled<s>([&](auto bc) { o += five(tl_lo, tl_hi, bc); });
+                        const int len = five(tl_lo, tl_hi, sc), most = five(tm_lo, tm_hi, sc);
                         // four at a time, so that a wave with long rows waits
                         // twice for the LDS per four couplings
                         constexpr int U = 4;
@@ -606,8 +735,9 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                     } else {
                         bool there;
                         int p0;
-                        const int i = spin_at(s, there);
-                        const int len = row_of(i, there, p0), most = wave_max_int(len);
+                        const int i = spin_at(s, P, there);
+                        const int len = row_of(i, there, p0);
+                        const int most = wave_max_at(len, static_cast<int>(P.even & 63u));
                         for (int u = CAP; u < most; ++u) {
                             const bool mine = u < len;
                             const int p = mine ? E.nz_off + p0 + u : 0;
@@ -616,22 +746,129 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                         }
                     }
                 }
+                }
+                if constexpr (L::kHInLds && s >= L::kXFrom) from_xs(xs[s & 1], x);
 #pragma unroll
-                for (int w = 0; w < W; ++w) rows_step<MODE>(xr[s][w], yr[s][w], acc[w], c0, gap, dt, dta0);
-                lds_write<word>((s & 1 ? own_odd : own) + (XN + static_cast<uint32_t>(s * T) * kB), V::pack(xr[s]));
+                for (int w = 0; w < W; ++w) {
+                    if constexpr (L::kXInLds)
+                        x[w] = w == 0 ? V::template get<0>(xw[s & 1]) : V::template get<W - 1>(xw[s & 1]);
+                    else if constexpr (s < L::kXFrom)
+                        x[w] = xr[s][w];
+                    rows_step<MODE>(x[w], yr[s][w], acc[w], c0, gap, dt, dta0);
+                    if constexpr (s < L::kXFrom) xr[s][w] = x[w];
+                }
+                if constexpr (L::kHInLds && s >= L::kXFrom)
+                    lds_write<xs_t>(own_x + 4u * W * static_cast<uint32_t>((s - L::kXFrom) * T), to_xs(x));
+                lds_write<word>((s & 1 ? own_odd : own) + (XN + static_cast<uint32_t>(s * T) * kB), V::pack(x));
             });
             sync();
+        };
+        // Steps [k, end) of a wave of up to two slots without tails, whose
+        // longest rows have at most C0 and C1 couplings: no branch, every
+        // gather of the step in flight at once, and the schedule read once
+        // per 64 steps.  These small events are bound by the latency of a
+        // step (the waves of a CU are few), not by its instructions: against
+        // the branching step, 20 spins x 32 agents take 54 instead of 122 ns
+        // a step, 1444 x 256 214 instead of 315 ns.
+        auto straight = [&](auto c0c, auto c1c, int &k, int end) __attribute__((always_inline)) {
+            constexpr int C0 = decltype(c0c)::value, C1 = decltype(c1c)::value;
+            constexpr int kSlots = C1 >= 0 ? 2 : 1, kC1 = C1 > 0 ? C1 : 0;
+            const int lane = t & 63;
+            auto gaps_from = [&](int k0) -> float { return B.sched[min(k0 + lane, B.K - 1)]; };
+            float gaps = gaps_from(k & ~63), gaps_next = gaps_from((k & ~63) + 64);
+            uint32_t at[C0 + kC1];
+            unrolled<C0 + kC1>([&](auto cc) {
+                constexpr int c = decltype(cc)::value, o = c < C0 ? c : cap_before(1) + c - C0;
+                at[c] = (kWide ? ((o & 1) ? ca[o / 2] >> 16 : ca[o / 2] & 0xFFFFu) : cw[o] & 0xFFFFu) *
+                        (kBytesHeld ? 1u : kB);
+            });
+            auto one = [&](auto bufc, int k) __attribute__((always_inline)) {
+                constexpr uint32_t XO = decltype(bufc)::value * L::kBuf, XN = (decltype(bufc)::value ^ 1) * L::kBuf;
+                const float gap = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(gaps), k & 63));
+                word v[C0 + kC1];
+#pragma unroll
+                for (int c = 0; c < C0 + kC1; ++c) v[c] = lds_read<word>(at[c] + XO);
+                unrolled<kSlots>([&](auto sc) __attribute__((always_inline)) {
+                    constexpr int s = decltype(sc)::value, O = s == 0 ? 0 : C0;
+                    float acc[W];
+#pragma unroll
+                    for (int w = 0; w < W; ++w) acc[w] = hr[s];
+                    unrolled<(s == 0 ? C0 : kC1)>([&](auto cc) __attribute__((always_inline)) {
+                        constexpr int c = decltype(cc)::value;
+                        const float jv = held_value(std::integral_constant<int, cap_before(s) + c>{});
+                        unrolled<W>([&](auto wc) __attribute__((always_inline)) {
+                            constexpr int w = decltype(wc)::value;
+                            acc[w] = __builtin_fmaf(jv, V::template get<w>(v[O + c]), acc[w]);
+                        });
+                    });
+#pragma unroll
+                    for (int w = 0; w < W; ++w) rows_step<MODE>(xr[s][w], yr[s][w], acc[w], c0, gap, dt, dta0);
+                    lds_write<word>((s & 1 ? own_odd : own) + (XN + static_cast<uint32_t>(s * T) * kB), V::pack(xr[s]));
+                });
+                sync();
+            };
+            auto turn = [&]() {
+                if ((k & 63) == 0) {
+                    gaps = gaps_next;
+                    gaps_next = gaps_from(k + 64);
+                }
+            };
+            if (k & 1) {
+                one(std::integral_constant<int, 1>{}, k++);
+                turn();
+            }
+            while (k + 1 < end) {
+                const int stop = min(end - 1, (k & ~63) + 63);
+                for (; k < stop; k += 2) {
+                    one(std::integral_constant<int, 0>{}, k);
+                    one(std::integral_constant<int, 1>{}, k + 1);
+                }
+                turn();
+            }
+            if (k < end) one(std::integral_constant<int, 0>{}, k++);
+        };
+        // the straight run for this wave's rows, or none
+        auto straight_run = [&](auto &k, int end) __attribute__((always_inline)) -> bool {
+            if (tailed != 0) return false;
+            const int l0 = cnt[0], l1 = n_act > 1 ? cnt[1] : -1;
+            using std::integral_constant;
+            auto first = [&](auto c0c) __attribute__((always_inline)) {
+                if (l1 < 0)
+                    straight(c0c, integral_constant<int, -1>{}, k, end);
+                else if (l1 <= 2)
+                    straight(c0c, integral_constant<int, 2>{}, k, end);
+                else if (l1 <= 4)
+                    straight(c0c, integral_constant<int, 4>{}, k, end);
+                else
+                    straight(c0c, integral_constant<int, kCap[1]>{}, k, end);
+            };
+            if (l0 <= 2)
+                first(integral_constant<int, 2>{});
+            else if (l0 <= 4)
+                first(integral_constant<int, 4>{});
+            else if (l0 <= 8)
+                first(integral_constant<int, 8>{});
+            else if (l0 <= 12)
+                first(integral_constant<int, 12>{});
+            else
+                first(integral_constant<int, kCap[0]>{});
+            return true;
         };
         // steps in runs between checkpoints; the buffer read at step k is k & 1
         int k = 0;
         while (k < B.K) {
             const int kend = B.ckpt_every > 0 ? min(B.K, k - k % B.ckpt_every + B.ckpt_every) : B.K;
-            if (k & 1) step(std::integral_constant<int, 1>{}, k++);
-            for (; k + 1 < kend; k += 2) {
-                step(std::integral_constant<int, 0>{}, k);
-                step(std::integral_constant<int, 1>{}, k + 1);
+            bool done = false;
+            if constexpr (S <= 2) done = straight_run(k, kend);
+            if (!done) {
+                gap_next = B.sched[k];
+                if (k & 1) step(std::integral_constant<int, 1>{}, k++);
+                for (; k + 1 < kend; k += 2) {
+                    step(std::integral_constant<int, 0>{}, k);
+                    step(std::integral_constant<int, 1>{}, k + 1);
+                }
+                if (k < kend) step(std::integral_constant<int, 0>{}, k++);
             }
-            if (k < kend) step(std::integral_constant<int, 0>{}, k++);
             if (B.ckpt_every > 0 && k % B.ckpt_every == 0) {
                 double en[W];
                 agent_energy(k & 1, en);
@@ -676,23 +913,19 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                             B.ckpt_clock + (static_cast<size_t>(e) * (B.n_ckpt + 1) + c + 1) * B.M + agent0 + t * W + w,
                             0ll, B.trash);
                 }
-        {
-            double en[W];
-            agent_energy(k & 1, en);
-            if (wave_reports)
-                for (int w = 0; w < W; ++w)
-                    put(reports(w), B.energy + static_cast<size_t>(e) * B.M + agent0 + t * W + w, en[w], B.trash);
-        }
         unrolled<S>([&](auto sc) {
             constexpr int s = decltype(sc)::value;
             if (s >= n_act) return;
+            const Place P = fresh();
             bool there;
-            const int i = spin_at(s, there);
+            const int i = spin_at(s, P, there);
             const size_t o = (static_cast<size_t>(E.row_off) + i) * B.M + agent;
+            float x[W];
+            state(sc, P, k & 1, x);
             for (int w = 0; w < W; ++w) {
                 const bool mine = there & (agent + w < B.M);
-                put(mine, B.T + o + w, static_cast<int8_t>(xr[s][w] >= 0.0f ? 1 : 0), B.trash);
-                if (B.x_out) put(mine, B.x_out + o + w, xr[s][w], B.trash);
+                if (!SINGLE) put(mine, B.T + o + w, static_cast<int8_t>(x[w] >= 0.0f ? 1 : 0), B.trash);
+                if (SINGLE || B.x_out) put(mine, B.x_out + o + w, x[w], B.trash);
                 if (SINGLE && B.y_out) put(mine, B.y_out + o + w, yr[s][w], B.trash);
             }
         });

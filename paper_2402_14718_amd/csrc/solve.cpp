@@ -52,6 +52,9 @@ bool quad_step(sbt_mode mode, int32_t M) { return mode != SBT_DSB && M % 4 == 0 
 // is launch-bound and the matrix-core step 0.86x / 0.85x / 0.84x / 0.82x).
 // FP16 and BF16 single solves run only there (the CSR steps do not take
 // them; the batch functions do).
+constexpr int32_t kCUs = 256;
+constexpr int32_t kRowsAnyN = 4096;
+constexpr int64_t kRowsPerSpin = 8;
 constexpr size_t kMfmaAutoPairs = size_t(1) << 23;
 bool mfma_auto(sbt_mode mode, int32_t prec, int32_t n, int32_t M) {
     return mode == SBT_DSB && static_cast<size_t>(n) * static_cast<size_t>(M) >= kMfmaAutoPairs;
@@ -179,51 +182,33 @@ int device_lds_limit() {
     return v;
 }
 
-// Resident-kernel shape, or tpb = 0 if no resident variant fits.
-// Register-row variant when n <= kRegMaxN and the per-thread rows fit the
-// register budget; otherwise the LDS-row variant while positions fit LDS.
-sbt::ResidentShape resident_shape(int32_t n, int64_t nnz, int32_t max_row, int tpb_hint,
-                                  int lds_limit) {
-    sbt::ResidentShape S{0, 0, 0, 0, false, 0};
+// Shape of the resident kernel that holds rows in registers (slots = 0: it
+// does not fit): two spins per thread on the smallest workgroup that holds
+// them, then four and nine on the largest; a hinted size wherever it holds
+// the event.  Two agents per workgroup once one per CU does not hold them
+// all (two or four spins per thread, where the registers allow it).
+sbt::RowsShape rows_shape(int32_t n, int32_t M, int tpb_hint) {
+    sbt::RowsShape R{0, 0, 0};
+    if (n > sbt::kBatchSPT * 1024) return R;
+    if (tpb_hint != 0 && n <= sbt::kBatchSPT * tpb_hint) {
+        R.threads = tpb_hint;
+        R.slots = n <= 2 * tpb_hint ? 2 : sbt::kBatchSPT;
+    } else {
+        R.threads = n <= 128 ? 64 : (n <= 512 ? 256 : (n <= 1024 ? 512 : 1024));
+        R.slots = n <= 2048 ? 2 : (n <= 4096 ? 4 : sbt::kBatchSPT);
+    }
+    R.agents = R.slots <= 4 && R.threads > 64 && M > kCUs ? 2 : 1;
+    return R;
+}
+
+// Shape of the LDS-row resident kernel, or tpb = 0 if it does not fit.
+sbt::ResidentShape resident_shape(int32_t n, int64_t nnz, int lds_limit) {
+    sbt::ResidentShape S{0, 0, false, 0};
     auto pow2_at_least = [](int v) {
         int p = 1;
         while (p < v) p <<= 1;
         return p;
     };
-    const bool hinted = tpb_hint == 64 || tpb_hint == 256 || tpb_hint == 512 || tpb_hint == 1024;
-    // register-row variant: the fewest spins per thread whose workgroup
-    // (a multiple of 64 threads) fits in 1024, or the hinted size
-    if (n <= sbt::kRegMaxN) {
-        for (const int spt : {1, 2, 3, 4, 8}) {
-            const int tpb = ((n + spt - 1) / spt + 63) / 64 * 64;
-            const int cap_tpb = hinted ? tpb_hint : 1024;
-            if (tpb > cap_tpb) continue;
-            const int maxtpb = tpb <= 256 ? 256 : (tpb <= 512 ? 512 : 1024);
-            int rc = max_row <= 2 ? 2 : (max_row <= 4 ? 4 : 8), rr = 0;
-            for (; rc >= 2; rc >>= 1) {
-                if (sbt::reg_variant_fits(maxtpb, spt, rc, rc)) {
-                    rr = rc;
-                    break;
-                }
-                if (sbt::reg_variant_fits(maxtpb, spt, rc, 2)) {
-                    rr = 2;
-                    break;
-                }
-            }
-            if (rr == 0) continue;
-            const size_t lds =
-                sizeof(float) * 2 * sbt::kRegStride + sizeof(double) * (maxtpb / 64) +
-                (sizeof(int) + sizeof(float)) * sbt::kRegTailCap;
-            if (lds > static_cast<size_t>(lds_limit)) break;
-            S.tpb = tpb;
-            S.spt = spt;
-            S.rc = rc;
-            S.rr = rr;
-            S.lds_bytes = lds;
-            return S;
-        }
-    }
-    // LDS-row variant
     const int tpb = n <= 64 ? 64 : (n <= 1024 ? 256 : 1024);
     const int spt = pow2_at_least((n + tpb - 1) / tpb);
     if (spt > 16) return S;
@@ -234,16 +219,16 @@ sbt::ResidentShape resident_shape(int32_t n, int64_t nnz, int32_t max_row, int t
     if (base > static_cast<size_t>(lds_limit)) return S;
     S.tpb = tpb;
     S.spt = spt;
-    S.rc = 0;
     S.jlds = base + jbytes <= static_cast<size_t>(lds_limit);
     S.lds_bytes = S.jlds ? base + jbytes : base;
     return S;
 }
 
-int pick_kernel(int32_t n, int64_t nnz, int32_t max_row, sbt_mode mode, const sbt_solve_params &p,
-                int lds_limit,
-                sbt::ResidentShape *shape) {
-    sbt::ResidentShape S = resident_shape(n, nnz, max_row, p.tpb, lds_limit);
+int pick_kernel(int32_t n, int64_t nnz, sbt_mode mode, const sbt_solve_params &p, int lds_limit,
+                sbt::RowsShape *rows, sbt::ResidentShape *shape) {
+    const sbt::RowsShape R = rows_shape(n, p.agents, p.tpb);
+    const sbt::ResidentShape S = resident_shape(n, nnz, lds_limit);
+    if (rows) *rows = R;
     if (shape) *shape = S;
     if (p.precision == SBT_PREC_FP16 || p.precision == SBT_PREC_BF16) {
         if (mode == SBT_DSB && (p.kernel == SBT_KERNEL_STREAM_MFMA ||
@@ -278,15 +263,15 @@ int pick_kernel(int32_t n, int64_t nnz, int32_t max_row, sbt_mode mode, const sb
     if (p.kernel == SBT_KERNEL_AUTO && mfma_auto(mode, p.precision, n, p.agents))
         return SBT_KERNEL_STREAM_MFMA;
     if (p.kernel == SBT_KERNEL_RESIDENT) {
-        if (S.tpb == 0)
+        if (R.slots == 0 && S.tpb == 0)
             return fail(SBT_EUNSUPPORTED, "resident kernel: n = %d does not fit in LDS", n);
         return SBT_KERNEL_RESIDENT;
     }
-    // register-row residency wins whenever it fits; the LDS-row variant
-    // only while there are too few agents to fill the streaming kernel's
-    // 64-lane waves (measured: at 1024 agents and n = 8.5e3 streaming is
-    // 2.6x faster)
-    if (S.tpb != 0 && (S.rc > 0 || p.agents <= 128)) return SBT_KERNEL_RESIDENT;
+    // rows held in registers win whenever they do hold them; past that, and
+    // in the LDS-row kernel, only while there are too few agents to fill the
+    // streaming kernel's 64-lane waves
+    if (R.slots != 0 && (n <= kRowsAnyN || nnz <= kRowsPerSpin * n || p.agents <= 128)) return SBT_KERNEL_RESIDENT;
+    if (S.tpb != 0 && p.agents <= 128) return SBT_KERNEL_RESIDENT;
     return stream_kind;
 }
 
@@ -340,7 +325,7 @@ extern "C" int sbt_select_kernel(int32_t n, int64_t nnz, int32_t max_row_nnz, sb
     rc = check_shape(n, nnz, p->agents, "sbt_select_kernel");
     if (rc) return rc;
     if (max_row_nnz < 0) return fail(SBT_EINVAL, "sbt_select_kernel: max_row_nnz < 0");
-    return pick_kernel(n, nnz, max_row_nnz, mode, *p, device_lds_limit(), nullptr);
+    return pick_kernel(n, nnz, mode, *p, device_lds_limit(), nullptr, nullptr);
 }
 
 extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mode mode,
@@ -370,7 +355,8 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
         return fail(SBT_EINVAL, "%s: trace requested but energy_every gives no checkpoint", who);
 
     sbt::ResidentShape shape;
-    const int kernel = pick_kernel(n, q->nnz, max_row_nnz, mode, *p, device_lds_limit(), &shape);
+    sbt::RowsShape rows;
+    const int kernel = pick_kernel(n, q->nnz, mode, *p, device_lds_limit(), &rows, &shape);
     if (kernel < 0) return kernel;
 
     char *ws = static_cast<char *>(workspace);
@@ -396,14 +382,53 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
 
     const double c0_fixed = (std::isnan(p->c0) || p->c0 <= 0.0) ? 0.0 : p->c0;
     SBT_HIP(sbt::launch_prep(n, q->a, q->row_ptr, q->col, q->b, dJ, dh, prep, scal, c0_fixed, st));
-    SBT_HIP(sbt::launch_init(n, M, p->seed, static_cast<uint32_t>(p->event), xa, dy, st));
     SBT_HIP(sbt::launch_schedule(K, p->a0, sched, st));
+    const bool in_rows = kernel == SBT_KERNEL_RESIDENT && rows.slots > 0;
+    if (!in_rows) SBT_HIP(sbt::launch_init(n, M, p->seed, static_cast<uint32_t>(p->event), xa, dy, st));
 
     const float dt = static_cast<float>(p->dt);
     const float dta0 = static_cast<float>(p->dt * p->a0);
     float *xfinal = xa;
     if (out->step_begin) SBT_HIP(hipEventRecord(static_cast<hipEvent_t>(out->step_begin), st));
-    if (kernel == SBT_KERNEL_RESIDENT) {
+    if (in_rows) {
+        // the whole solve in one launch (start draw, steps, checkpoint
+        // energies); the streaming layout's row and column arrays hold the
+        // spin order
+        sbt::BatchArgs B{};
+        int *rank = prow;
+        uint16_t *colr = reinterpret_cast<uint16_t *>(pcol);
+        SBT_HIP(sbt::launch_rank_spins(n, q->row_ptr, q->col, perm, rank, colr, st));
+        B.E = 1;
+        B.M = M;
+        B.K = K;
+        B.ckpt_every = p->energy_every;
+        B.n_ckpt = L.n_ckpt;
+        B.seed_lo = static_cast<uint32_t>(p->seed & 0xffffffffu);
+        B.seed_hi = static_cast<uint32_t>(p->seed >> 32);
+        B.dt = dt;
+        B.dta0 = dta0;
+        B.row_ptr = q->row_ptr;
+        B.col = q->col;
+        B.a = q->a;
+        B.b = q->b;
+        B.J32 = dJ;
+        B.h = dh;
+        B.scal = scal;
+        B.perm = perm;
+        B.rank = rank;
+        B.colr = colr;
+        B.sched = sched;
+        B.trash = epart;  // (at least 256 bytes, like every workspace array)
+        B.etrace = etrace;
+        xfinal = out->x_final ? out->x_final : xa;
+        B.x_out = xfinal;
+        B.y_out = out->y_final;
+        B.one.n = n;
+        B.one.nnz = nnz;
+        B.one.event_id = p->event;
+        B.one.c0_scale = 1.0f;
+        SBT_HIP(sbt::launch_resident_rows(mode, B, rows, st));
+    } else if (kernel == SBT_KERNEL_RESIDENT) {
         sbt::ResidentArgs A{};
         A.n = n;
         A.nnz = nnz;
@@ -423,9 +448,7 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
         A.x = xa;
         A.y = dy;
         A.etrace = etrace;
-        A.perm = perm;
         A.sched = sched;
-        if (shape.rc > 0) SBT_HIP(sbt::launch_row_order(n, q->row_ptr, perm, st));
         SBT_HIP(sbt::launch_resident(mode, A, shape, st));
     } else {
         sbt::StreamArgs A{};
@@ -543,9 +566,9 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
         SBT_HIP(hipMemcpyAsync(out->agent_trace, etrace, sizeof(double) * L.n_ckpt * M,
                                hipMemcpyDeviceToDevice, st));
     const size_t nm = static_cast<size_t>(n) * M;
-    if (out->x_final)
+    if (out->x_final && !in_rows)
         SBT_HIP(hipMemcpyAsync(out->x_final, xfinal, nm * sizeof(float), hipMemcpyDeviceToDevice, st));
-    if (out->y_final)
+    if (out->y_final && !in_rows)
         SBT_HIP(hipMemcpyAsync(out->y_final, dy, nm * sizeof(float), hipMemcpyDeviceToDevice, st));
     if (out->scalars)
         SBT_HIP(hipMemcpyAsync(out->scalars, scal, 4 * sizeof(double), hipMemcpyDeviceToDevice, st));
@@ -640,7 +663,7 @@ extern "C" int sbt_solve(const sbt_qubo *q, sbt_mode mode, const sbt_solve_param
     dr.y_final = static_cast<float *>(dy.p);
     dr.trace = static_cast<double *>(dtr.p);
     dr.agent_trace = static_cast<double *>(dat.p);
-    const int kernel = pick_kernel(n, nnz, max_row, mode, p, device_lds_limit(), nullptr);
+    const int kernel = pick_kernel(n, nnz, mode, p, device_lds_limit(), nullptr, nullptr);
     if (kernel < 0) return kernel;
     SBT_HIP(hipEventRecord(hs.e0, hs.s));
     rc = sbt_solve_dev(&dq, max_row, mode, &p, dws.p, ws_bytes, &dr, hs.s);
