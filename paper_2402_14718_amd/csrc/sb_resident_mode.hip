@@ -25,7 +25,7 @@ hipError_t launch_shape(const BatchArgs &B, hipStream_t st) {
     using L = RowsLds<MODE, TPB, S, W>;
     if (B.one.n > S * TPB) return hipErrorInvalidValue;
     BatchArgs A = B;
-    A.tail_cap = L::tail_words(kBatchTailCap);
+    A.tail_cap = L::tail_words(B.tail_cap);
     // the 16-bit LDS addresses assume the dynamic LDS starts at address 0,
     // which holds when the kernel has no static LDS
     static const bool base_zero = [] {

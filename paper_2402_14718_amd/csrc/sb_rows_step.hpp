@@ -307,15 +307,18 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
         // high); FP32 a word each and two addresses per word
         uint32_t cw[kHeld], ca[kWide ? (kHeld + 1) / 2 : 1];
         int cnt[S];  // longest row of this wave per slot, up to the capacity
-        // tail lengths of the slots, 5 bits each: slots 0-5 in tp_lo, 6-8 in
-        // the low 15 bits of tp_hi, the tails' first entry above; the wave's
-        // longest per slot likewise in tm_lo, tm_hi
+        // tail lengths of the slots, 8 bits each in tp_lo of up to four
+        // slots, else 5: slots 0-5 in tp_lo, 6-8 in the low 15 bits of
+        // tp_hi; the tails' first entry above those; the wave's longest per
+        // slot likewise in tm_lo, tm_hi
+        constexpr int kBits = S <= 4 ? 8 : 5, kLongest = (1 << kBits) - 1;
         uint32_t tp_lo = 0, tp_hi = 0, tm_lo = 0, tm_hi = 0;
         int tsum = 0, tbig = 0, act = 0;
         // (the workgroup's LDS starts at address 0; launchers check it)
-        auto five = [](uint32_t lo, uint32_t hi, auto sc) -> int {
+        auto tail_of = [](uint32_t lo, uint32_t hi, auto sc) -> int {
             constexpr int s = decltype(sc)::value;
-            return static_cast<int>((s < 6 ? lo >> (5 * (s < 6 ? s : 0)) : hi >> (5 * (s < 6 ? 0 : s - 6))) & 31u);
+            return static_cast<int>((s < 6 ? lo >> (kBits * (s < 6 ? s : 0)) : hi >> (5 * (s < 6 ? 0 : s - 6))) &
+                                    kLongest);
         };
         // the spin of slot s and whether there is one (otherwise another's)
         auto spin_at = [&](int s, const Place &P, bool &there) -> int {
@@ -393,14 +396,15 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                 }
             }
             const int tl = max(0, len - CAP);
-            tbig |= tl > 31 ? 1 : 0;
-            const uint32_t tl5 = static_cast<uint32_t>(min(tl, 31)), tm5 = static_cast<uint32_t>(wave_max_int(min(tl, 31)));
+            tbig |= tl > kLongest ? 1 : 0;
+            const uint32_t tlen = static_cast<uint32_t>(min(tl, kLongest));
+            const uint32_t most = static_cast<uint32_t>(wave_max_int(min(tl, kLongest)));
             if constexpr (s < 6) {
-                tp_lo |= tl5 << (5 * s);
-                tm_lo |= tm5 << (5 * s);
+                tp_lo |= tlen << (kBits * s);
+                tm_lo |= most << (kBits * s);
             } else {
-                tp_hi |= tl5 << (5 * (s - 6));
-                tm_hi |= tm5 << (5 * (s - 6));
+                tp_hi |= tlen << (5 * (s - 6));
+                tm_hi |= most << (5 * (s - 6));
             }
             tsum += tl;
             act |= there ? 1 << s : 0;
@@ -412,7 +416,7 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
         int n_act = act ? 32 - __builtin_clz(act) : 0;  // slots with a spin: a prefix
         const int any_tail = wave_max_int(tsum);
         // offsets of the tails by a block scan; an item whose tails do not
-        // fit, or that has more than 31 for one row, reads them from global
+        // fit, or that has more than a field holds, reads them from global
         // memory.  The scan's scratch is the buffer no wave reads yet.
         int *scan = reinterpret_cast<int *>(L::kRedInBuf ? smem + L::kBuf : smem + 2 * L::kBuf);
         int t_total = 0, big_total = 0;
@@ -425,7 +429,7 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
             int o = t_base;
             unrolled<S>([&](auto sc) {
                 constexpr int s = decltype(sc)::value;
-                const int most = five(tm_lo, tm_hi, sc), len = five(tp_lo, tp_hi, sc);
+                const int most = tail_of(tm_lo, tm_hi, sc), len = tail_of(tp_lo, tp_hi, sc);
                 if (most > 0) {
                     bool there;
                     int p0;
@@ -452,7 +456,7 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
         int tailed = 0, slow = 0;
         unrolled<S>([&](auto sc) {
             constexpr int s = decltype(sc)::value;
-            if (five(tm_lo, tm_hi, sc) > 0) tailed |= 1 << s;
+            if (tail_of(tm_lo, tm_hi, sc) > 0) tailed |= 1 << s;
             if (cnt[s] > ahead(s)) slow |= 1 << s;
         });
         tailed = __builtin_amdgcn_readfirstlane(tailed);
@@ -703,8 +707,8 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                     };
                     if (lds_tails) {
                         int o = static_cast<int>(tl_hi >> 15);
-                        unrolled<s>([&](auto bc) { o += five(tl_lo, tl_hi, bc); });
-                        const int len = five(tl_lo, tl_hi, sc), most = five(tm_lo, tm_hi, sc);
+                        unrolled<s>([&](auto bc) { o += tail_of(tl_lo, tl_hi, bc); });
+                        const int len = tail_of(tl_lo, tl_hi, sc), most = tail_of(tm_lo, tm_hi, sc);
                         // four at a time, so that a wave with long rows waits
                         // twice for the LDS per four couplings
                         constexpr int U = 4;
@@ -738,11 +742,28 @@ __device__ __forceinline__ void rows_solve(const BatchArgs &B, unsigned char *sm
                         const int i = spin_at(s, P, there);
                         const int len = row_of(i, there, p0);
                         const int most = wave_max_at(len, static_cast<int>(P.even & 63u));
-                        for (int u = CAP; u < most; ++u) {
-                            const bool mine = u < len;
-                            const int p = mine ? E.nz_off + p0 + u : 0;
-                            const uint32_t v = coupling(p), a = address(B.colr[p]);
-                            tail_add(mine ? v : 0u, tail_word(mine ? a : self));
+                        // (eight in flight: one at a time they cost a memory
+                        // latency each)
+                        constexpr int U = 8;
+                        for (int u0 = CAP; u0 < most; u0 += U) {
+                            uint32_t v[U], a[U];
+                            word x[U];
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const int p = u0 + u < len ? E.nz_off + p0 + u0 + u : 0;
+                                v[u] = coupling(p);
+                                a[u] = B.colr[p];
+                            }
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                launder(v[u]);
+                                launder(a[u]);
+                                const bool mine = u0 + u < len;
+                                v[u] = mine ? v[u] : 0u;
+                                x[u] = tail_word(mine ? address(a[u]) : self);
+                            }
+#pragma unroll
+                            for (int u = 0; u < U; ++u) tail_add(v[u], x[u]);
                         }
                     }
                 }

@@ -53,8 +53,6 @@ bool quad_step(sbt_mode mode, int32_t M) { return mode != SBT_DSB && M % 4 == 0 
 // FP16 and BF16 single solves run only there (the CSR steps do not take
 // them; the batch functions do).
 constexpr int32_t kCUs = 256;
-constexpr int32_t kRowsAnyN = 4096;
-constexpr int64_t kRowsPerSpin = 8;
 constexpr size_t kMfmaAutoPairs = size_t(1) << 23;
 bool mfma_auto(sbt_mode mode, int32_t prec, int32_t n, int32_t M) {
     return mode == SBT_DSB && static_cast<size_t>(n) * static_cast<size_t>(M) >= kMfmaAutoPairs;
@@ -201,6 +199,30 @@ sbt::RowsShape rows_shape(int32_t n, int32_t M, int tpb_hint) {
     return R;
 }
 
+// LDS words that the tails of an event can take (two per coupling), at most
+// what the step loop's buffers leave of 160 KB in any mode.
+int rows_tail_words(int64_t nnz, const sbt::RowsShape &R) {
+    const int64_t left = (163840 - 1024 - 12 * int64_t(R.slots) * R.threads * R.agents) / 4;
+    return static_cast<int>(std::min(2 * nnz, left));
+}
+
+// Whether AUTO takes the resident step loop: while a row's couplings stay in
+// registers and LDS it beats a launch per step at every number of agents
+// (us per step, 256 / 1024 agents, resident against streaming bSB: 1000
+// spins of 16 couplings 1.9 against 9.4 / 3.8 against 10.4; 4000 of 8 2.6
+// against 9.3 / 5.5 against 16.8; 8000 of 3 1.9 against 9.9 / 7.4 against
+// 29.2); once the tails overflow the LDS it loses (2000 of 32 with 32 agents
+// 31 against 5; 8000 of 8 25 against 13 / 102 against 41).  Only n and the
+// number of couplings are known here: either all couplings fit the tail
+// list, or there are few enough per spin for the registers of a shape (33
+// to 43 couplings per 4 to 9 slots, longest rows first).  The LDS-row kernel
+// loses to the streaming step at every size past these shapes.
+bool rows_fit(int32_t n, int64_t nnz, const sbt::RowsShape &R) {
+    if (R.slots == 0) return false;
+    const int per_spin = R.slots == 2 ? 16 : (R.slots == 4 ? 8 : 4);
+    return rows_tail_words(nnz, R) == 2 * nnz || nnz <= per_spin * int64_t(n);
+}
+
 // Shape of the LDS-row resident kernel, or tpb = 0 if it does not fit.
 sbt::ResidentShape resident_shape(int32_t n, int64_t nnz, int lds_limit) {
     sbt::ResidentShape S{0, 0, false, 0};
@@ -267,11 +289,7 @@ int pick_kernel(int32_t n, int64_t nnz, sbt_mode mode, const sbt_solve_params &p
             return fail(SBT_EUNSUPPORTED, "resident kernel: n = %d does not fit in LDS", n);
         return SBT_KERNEL_RESIDENT;
     }
-    // rows held in registers win whenever they do hold them; past that, and
-    // in the LDS-row kernel, only while there are too few agents to fill the
-    // streaming kernel's 64-lane waves
-    if (R.slots != 0 && (n <= kRowsAnyN || nnz <= kRowsPerSpin * n || p.agents <= 128)) return SBT_KERNEL_RESIDENT;
-    if (S.tpb != 0 && p.agents <= 128) return SBT_KERNEL_RESIDENT;
+    if (rows_fit(n, nnz, R)) return SBT_KERNEL_RESIDENT;
     return stream_kind;
 }
 
@@ -423,6 +441,7 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
         xfinal = out->x_final ? out->x_final : xa;
         B.x_out = xfinal;
         B.y_out = out->y_final;
+        B.tail_cap = rows_tail_words(nnz, rows);
         B.one.n = n;
         B.one.nnz = nnz;
         B.one.event_id = p->event;

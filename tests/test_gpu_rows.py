@@ -89,3 +89,18 @@ def test_batch_rows_equal_single_solves_with_exact_couplings(mode, prec):
                 assert np.unique(E[which.ravel() == g]).size == 1
             assert np.array_equal(E, states[0]["agent_energy"][e])
             assert r["best_agent"][e] == np.argmin(E)
+
+
+@pytest.mark.parametrize("n,per_spin,kernel", [(128, 100, "resident"), (1000, 12, "resident"),
+                                               (1000, 40, "stream"), (4096, 7, "resident"),
+                                               (4096, 10, "stream"), (9216, 3, "resident"),
+                                               (9216, 6, "stream"), (9217, 2, "stream")])
+def test_auto_takes_the_loop_while_couplings_fit_and_equals_the_row_step(n, per_spin, kernel):
+    hubs = [min(250, n - 1)] * max(0, int((per_spin - 2) * n / 2 / min(250, n - 1)))
+    q = _qubo(n, hubs, n)
+    kw = dict(agents=40, steps=40, dt=0.5, c0=0.15, seed=n, want_state=True)
+    got = sbt.solve(q, "bsb", **kw)
+    ref = sbt.solve(q, "bsb", kernel="stream_rows", **kw)
+    assert got["kernel"] == kernel, q.nnz / n
+    for k in ("x", "y", "T", "agent_energy", "best_agent"):
+        assert np.array_equal(got[k], ref[k]), k
