@@ -41,8 +41,12 @@ bool lds_attribute_needed(const void *fn, size_t lds) {
 
 // ------------------------------------------------------------ Ising prep
 
-// One thread per row: J = -b/4 in FP32, h_i = -(a_i/2 + 1/4 sum_j b_ij),
-// and per-block partial sums {sum J, sum J^2, sum_{j>i} b, sum a} in FP64.
+// J = -b/4 in FP32, h_i = -(a_i/2 + 1/4 sum_j b_ij), and per-block partial
+// sums {sum J, sum J^2, sum_{j>i} b, sum a} in FP64.  A thread sums a row,
+// in order; the block's couplings come through LDS in tiles, since a thread
+// that reads its row from memory touches a line per coupling and lane
+// (208710 rows: 0.60 -> 0.33 ms).
+constexpr int kPrepTile = 2048;
 __global__ __launch_bounds__(256) void prep_ising_rows(int n, const double *__restrict__ a,
                                                        const int *__restrict__ row_ptr,
                                                        const int *__restrict__ col,
@@ -51,19 +55,40 @@ __global__ __launch_bounds__(256) void prep_ising_rows(int n, const double *__re
                                                        float *__restrict__ h,
                                                        double *__restrict__ part) {
     __shared__ double red[4];
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    double sj = 0.0, sj2 = 0.0, sup = 0.0, sa = 0.0;
-    if (i < n) {
-        double rs = 0.0;
-        for (int p = row_ptr[i]; p < row_ptr[i + 1]; ++p) {
-            const double bv = b[p];
-            const double jv = -0.25 * bv;
-            J[p] = static_cast<float>(jv);
-            rs += bv;
+    __shared__ double tb[kPrepTile];
+    __shared__ int tc[kPrepTile];
+    const int i0 = blockIdx.x * 256, i = i0 + threadIdx.x;
+    const int p0 = i < n ? row_ptr[i] : 0, p1 = i < n ? row_ptr[i + 1] : 0;
+    const int q1 = row_ptr[min(n, i0 + 256)];
+    double sj = 0.0, sj2 = 0.0, sup = 0.0, sa = 0.0, rs = 0.0;
+    for (int q = row_ptr[i0]; q < q1; q += kPrepTile) {
+        double bv[kPrepTile / 256];
+        int cv[kPrepTile / 256];
+#pragma unroll
+        for (int u = 0; u < kPrepTile / 256; ++u) {
+            const int p = min(q + u * 256 + static_cast<int>(threadIdx.x), q1 - 1);
+            bv[u] = b[p];
+            cv[u] = col[p];
+        }
+#pragma unroll
+        for (int u = 0; u < kPrepTile / 256; ++u) {
+            const int k = u * 256 + threadIdx.x;
+            tb[k] = bv[u];
+            tc[k] = cv[u];
+            if (q + k < q1) J[q + k] = static_cast<float>(-0.25 * bv[u]);
+        }
+        __syncthreads();
+        const int e1 = min(p1, q + kPrepTile);
+        for (int p = max(p0, q); p < e1; ++p) {
+            const double v = tb[p - q], jv = -0.25 * v;
+            rs += v;
             sj += jv;
             sj2 += jv * jv;
-            if (col[p] > i) sup += bv;
+            if (tc[p - q] > i) sup += v;
         }
+        __syncthreads();
+    }
+    if (i < n) {
         h[i] = static_cast<float>(-(0.5 * a[i] + 0.25 * rs));
         sa = a[i];
     }

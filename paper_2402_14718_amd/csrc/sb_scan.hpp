@@ -1,0 +1,83 @@
+// Exclusive prefix sums over the rows (or blocks of rows) of an event, in one
+// launch: off[i] = len(0) + .. + len(i - 1), i = 0 .. n.
+//
+// A workgroup sums every length before its range (they are in the L2: a
+// launch of at most 64 workgroups reads them 32 times), then scans its
+// range, kScanThreads x 4 lengths at a time.  One workgroup that reads the
+// lengths strided by threads took 0.51 ms at n = 208710; this takes 0.02.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace sbt {
+
+namespace {
+
+constexpr int kScanThreads = 1024;
+constexpr int kScanTile = 4 * kScanThreads;
+
+inline int scan_range(int n) {  // lengths per workgroup, a multiple of the tile
+    const int tiles = (n + kScanTile - 1) / kScanTile;
+    return kScanTile * ((tiles + 63) / 64 > 0 ? (tiles + 63) / 64 : 1);
+}
+inline int scan_grid(int n) {
+    const int r = scan_range(n);
+    return n > 0 ? (n + r - 1) / r : 1;
+}
+
+// Inclusive scan of one value per thread over the workgroup; total in every
+// thread.
+__device__ __forceinline__ int scan_threads(int v, int *wsum, int &total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(v, d, 64);
+        v += lane >= d ? o : 0;
+    }
+    __syncthreads();  // (wsum may still be read from the call before)
+    if (lane == 63) wsum[wave] = v;
+    __syncthreads();
+    int before = 0;
+    total = 0;
+    for (int w = 0; w < kScanThreads / 64; ++w) {
+        const int s = wsum[w];
+        before += w < wave ? s : 0;
+        total += s;
+    }
+    return v + before;
+}
+
+template <class Len>
+__device__ __forceinline__ void scan_lengths(int n, int range, Len len, int *off) {
+    __shared__ int wsum[kScanThreads / 64];
+    const int t = threadIdx.x;
+    const int lo = min(n, static_cast<int>(blockIdx.x) * range), hi = min(n, lo + range);
+    int v = 0, base;
+    for (int i = t; i < lo; i += 8 * kScanThreads) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += i + u * kScanThreads < lo ? len(i + u * kScanThreads) : 0;
+    }
+    (void)scan_threads(v, wsum, base);
+    for (int i0 = lo; i0 < hi; i0 += kScanTile) {
+        const int i = i0 + 4 * t;
+        int l[4], sum = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            l[u] = i + u < hi ? len(i + u) : 0;
+            sum += l[u];
+        }
+        int total;
+        int at = base + scan_threads(sum, wsum, total) - sum;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (i + u < hi) off[i + u] = at;
+            at += l[u];
+        }
+        base += total;
+    }
+    if (hi == n && (lo < n || n == 0) && t == 0) off[n] = base;
+}
+
+}  // namespace
+
+}  // namespace sbt

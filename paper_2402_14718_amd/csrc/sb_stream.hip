@@ -30,6 +30,7 @@
 
 #include "sb_device.hpp"
 #include "sb_kernels.hpp"
+#include "sb_scan.hpp"
 #include "sb_stream_kernels.hpp"
 #include "sb_stream_chunk.hpp"
 
@@ -49,7 +50,6 @@ constexpr bool kStreamVec4 = true;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kChunk = kStreamChunk;
-constexpr int kPackThreads = 1024;
 
 // Workgroup id -> (row block, agent block), XCD-contiguous.
 __device__ __forceinline__ bool map_block(int nrb, int nab, int &rb, int &ab) {
@@ -79,47 +79,30 @@ __global__ __launch_bounds__(256) void sign_planes(int n, int M, int SW, const f
     if (lane == 0) S[idx] = bal;
 }
 
-// Padded row lengths -> row pointers: one workgroup, each thread a
-// contiguous range of rows, then a scan over the threads' totals in LDS.
-__global__ __launch_bounds__(kPackThreads) void stream_pack_scan(int n, const int *__restrict__ row_ptr,
-                                                                  int *__restrict__ prow) {
-    __shared__ int tot[kPackThreads];
-    const int t = threadIdx.x;
-    const int per = (n + kPackThreads - 1) / kPackThreads;
-    const int r0 = min(n, t * per), r1 = min(n, r0 + per);
-    int sum = 0;
-    for (int i = r0; i < r1; ++i) sum += (row_ptr[i + 1] - row_ptr[i] + kChunk - 1) / kChunk * kChunk;
-    tot[t] = sum;
-    __syncthreads();
-    for (int d = 1; d < kPackThreads; d <<= 1) {  // inclusive Hillis-Steele scan
-        const int v = t >= d ? tot[t - d] : 0;
-        __syncthreads();
-        tot[t] += v;
-        __syncthreads();
-    }
-    int at = tot[t] - sum;
-    for (int i = r0; i < r1; ++i) {
-        prow[i] = at;
-        at += (row_ptr[i + 1] - row_ptr[i] + kChunk - 1) / kChunk * kChunk;
-    }
-    if (t == kPackThreads - 1) prow[n] = tot[t];
+// Padded row lengths -> row pointers.
+__global__ __launch_bounds__(kScanThreads) void stream_pack_scan(int n, int range,
+                                                                 const int *__restrict__ row_ptr,
+                                                                 int *__restrict__ prow) {
+    scan_lengths(n, range, [&](int i) { return (row_ptr[i + 1] - row_ptr[i] + kChunk - 1) / kChunk * kChunk; },
+                 prow);
 }
+
+// Rows are copied and quantised by kRowLanes lanes each, so that a wave
+// reads and writes runs of memory (a thread per row: 0.78 ms to pack 208710
+// rows and 0.23 ms to quantise them).
+constexpr int kRowLanes = 16;
 
 __global__ __launch_bounds__(256) void stream_pack_fill(int n, const int *__restrict__ row_ptr,
                                                         const int *__restrict__ col,
                                                         const float *__restrict__ J,
                                                         const int *__restrict__ prow,
                                                         int *__restrict__ pcol, float *__restrict__ pJ) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int i = blockIdx.x * (256 / kRowLanes) + threadIdx.x / kRowLanes;
     if (i >= n) return;
-    int q = prow[i];
-    for (int p = row_ptr[i]; p < row_ptr[i + 1]; ++p, ++q) {
-        pcol[q] = col[p];
-        pJ[q] = J[p];
-    }
-    for (; q < prow[i + 1]; ++q) {
-        pcol[q] = i;
-        pJ[q] = 0.0f;
+    const int q0 = prow[i], len = prow[i + 1] - q0, p0 = row_ptr[i], have = row_ptr[i + 1] - p0;
+    for (int u = threadIdx.x % kRowLanes; u < len; u += kRowLanes) {
+        pcol[q0 + u] = u < have ? col[p0 + u] : i;
+        pJ[q0 + u] = u < have ? J[p0 + u] : 0.0f;
     }
 }
 
@@ -128,13 +111,15 @@ __global__ __launch_bounds__(256) void quantize_fp8_rows(int n, const int *__res
                                                          const float *__restrict__ J,
                                                          uint8_t *__restrict__ J8,
                                                          float *__restrict__ scale) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
+    const int i = blockIdx.x * (256 / kRowLanes) + threadIdx.x / kRowLanes, r = threadIdx.x % kRowLanes;
+    const int p0 = i < n ? row_ptr[i] : 0, p1 = i < n ? row_ptr[i + 1] : 0;
     float mx = 0.0f;
-    for (int p = row_ptr[i]; p < row_ptr[i + 1]; ++p) mx = fmaxf(mx, __builtin_fabsf(J[p]));
+    for (int p = p0 + r; p < p1; p += kRowLanes) mx = fmaxf(mx, __builtin_fabsf(J[p]));
+#pragma unroll
+    for (int d = 1; d < kRowLanes; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
     const float s = mx > 0.0f ? mx / 448.0f : 1.0f;
-    scale[i] = s;
-    for (int p = row_ptr[i]; p < row_ptr[i + 1]; ++p) {
+    if (i < n && r == 0) scale[i] = s;
+    for (int p = p0 + r; p < p1; p += kRowLanes) {
         // |J / s| can round a hair above 448; e4m3's largest finite is 448
         const float q = fminf(fmaxf(J[p] / s, -448.0f), 448.0f);
         J8[p] = static_cast<uint8_t>(__builtin_amdgcn_cvt_pk_fp8_f32(q, q, 0, false) & 0xFF);
@@ -322,8 +307,8 @@ hipError_t launch_sign_planes(int n, int M, const float *x, uint64_t *S, hipStre
 
 hipError_t launch_stream_pack(int n, const int *row_ptr, const int *col, const float *J, int *prow,
                               int *pcol, float *pJ, hipStream_t st) {
-    stream_pack_scan<<<1, kPackThreads, 0, st>>>(n, row_ptr, prow);
-    stream_pack_fill<<<(n + 255) / 256, 256, 0, st>>>(n, row_ptr, col, J, prow, pcol, pJ);
+    stream_pack_scan<<<scan_grid(n), kScanThreads, 0, st>>>(n, scan_range(n), row_ptr, prow);
+    stream_pack_fill<<<(n + 256 / kRowLanes - 1) / (256 / kRowLanes), 256, 0, st>>>(n, row_ptr, col, J, prow, pcol, pJ);
     return hipGetLastError();
 }
 
@@ -346,7 +331,7 @@ hipError_t launch_split_bf16x2(int n, const int *prow, int64_t pnnz, const float
 
 hipError_t launch_quantize_fp8(int n, const int *row_ptr, const float *J, uint8_t *J8, float *scale,
                                hipStream_t st) {
-    quantize_fp8_rows<<<(n + 255) / 256, 256, 0, st>>>(n, row_ptr, J, J8, scale);
+    quantize_fp8_rows<<<(n + 256 / kRowLanes - 1) / (256 / kRowLanes), 256, 0, st>>>(n, row_ptr, J, J8, scale);
     return hipGetLastError();
 }
 

@@ -44,9 +44,11 @@
 
 #include "sb_device.hpp"
 #include "sb_kernels.hpp"
+#include "sb_scan.hpp"
 #include "sb_stream_kernels.hpp"
 #include "sb_stream_chunk.hpp"
 #include "sb_stream_mfma.hpp"
+#include "sb_union.hpp"
 
 namespace sbt {
 
@@ -55,77 +57,21 @@ namespace {
 constexpr int kBR = kMfmaRows;
 constexpr int kBK = kMfmaK;
 constexpr int kChunkSteps = 4;   // K-steps whose sign records are staged in LDS at once
-constexpr int kScanThreads = 1024;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// Walks the union of block b's rows (padded CSR; a row's own column marks
-// its padding) in ascending column order, calling f(column, at[kBR]) with
-// at[r] the row's entry for that column or -1.
-template <class F>
-__device__ __forceinline__ void block_union(int n, const int *prow, const int *pcol, int b, F &&f) {
-    int pos[kBR], end[kBR], head[kBR];  // head: the row's next column (INT32_MAX: none)
-#pragma unroll
-    for (int r = 0; r < kBR; ++r) {
-        const int i = b * kBR + r;
-        pos[r] = i < n ? prow[i] : 0;
-        end[r] = i < n ? prow[i + 1] : 0;
-        while (pos[r] < end[r] && pcol[end[r] - 1] == i) --end[r];  // drop the padding
-        head[r] = pos[r] < end[r] ? pcol[pos[r]] : INT32_MAX;
-    }
-    while (true) {
-        int c = INT32_MAX;
-#pragma unroll
-        for (int r = 0; r < kBR; ++r) c = min(c, head[r]);
-        if (c == INT32_MAX) break;
-        int at[kBR];
-#pragma unroll
-        for (int r = 0; r < kBR; ++r) {
-            at[r] = -1;
-            if (head[r] == c) {
-                at[r] = pos[r]++;
-                head[r] = pos[r] < end[r] ? pcol[pos[r]] : INT32_MAX;
-            }
-        }
-        f(c, at);
-    }
-}
-
 __global__ __launch_bounds__(256) void mfma_count(int n, int nb, const int *__restrict__ prow,
                                                   const int *__restrict__ pcol, int *__restrict__ cnt) {
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b >= nb) return;
-    int d = 0;
-    block_union(n, prow, pcol, b, [&](int, const int *) { ++d; });
-    cnt[b] = (d + kBK - 1) / kBK;
+    const int i = blockIdx.x * 256 + threadIdx.x, b = i / kBR;
+    const int d = union_size<kBR>(RowWalk(n, prow, pcol, i));
+    if (i % kBR == 0 && b < nb) cnt[b] = (d + kBK - 1) / kBK;
 }
 
-// cnt[0..nb) -> off[0..nb] (exclusive prefix sums, off[nb] = total); one
-// workgroup, each thread a contiguous range.
-__global__ __launch_bounds__(kScanThreads) void mfma_scan(int nb, const int *__restrict__ cnt,
+__global__ __launch_bounds__(kScanThreads) void mfma_scan(int nb, int range, const int *__restrict__ cnt,
                                                           int *__restrict__ off) {
-    __shared__ int tot[kScanThreads];
-    const int t = threadIdx.x;
-    const int per = (nb + kScanThreads - 1) / kScanThreads;
-    const int b0 = min(nb, t * per), b1 = min(nb, b0 + per);
-    int sum = 0;
-    for (int b = b0; b < b1; ++b) sum += cnt[b];
-    tot[t] = sum;
-    __syncthreads();
-    for (int d = 1; d < kScanThreads; d <<= 1) {
-        const int v = t >= d ? tot[t - d] : 0;
-        __syncthreads();
-        tot[t] += v;
-        __syncthreads();
-    }
-    int at = tot[t] - sum;
-    for (int b = b0; b < b1; ++b) {
-        off[b] = at;
-        at += cnt[b];
-    }
-    if (t == kScanThreads - 1) off[nb] = tot[t];
+    scan_lengths(nb, range, [&](int b) { return cnt[b]; }, off);
 }
 
 // FP32 -> BF16, round to nearest even (finite values).
@@ -149,68 +95,69 @@ __device__ __forceinline__ void bf16_triple(float v, uint32_t (&t)[3]) {
 // 16 ((u % 32) / 8) + r in K-step u / 32 (FP8: byte e of the lane's word;
 // BF16 terms: term k in words 2 k and 2 k + 1, 16 bits per element); zeros
 // where a row has no coupling and in the padding, whose column repeats the
-// last listed one.  A lane's word is assembled over 8 consecutive listed
-// columns and stored whole.
+// last listed one.  A lane is a row of the block: it assembles its words over
+// 8 consecutive listed columns and stores them whole, next to the 15 others'.
 template <int JP>
 __global__ __launch_bounds__(256) void mfma_fill(int nb, StreamArgs A, const int *__restrict__ koff,
                                                  int *__restrict__ kcol, uint64_t *__restrict__ kA) {
     constexpr int W = mfma_words(JP);
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b >= nb) return;
-    const int ks0 = koff[b], u1 = (koff[b + 1] - ks0) * kBK;
-    uint64_t buf[kBR][W];
+    const int i = blockIdx.x * 256 + threadIdx.x, b = i / kBR, r = i % kBR;
+    RowWalk walk(A.n, A.row_ptr, A.col, i);
+    const int ks0 = b < nb ? koff[b] : 0, u1 = b < nb ? (koff[b + 1] - ks0) * kBK : 0;
+    int last = 0;
+    for (int u = 0; __any(u < u1); u += 8) {
+        int at[8], mine = 0;
 #pragma unroll
-    for (int r = 0; r < kBR; ++r)
+        for (int e = 0; e < 8; ++e) {
+            const int c = group_min<kBR>(walk.head);
+            at[e] = walk.take(c);
+            last = c == kNoColumn ? last : c;
+            mine = e == r ? last : mine;
+        }
+        if (u >= u1) continue;
+        uint64_t buf[W] = {};
+        if constexpr (JP == kJFp8) {
+            uint64_t code[8];
 #pragma unroll
-        for (int w = 0; w < W; ++w) buf[r][w] = 0;
-    auto flush = [&](int u) {  // u: the last listed column of a group of 8
-        const size_t lane0 = static_cast<size_t>(ks0 + u / kBK) * 64 + 16 * ((u % kBK) / 8);
+            for (int e = 0; e < 8; ++e) code[e] = at[e] >= 0 ? A.J8[at[e]] : 0u;
 #pragma unroll
-        for (int r = 0; r < kBR; ++r)
+            for (int e = 0; e < 8; ++e) buf[0] |= code[e] << (8 * e);
+        } else {
+            float v[8];      // the coupling, or of BF16 pairs
+            uint32_t v2[8];  // both terms
 #pragma unroll
-            for (int w = 0; w < W; ++w) {
-                kA[(lane0 + r) * W + w] = buf[r][w];
-                buf[r][w] = 0;
+            for (int e = 0; e < 8; ++e) {
+                const bool there = at[e] >= 0;
+                if constexpr (JP == kJBf16x2)
+                    v2[e] = there ? A.J2[at[e]] : 0u;
+                else if constexpr (JP == kJFp8Blk)  // the CSR step's decoded value
+                    v[e] = there ? A.blkscale[at[e] / kStreamChunk] * e4m3_to_f32<0>(A.J8[at[e]]) : 0.0f;
+                else
+                    v[e] = there ? A.J[at[e]] : 0.0f;
             }
-    };
-    int u = 0, last = 0;
-    block_union(A.n, A.row_ptr, A.col, b, [&](int c, const int *at) {
-        kcol[static_cast<size_t>(ks0) * kBK + u] = c;
-        const int e = u % 8;
 #pragma unroll
-        for (int r = 0; r < kBR; ++r) {
-            if (at[r] < 0) continue;
-            if constexpr (JP != kJFp8) {
+            for (int e = 0; e < 8; ++e) {
                 uint32_t term[3] = {0u, 0u, 0u};
-                if constexpr (JP == kJBf16) {
-                    term[0] = bf16_bits(A.J[at[r]]);
+                if constexpr (JP == kJBf16x2) {
+                    term[0] = v2[e] >> 16;
+                    term[1] = v2[e] & 0xFFFFu;
+                } else if constexpr (JP == kJBf16) {
+                    term[0] = bf16_bits(v[e]);
                 } else if constexpr (JP == kJFp16) {
-                    term[0] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(A.J[at[r]]));
-                } else if constexpr (JP == kJBf16x2) {
-                    term[0] = A.J2[at[r]] >> 16;
-                    term[1] = A.J2[at[r]] & 0xFFFFu;
-                } else if constexpr (JP == kJFp8Blk) {  // the CSR step's decoded value
-                    bf16_triple(A.blkscale[at[r] / kStreamChunk] * e4m3_to_f32<0>(A.J8[at[r]]), term);
+                    term[0] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(v[e]));
                 } else {
-                    bf16_triple(A.J[at[r]], term);
+                    bf16_triple(v[e], term);
                 }
                 const int sh = 16 * (e % 4);
 #pragma unroll
                 for (int k = 0; k < W / 2; ++k)
-#pragma unroll
-                    for (int w = 0; w < 2; ++w)
-                        if (e / 4 == w) buf[r][2 * k + w] |= static_cast<uint64_t>(term[k]) << sh;
-            } else {
-                buf[r][0] |= static_cast<uint64_t>(A.J8[at[r]]) << (8 * e);
+                    buf[2 * k + e / 4] |= static_cast<uint64_t>(at[e] >= 0 ? term[k] : 0u) << sh;
             }
         }
-        last = c;
-        if (e == 7) flush(u);
-        ++u;
-    });
-    for (; u < u1; ++u) {
-        kcol[static_cast<size_t>(ks0) * kBK + u] = last;
-        if (u % 8 == 7) flush(u);
+        if (r < 8) kcol[static_cast<size_t>(ks0) * kBK + u + r] = mine;
+        const size_t lane = static_cast<size_t>(ks0 + u / kBK) * 64 + 16 * ((u % kBK) / 8) + r;
+#pragma unroll
+        for (int w = 0; w < W; ++w) kA[lane * W + w] = buf[w];
     }
 }
 
@@ -503,9 +450,9 @@ size_t mfma_ksteps_bound(int n, int64_t nnz) {
 
 hipError_t launch_mfma_plan(int jprec, const StreamArgs &A, const MfmaArgs &P, hipStream_t st) {
     const int nb = (A.n + kBR - 1) / kBR;
-    const unsigned gr = static_cast<unsigned>((nb + 255) / 256);
+    const unsigned gr = static_cast<unsigned>((nb * static_cast<int64_t>(kBR) + 255) / 256);
     mfma_count<<<gr, 256, 0, st>>>(A.n, nb, A.row_ptr, A.col, P.kcnt);
-    mfma_scan<<<1, kScanThreads, 0, st>>>(nb, P.kcnt, P.koff);
+    mfma_scan<<<scan_grid(nb), kScanThreads, 0, st>>>(nb, scan_range(nb), P.kcnt, P.koff);
     switch (jprec) {
         case kJFp8: mfma_fill<kJFp8><<<gr, 256, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
         case kJBf16x2: mfma_fill<kJBf16x2><<<gr, 256, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;

@@ -18,8 +18,10 @@
 
 #include "sb_device.hpp"
 #include "sb_kernels.hpp"
+#include "sb_scan.hpp"
 #include "sb_stream_kernels.hpp"
 #include "sb_stream_chunk.hpp"
+#include "sb_union.hpp"
 
 namespace sbt {
 
@@ -27,7 +29,6 @@ namespace {
 
 constexpr int kR = kQuadRows;
 constexpr int kChunk = kStreamChunk;
-constexpr int kScanThreads = 1024;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // A stored coupling of the padded rows decoded to FP32 exactly as the CSR
@@ -44,90 +45,48 @@ __device__ __forceinline__ float stored_coupling(const StreamArgs &A, int p, int
         return A.J[p];
 }
 
-// Walks the union of the quad's rows (padded CSR; a row's own column marks
-// its padding) in ascending column order, calling f(column, p[kR]) with
-// p[r] the row's entry for that column or -1.
-template <class F>
-__device__ __forceinline__ void quad_union(int n, const int *prow, const int *pcol, int quad, F &&f) {
-    int pos[kR], end[kR];
-#pragma unroll
-    for (int r = 0; r < kR; ++r) {
-        const int i = quad * kR + r;
-        pos[r] = i < n ? prow[i] : 0;
-        end[r] = i < n ? prow[i + 1] : 0;
-        while (pos[r] < end[r] && pcol[end[r] - 1] == i) --end[r];  // drop the padding
-    }
-    while (true) {
-        int c = INT32_MAX;
-#pragma unroll
-        for (int r = 0; r < kR; ++r)
-            if (pos[r] < end[r]) c = min(c, pcol[pos[r]]);
-        if (c == INT32_MAX) break;
-        int at[kR];
-#pragma unroll
-        for (int r = 0; r < kR; ++r) {
-            at[r] = -1;
-            if (pos[r] < end[r] && pcol[pos[r]] == c) at[r] = pos[r]++;
-        }
-        f(c, at);
-    }
-}
-
 __global__ __launch_bounds__(256) void quad_count(int n, int nq, const int *__restrict__ prow,
                                                   const int *__restrict__ pcol, int *__restrict__ cnt) {
-    const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= nq) return;
-    int d = 0;
-    quad_union(n, prow, pcol, q, [&](int, const int *) { ++d; });
-    cnt[q] = (d + kChunk - 1) / kChunk * kChunk;
+    const int i = blockIdx.x * 256 + threadIdx.x, q = i / kR;
+    const int d = union_size<kR>(RowWalk(n, prow, pcol, i));
+    if (i % kR == 0 && q < nq) cnt[q] = (d + kChunk - 1) / kChunk * kChunk;
 }
 
-// cnt[0..nq) -> qoff[0..nq] (exclusive prefix sums, qoff[nq] = total); one
-// workgroup, each thread a contiguous range.
-__global__ __launch_bounds__(kScanThreads) void quad_scan(int nq, const int *__restrict__ cnt,
+__global__ __launch_bounds__(kScanThreads) void quad_scan(int nq, int range, const int *__restrict__ cnt,
                                                           int *__restrict__ qoff) {
-    __shared__ int tot[kScanThreads];
-    const int t = threadIdx.x;
-    const int per = (nq + kScanThreads - 1) / kScanThreads;
-    const int q0 = min(nq, t * per), q1 = min(nq, q0 + per);
-    int sum = 0;
-    for (int q = q0; q < q1; ++q) sum += cnt[q];
-    tot[t] = sum;
-    __syncthreads();
-    for (int d = 1; d < kScanThreads; d <<= 1) {
-        const int v = t >= d ? tot[t - d] : 0;
-        __syncthreads();
-        tot[t] += v;
-        __syncthreads();
-    }
-    int at = tot[t] - sum;
-    for (int q = q0; q < q1; ++q) {
-        qoff[q] = at;
-        at += cnt[q];
-    }
-    if (t == kScanThreads - 1) qoff[nq] = tot[t];
+    scan_lengths(nq, range, [&](int q) { return cnt[q]; }, qoff);
 }
 
+// Lists a quad's columns, eight at a time (the padding to whole chunks: a
+// listed column, no coupling).
 template <int JP>
 __global__ __launch_bounds__(256) void quad_fill(int nq, StreamArgs A, const int *__restrict__ qoff,
                                                  int *__restrict__ qcol, float *__restrict__ qJ) {
-    const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= nq) return;
-    int u = qoff[q];
-    const int u1 = qoff[q + 1];
+    const int i = blockIdx.x * 256 + threadIdx.x, q = i / kR, r = i % kR;
+    RowWalk w(A.n, A.row_ptr, A.col, i);
+    int u = q < nq ? qoff[q] : 0;
+    const int u1 = q < nq ? qoff[q + 1] : 0;
     int last = 0;
-    quad_union(A.n, A.row_ptr, A.col, q, [&](int c, const int *at) {
-        qcol[u] = c;
+    static_assert(kChunk == 2 * kR, "a lane stores two of a chunk's columns");
+    for (; __any(u < u1); u += kChunk) {
+        int at[kChunk], c0 = 0, c1 = 0;
 #pragma unroll
-        for (int r = 0; r < kR; ++r)
-            qJ[static_cast<size_t>(u) * kR + r] = at[r] >= 0 ? stored_coupling<JP>(A, at[r], q * kR + r) : 0.0f;
-        last = c;
-        ++u;
-    });
-    for (; u < u1; ++u) {  // padding to whole chunks: a listed column, no coupling
-        qcol[u] = last;
+        for (int e = 0; e < kChunk; ++e) {
+            const int c = group_min<kR>(w.head);
+            at[e] = w.take(c);
+            last = c == kNoColumn ? last : c;
+            if (e % 2 == 0)
+                c0 = e / 2 == r ? last : c0;
+            else
+                c1 = e / 2 == r ? last : c1;
+        }
+        if (u >= u1) continue;
+        float v[kChunk];
 #pragma unroll
-        for (int r = 0; r < kR; ++r) qJ[static_cast<size_t>(u) * kR + r] = 0.0f;
+        for (int e = 0; e < kChunk; ++e) v[e] = at[e] >= 0 ? stored_coupling<JP>(A, at[e], i) : 0.0f;
+        *reinterpret_cast<int2 *>(qcol + u + 2 * r) = make_int2(c0, c1);
+#pragma unroll
+        for (int e = 0; e < kChunk; ++e) qJ[static_cast<size_t>(u + e) * kR + r] = v[e];
     }
 }
 
@@ -227,9 +186,9 @@ size_t quad_cols_bound(int n, int64_t nnz) {
 
 hipError_t launch_quad_plan(int jprec, const StreamArgs &A, const QuadArgs &Q, hipStream_t st) {
     const int nq = (A.n + kR - 1) / kR;
-    const unsigned g = static_cast<unsigned>((nq + 255) / 256);
+    const unsigned g = static_cast<unsigned>((nq * static_cast<int64_t>(kR) + 255) / 256);
     quad_count<<<g, 256, 0, st>>>(A.n, nq, A.row_ptr, A.col, Q.qcnt);
-    quad_scan<<<1, kScanThreads, 0, st>>>(nq, Q.qcnt, Q.qoff);
+    quad_scan<<<scan_grid(nq), kScanThreads, 0, st>>>(nq, scan_range(nq), Q.qcnt, Q.qoff);
     switch (jprec) {
         case kJFp8: quad_fill<kJFp8><<<g, 256, 0, st>>>(nq, A, Q.qoff, Q.qcol, Q.qJ); break;
         case kJFp8Blk: quad_fill<kJFp8Blk><<<g, 256, 0, st>>>(nq, A, Q.qoff, Q.qcol, Q.qJ); break;
