@@ -40,6 +40,8 @@
 // layout they touch 16 rows x 64 bytes and the step ran 1.4 x slower.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstdint>
 
 #include "sb_device.hpp"
@@ -219,6 +221,54 @@ __global__ __launch_bounds__(256) void mfma_state(int n, int M, bool to_tiles, c
     }
 }
 
+// One K-step of a tile: acc[t] += (-sgn of 8 columns, agents of tile t) x
+// (the row's couplings on them).
+template <int JP>
+__device__ __forceinline__ void mfma_kstep(const uint32_t (&s8)[8], const uint64_t (&a8)[mfma_words(JP)],
+                                           f32x4 (&acc)[kMfmaGroup / 16]) {
+    constexpr int T = kMfmaGroup / 16, W = mfma_words(JP);
+    // -sgn(x_j): a set sign bit (x >= 0) gives -1
+    if constexpr (JP != kJFp8) {
+        // 16-bit operands: +-1 is 0x3F80 | sign in BF16, 0x3C00 | sign in FP16
+        constexpr uint32_t kOne = JP == kJFp16 ? 0x3C003C00u : 0x3F803F80u;
+        uint32_t yq[4];  // columns 2q, 2q+1 at bits 0 and 16
+#pragma unroll
+        for (int q = 0; q < 4; ++q) yq[q] = s8[2 * q] | (s8[2 * q + 1] << 16);
+        u32x4 aop[W / 2];  // the terms, largest first
+#pragma unroll
+        for (int k = 0; k < W / 2; ++k)
+            aop[k] = u32x4{static_cast<uint32_t>(a8[2 * k]), static_cast<uint32_t>(a8[2 * k] >> 32),
+                           static_cast<uint32_t>(a8[2 * k + 1]), static_cast<uint32_t>(a8[2 * k + 1] >> 32)};
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            u32x4 bv;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bv[q] = ((yq[q] << (15 - t)) & 0x80008000u) | kOne;
+#pragma unroll
+            for (int k = 0; k < W / 2; ++k) {
+                if constexpr (JP == kJFp16)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                        __builtin_bit_cast(f16x8, bv), __builtin_bit_cast(f16x8, aop[k]), acc[t], 0, 0, 0);
+                else
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, bv), __builtin_bit_cast(bf16x8, aop[k]), acc[t], 0, 0, 0);
+            }
+        }
+    } else {
+        // byte e of xl / xh: the sign byte of column e / e + 4
+        const uint32_t xl = s8[0] | (s8[1] << 8) | (s8[2] << 16) | (s8[3] << 24);
+        const uint32_t xh = s8[4] | (s8[5] << 8) | (s8[6] << 16) | (s8[7] << 24);
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const uint32_t lo = ((xl << (7 - t)) & 0x80808080u) | 0x38383838u;  // e4m3 +-1
+            const uint32_t hi = ((xh << (7 - t)) & 0x80808080u) | 0x38383838u;
+            const long bop = static_cast<long>((static_cast<uint64_t>(hi) << 32) | lo);
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(bop, static_cast<long>(a8[0]),
+                                                                acc[t], 0, 0, 0);
+        }
+    }
+}
+
 }  // namespace
 
 // One dSB step: a wave = one block of 16 rows x one group of 128 agents.
@@ -372,46 +422,7 @@ __global__ __launch_bounds__(256) void sb_stream_mfma(StreamArgs A, int k, const
                 for (int w = 0; w < W; ++w) a8[w] = an[w];
                 if (ks + 1 < ks1) load_operand(ks + 1);
             }
-            // -sgn(x_j): a set sign bit (x >= 0) gives -1
-            if constexpr (JP != kJFp8) {
-                // 16-bit operands: +-1 is 0x3F80 | sign in BF16, 0x3C00 | sign in FP16
-                constexpr uint32_t kOne = JP == kJFp16 ? 0x3C003C00u : 0x3F803F80u;
-                uint32_t yq[4];  // columns 2q, 2q+1 at bits 0 and 16
-#pragma unroll
-                for (int q = 0; q < 4; ++q) yq[q] = s8[2 * q] | (s8[2 * q + 1] << 16);
-                u32x4 aop[W / 2];  // the terms, largest first
-#pragma unroll
-                for (int k = 0; k < W / 2; ++k)
-                    aop[k] = u32x4{static_cast<uint32_t>(a8[2 * k]), static_cast<uint32_t>(a8[2 * k] >> 32),
-                                   static_cast<uint32_t>(a8[2 * k + 1]), static_cast<uint32_t>(a8[2 * k + 1] >> 32)};
-#pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    u32x4 bv;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) bv[q] = ((yq[q] << (15 - t)) & 0x80008000u) | kOne;
-#pragma unroll
-                    for (int k = 0; k < W / 2; ++k) {
-                        if constexpr (JP == kJFp16)
-                            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                                __builtin_bit_cast(f16x8, bv), __builtin_bit_cast(f16x8, aop[k]), acc[t], 0, 0, 0);
-                        else
-                            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                __builtin_bit_cast(bf16x8, bv), __builtin_bit_cast(bf16x8, aop[k]), acc[t], 0, 0, 0);
-                    }
-                }
-            } else {
-                // byte e of xl / xh: the sign byte of column e / e + 4
-                const uint32_t xl = s8[0] | (s8[1] << 8) | (s8[2] << 16) | (s8[3] << 24);
-                const uint32_t xh = s8[4] | (s8[5] << 8) | (s8[6] << 16) | (s8[7] << 24);
-#pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    const uint32_t lo = ((xl << (7 - t)) & 0x80808080u) | 0x38383838u;  // e4m3 +-1
-                    const uint32_t hi = ((xh << (7 - t)) & 0x80808080u) | 0x38383838u;
-                    const long bop = static_cast<long>((static_cast<uint64_t>(hi) << 32) | lo);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(bop, static_cast<long>(a8[0]),
-                                                                        acc[t], 0, 0, 0);
-                }
-            }
+            mfma_kstep<JP>(s8, a8, acc);
         }
     }
 
@@ -441,6 +452,272 @@ __global__ __launch_bounds__(256) void sb_stream_mfma(StreamArgs A, int k, const
         st_stream<NT>(yv, reinterpret_cast<f32x4 *>(y + tile + 256 * t));
     }
     reinterpret_cast<uint32_t *>(Sout)[(static_cast<size_t>(i) * R + ab) * 4 + g] = word;
+}
+
+// ------------------------------------------------------- steps on the chip
+//
+// A streamed step moves 16 bytes of x and y per spin and agent, and a state
+// of 70 to 100 MB misses the XCDs' L2s, so the step above is bound by the
+// Infinity Cache and by its launch (8484 x 1024, FP32: 24 us, 134 MB).  The
+// registers and LDS of the chip hold such a state.  sb_mfma_gang keeps it
+// there for a run of steps: a gang is one group of 128 agents over all rows,
+// its blocks are spread over `bands` workgroups of eight waves, a wave holds
+// up to three tiles (two in registers, one in LDS), and what the workgroups
+// exchange each step are the sign records, 16 bytes per row.  The arithmetic
+// of a tile is that of sb_stream_mfma in its order.
+//
+// The records are written and read with agent-scope atomics, which are
+// coherent over the XCDs; nothing else that is written is read by another
+// workgroup, so a step needs no cache write-back and no invalidation (which
+// would cost it the operands in the L2), only that a workgroup's stores are
+// done before it arrives.  Gangs are queued one after the other and taken
+// band by band by running workgroups, so a gang that has been started gets
+// all its bands as long as `bands` workgroups fit the device beside what else
+// runs there (an eighth of it for M = 1024).  Waits are
+// bounded: past kGangWait ticks of the 100 MHz clock the run is given up
+// and ctl[1] set (the solve's energies are then NaN).
+//
+// A step of 8484 x 1024: FP32 24.3 -> 10.2 us, FP8 23.6 -> 8.1; 1480 x 256
+// 5.2 -> 4.6, 4.9 -> 4.8.  What is left is the meeting (2.3 us), the latency
+// of the records (1.7) and the update of 16 or 17 tiles per CU.  Two
+// workgroups of four waves per CU, of different gangs, do not hide one
+// another's meeting (13.5 us): a gang of 64 meets more slowly.
+constexpr long long kGangWait = 1000000000LL;
+constexpr int kGangHead = 32;  // control words before the gangs' flags: work counter, verdict
+// flags of a gang, in cache lines of their own
+__host__ __device__ constexpr int gang_words(int bands) { return (bands + 31) / 32 * 32; }
+constexpr int kGangSlots = kChunkSteps * kBK;
+constexpr int kGangRec = kGangSlots + kGangSlots / 8;  // records of a chunk, padded (uint4)
+
+// Every workgroup of a gang says how many steps it has done in a word of its
+// own and waits until all have done as many: 32 additions to one counter
+// took longer (8 gangs of 32 workgroups: 2.65 against 2.35 us,
+// and 8.6 with the counters in one cache line).
+__device__ __forceinline__ bool gang_meet(int *flags, int bands, int band, int done, int *fault, int *stop) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's records are out
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        if (threadIdx.x == 0)
+            __hip_atomic_store(flags + band, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const long long t0 = wall_clock64();
+        bool bad = false;
+        for (int w0 = 0; w0 < bands && !bad; w0 += 64) {
+            const int *mine = flags + min(w0 + static_cast<int>(threadIdx.x), bands - 1);
+            for (int tries = 1; __any(__hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < done); ++tries) {
+                if (tries % 64 == 0) {
+                    bad = __hip_atomic_load(fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+                    if (!bad && wall_clock64() - t0 > kGangWait) {
+                        __hip_atomic_store(fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        bad = true;
+                    }
+                    if (__any(bad)) break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+            bad = __any(bad);
+        }
+        if (threadIdx.x == 0) *stop = bad;
+    }
+    __syncthreads();
+    return *stop != 0;
+}
+
+// (w << 1) | (x >= 0): the comparison's carry added in.
+__device__ __forceinline__ uint32_t shift_in(uint32_t w, float x) {
+    asm("v_cmp_le_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(w) : "v"(x) : "vcc");
+    return w;
+}
+
+template <int JP>
+__global__ __launch_bounds__(64 * kGangWaves, 2) void sb_mfma_gang(
+    StreamArgs A, int k0, int k1, const int *__restrict__ koff, const int *__restrict__ kcol,
+    const uint64_t *__restrict__ kA, const float *__restrict__ h, const float *__restrict__ rowscale,
+    float *__restrict__ x, float *__restrict__ y, uint8_t *S0, uint8_t *S1, int bands, int items, int *ctl) {
+    constexpr int T = kMfmaGroup / 16, W = mfma_words(JP), kRegTiles = kGangRegTiles, kTiles = kGangTiles;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int item_s, stop_s;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int g = lane >> 4, c = lane & 15;
+    uint4 *rec = reinterpret_cast<uint4 *>(smem) + wave * kGangRec;
+    // the LDS tile: x then y, lane by lane
+    f32x4 *spare = reinterpret_cast<f32x4 *>(smem + kGangWaves * kGangRec * 16) + wave * 2 * T * 64 + lane;
+    const int M = A.M, R = mfma_groups(M), nb = (A.n + kBR - 1) / kBR;
+    const float c0 = static_cast<float>(A.scal[0]);
+    for (;;) {
+        if (threadIdx.x == 0) item_s = atomicAdd(ctl, 1);
+        __syncthreads();
+        const int item = __builtin_amdgcn_readfirstlane(item_s);
+        __syncthreads();
+        if (item >= items) return;
+        const int ab = item / bands, band = item % bands;
+        const int b0 = static_cast<int>(static_cast<int64_t>(nb) * band / bands);
+        const int b1 = static_cast<int>(static_cast<int64_t>(nb) * (band + 1) / bands);
+        int *flags = ctl + gang_words(bands) * ab + kGangHead;
+        uint32_t live = 0;  // this lane's agents below M: byte r, bit t
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) live |= kMfmaGroup * ab + 16 * t + 4 * g + r < M ? 1u << (8 * r + t) : 0u;
+        f32x4 xs[kRegTiles][T], ys[kRegTiles][T];
+        float hv[kTiles], sc[kTiles];
+        int bs[kTiles], ks0[kTiles], nk[kTiles], cn[kTiles][2];
+        bool has[kTiles];
+        auto tile_of = [&](int i) { return (static_cast<size_t>(bs[i]) * R + ab) * (kBR * kMfmaGroup) + 4 * lane; };
+#pragma unroll
+        for (int i = 0; i < kTiles; ++i) {
+            bs[i] = b0 + wave + kGangWaves * i;
+            has[i] = bs[i] < b1;
+            if (!has[i]) bs[i] = 0;
+            ks0[i] = koff[bs[i]];
+            nk[i] = has[i] ? koff[bs[i] + 1] - ks0[i] : 0;
+            const int row = min(bs[i] * kBR + c, A.n - 1);
+            hv[i] = h[row];
+            sc[i] = JP == kJFp8 ? rowscale[row] : 1.0f;
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                const int u = lane + 64 * hh;
+                cn[i][hh] = u < nk[i] * kBK ? kcol[static_cast<size_t>(ks0[i]) * kBK + u] : 0;
+            }
+            if (has[i]) {
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const f32x4 xv = *reinterpret_cast<const f32x4 *>(x + tile_of(i) + 256 * t);
+                    const f32x4 yv = *reinterpret_cast<const f32x4 *>(y + tile_of(i) + 256 * t);
+                    if (i < kRegTiles) {
+                        xs[i][t] = xv;
+                        ys[i][t] = yv;
+                    } else {
+                        spare[64 * t] = xv;
+                        spare[64 * (T + t)] = yv;
+                    }
+                }
+            }
+        }
+        bool stop = false;
+        for (int k = k0; k < k1 && !stop; ++k) {
+            const uint8_t *Sin = ((k - k0) & 1) ? S1 : S0;
+            uint8_t *Sout = ((k - k0) & 1) ? S0 : S1;
+            const float gk = A.sched[k];
+            auto load_rec = [&](int col) -> uint4 {
+                const uint64_t *p = reinterpret_cast<const uint64_t *>(Sin + (static_cast<size_t>(col) * R + ab) * 16);
+                const uint64_t a = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint64_t b = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return uint4{static_cast<uint32_t>(a), static_cast<uint32_t>(a >> 32), static_cast<uint32_t>(b),
+                             static_cast<uint32_t>(b >> 32)};
+            };
+            uint4 rn[kTiles][2];
+#pragma unroll
+            for (int i = 0; i < kTiles; ++i)
+                if (nk[i] > 0) {
+                    rn[i][0] = load_rec(cn[i][0]);
+                    if (nk[i] > 2) rn[i][1] = load_rec(cn[i][1]);
+                }
+            uint64_t an[W];
+            auto load_operand = [&](int ks) {
+#pragma unroll
+                for (int w = 0; w < W; ++w) an[w] = kA[(static_cast<size_t>(ks) * 64 + lane) * W + w];
+            };
+            if (nk[0] > 0) load_operand(ks0[0]);
+#pragma unroll
+            for (int i = 0; i < kTiles; ++i) {
+                if (!has[i]) continue;
+                f32x4 acc[T];
+#pragma unroll
+                for (int t = 0; t < T; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int j = 0; j * kChunkSteps < nk[i]; ++j) {
+                    if (j > 0) {
+#pragma unroll
+                        for (int hh = 0; hh < 2; ++hh) {
+                            const int u = min(j * kGangSlots + lane + 64 * hh, nk[i] * kBK - 1);
+                            rn[i][hh] = load_rec(kcol[static_cast<size_t>(ks0[i]) * kBK + u]);
+                        }
+                    }
+                    __builtin_amdgcn_wave_barrier();  // the LDS reads of the chunk before come first
+#pragma unroll
+                    for (int hh = 0; hh < 2; ++hh) {
+                        const int sl = lane + 64 * hh;
+                        if (hh == 0 || nk[i] - j * kChunkSteps > 2) rec[sl + sl / 8] = rn[i][hh];
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    const int kend = min(kChunkSteps, nk[i] - j * kChunkSteps);
+                    for (int kk = 0; kk < kend; ++kk) {
+                        const int ks = ks0[i] + j * kChunkSteps + kk;
+                        uint32_t s8[8];
+                        uint64_t a8[W];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const int sl = kk * kBK + 8 * g + e;
+                            s8[e] = reinterpret_cast<const uint8_t *>(rec + sl + sl / 8)[c];
+                        }
+#pragma unroll
+                        for (int w = 0; w < W; ++w) a8[w] = an[w];
+                        if (ks + 1 < ks0[i] + nk[i])
+                            load_operand(ks + 1);
+                        else if (i + 1 < kTiles && nk[i + 1 < kTiles ? i + 1 : i] > 0)
+                            load_operand(ks0[i + 1 < kTiles ? i + 1 : i]);
+                        mfma_kstep<JP>(s8, a8, acc);
+                    }
+                }
+                uint32_t bits[4] = {0u, 0u, 0u, 0u};  // of agent 16 t + 4 g + r: bit t of word r
+#pragma unroll
+                for (int t = T - 1; t >= 0; --t) {
+                    f32x4 xv, yv;
+                    if (i < kRegTiles) {
+                        xv = xs[i < kRegTiles ? i : 0][t];
+                        yv = ys[i < kRegTiles ? i : 0][t];
+                    } else {
+                        xv = spare[64 * t];
+                        yv = spare[64 * (T + t)];
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float xr = xv[r], yr = yv[r];
+                        sb_update(xr, yr, __builtin_fmaf(-sc[i], acc[t][r], hv[i]), c0, gk, A.dt, A.dta0);
+                        xv[r] = xr;
+                        yv[r] = yr;
+                        bits[r] = shift_in(bits[r], xr);
+                    }
+                    if (i < kRegTiles) {
+                        xs[i < kRegTiles ? i : 0][t] = xv;
+                        ys[i < kRegTiles ? i : 0][t] = yv;
+                    } else {
+                        spare[64 * t] = xv;
+                        spare[64 * (T + t)] = yv;
+                    }
+                }
+                const uint32_t word = (bits[0] | bits[1] << 8 | bits[2] << 16 | bits[3] << 24) & live;
+                const int row = bs[i] * kBR + c;
+                if (row < A.n)
+                    __hip_atomic_store(reinterpret_cast<uint32_t *>(Sout) + (static_cast<size_t>(row) * R + ab) * 4 + g,
+                                       word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (k + 1 < k1) stop = gang_meet(flags, bands, band, k + 1 - k0, ctl + 1, &stop_s);
+        }
+#pragma unroll
+        for (int i = 0; i < kTiles; ++i) {
+            if (!has[i]) continue;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                f32x4 xv, yv;
+                if (i < kRegTiles) {
+                    xv = xs[i < kRegTiles ? i : 0][t];
+                    yv = ys[i < kRegTiles ? i : 0][t];
+                } else {
+                    xv = spare[64 * t];
+                    yv = spare[64 * (T + t)];
+                }
+                *reinterpret_cast<f32x4 *>(x + tile_of(i) + 256 * t) = xv;
+                *reinterpret_cast<f32x4 *>(y + tile_of(i) + 256 * t) = yv;
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Energies of a run that was given up are NaN.
+__global__ void mfma_gang_verdict(int M, const int *__restrict__ ctl, double *__restrict__ energy) {
+    const int m = blockIdx.x * blockDim.x + threadIdx.x;
+    if (m < M && ctl[1] != 0) energy[m] = NAN;
 }
 
 size_t mfma_ksteps_bound(int n, int64_t nnz) {
@@ -511,6 +788,55 @@ hipError_t launch_stream_mfma(int jprec, const StreamArgs &A, const MfmaArgs &P,
         case kJFp16: return launch_mfma_form<kJFp16>(A, P, k, x, y, Sin, Sout, st);
         default: return hipErrorInvalidValue;
     }
+}
+
+int mfma_gang_bands(int n, int M, int cus) {
+    const int nb = (n + kBR - 1) / kBR, R = mfma_groups(M);
+    const int bands = std::min(cus / std::min(R, 8), nb);
+    if (bands < 1 || n < kGangHead + gang_words(bands) * R) return 0;
+    return (nb + bands - 1) / bands <= kGangTiles * kGangWaves ? bands : 0;
+}
+
+namespace {
+
+template <int JP>
+hipError_t launch_gang_form(const StreamArgs &A, const MfmaArgs &P, int k0, int k1, float *x, float *y,
+                            uint8_t *S0, uint8_t *S1, int cus, int *ctl,
+                            hipStream_t st) {
+    const int R = mfma_groups(A.M), nb = (A.n + kBR - 1) / kBR;
+    const int bands = mfma_gang_bands(A.n, A.M, cus);
+    if (bands == 0) return hipErrorInvalidValue;
+    const bool spare = (nb + bands - 1) / bands > kGangRegTiles * kGangWaves;
+    const size_t lds = kGangWaves * (kGangRec * sizeof(uint4) + (spare ? 2 * kMfmaGroup / 16 * 64 * 16 : 0));
+    return launch_with_lds(sb_mfma_gang<JP>, dim3(std::min(cus, R * bands)), dim3(64 * kGangWaves), lds, st, A,
+                           k0, k1, P.koff, P.kcol, P.kA, A.h, A.rowscale, x, y, S0, S1, bands, R * bands, ctl);
+}
+
+}  // namespace
+
+hipError_t launch_mfma_gang(int jprec, const StreamArgs &A, const MfmaArgs &P, int k0, int k1, float *x,
+                            float *y, uint8_t *Sin, uint8_t *Sout, int cus, int *ctl, hipStream_t st) {
+    const int bands = mfma_gang_bands(A.n, A.M, cus);
+    if (bands == 0) return hipErrorInvalidValue;
+    // (work counter and flags; the verdict of earlier runs of the solve stays)
+    hipError_t e = launch_zero_ints(ctl, k0 == 0 ? 2 : 1, st);
+    if (e == hipSuccess)
+        e = launch_zero_ints(ctl + kGangHead, gang_words(bands) * mfma_groups(A.M), st);
+    if (e != hipSuccess) return e;
+    switch (jprec) {
+        case kJFp8: return launch_gang_form<kJFp8>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
+        case kJBf16x2: return launch_gang_form<kJBf16x2>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
+        case kJFp32: return launch_gang_form<kJFp32>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
+        case kJFp8Blk: return launch_gang_form<kJFp8Blk>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
+        case kJBf16: return launch_gang_form<kJBf16>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
+        case kJFp16: return launch_gang_form<kJFp16>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_mfma_gang_verdict(int M, const int *ctl, double *energy, hipStream_t st) {
+    mfma_gang_verdict<<<(M + 255) / 256, 256, 0, st>>>(M, ctl, energy);
+    return hipGetLastError();
 }
 
 }  // namespace sbt

@@ -54,6 +54,11 @@ bool quad_step(sbt_mode mode, int32_t M) { return mode != SBT_DSB && M % 4 == 0 
 // them; the batch functions do).
 constexpr int32_t kCUs = 256;
 constexpr size_t kMfmaAutoPairs = size_t(1) << 23;
+
+// Matrix-core steps between two checkpoints are one launch from this many on:
+// it reads and writes the state once (70 us at 8484 x 1024) and saves half of
+// a step or more.
+constexpr int32_t kGangSteps = 4;
 bool mfma_auto(sbt_mode mode, int32_t prec, int32_t n, int32_t M) {
     return mode == SBT_DSB && static_cast<size_t>(n) * static_cast<size_t>(M) >= kMfmaAutoPairs;
 }
@@ -170,6 +175,24 @@ int check_shape(int32_t n, int64_t nnz, int32_t M, const char *who) {
     if (static_cast<int64_t>(n) * M > (int64_t(1) << 31) - 1)
         return fail(SBT_EINVAL, "%s: n * agents exceeds 2^31 - 1", who);
     return SBT_OK;
+}
+
+// Compute units that a stream's kernels may use (a stream can be made with a
+// mask of them).
+int stream_cus(hipStream_t st) {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(st, 32, mask) == hipSuccess) {
+        int allowed = 0;
+        for (uint32_t m : mask) allowed += __builtin_popcount(m);
+        if (allowed > 0) cus = std::min(cus, allowed);
+    } else {
+        (void)hipGetLastError();
+    }
+    return cus;
 }
 
 int device_lds_limit() {
@@ -402,6 +425,7 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
     SBT_HIP(sbt::launch_prep(n, q->a, q->row_ptr, q->col, q->b, dJ, dh, prep, scal, c0_fixed, st));
     SBT_HIP(sbt::launch_schedule(K, p->a0, sched, st));
     const bool in_rows = kernel == SBT_KERNEL_RESIDENT && rows.slots > 0;
+    bool gang_run = false;
     if (!in_rows) SBT_HIP(sbt::launch_init(n, M, p->seed, static_cast<uint32_t>(p->event), xa, dy, st));
 
     const float dt = static_cast<float>(p->dt);
@@ -549,9 +573,20 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
             SBT_HIP(sbt::launch_mfma_state(n, M, true, dy, yt, st));
         } else if (mode == SBT_DSB)
             SBT_HIP(sbt::launch_sign_planes(n, M, xa, S0, st));
+        // the matrix-core steps between two checkpoints in one launch, with
+        // the state on the chip, where it fits
+        const int run = p->energy_every > 0 ? std::min(K, p->energy_every) : K;
+        const int cus = mfma ? stream_cus(st) : 0;
+        const bool gang = mfma && run >= kGangSteps && sbt::mfma_gang_bands(n, M, cus) > 0;
         int ck = 0;
         for (int k = 0; k < K; ++k) {
-            if (tiled)
+            if (gang) {
+                const int k1 = std::min(K, k + run);
+                SBT_HIP(sbt::launch_mfma_gang(jprec, A, P, k, k1, xt, yt, reinterpret_cast<uint8_t *>(Sin),
+                                              reinterpret_cast<uint8_t *>(Sout), cus, prow, st));
+                if ((k1 - k) % 2 == 0) std::swap(Sin, Sout);  // (swapped back below)
+                k = k1 - 1;
+            } else if (tiled)
                 SBT_HIP(sbt::launch_stream_tile(static_cast<int>(mode), jprec, A, T, k, xin, xout, st));
             else if (mfma)
                 SBT_HIP(sbt::launch_stream_mfma(jprec, A, P, k, xt, yt, reinterpret_cast<const uint8_t *>(Sin),
@@ -573,11 +608,13 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
             SBT_HIP(sbt::launch_mfma_state(n, M, false, xt, xin, st));
             SBT_HIP(sbt::launch_mfma_state(n, M, false, yt, dy, st));
         }
+        gang_run = gang;
         xfinal = xin;
     }
     if (out->step_end) SBT_HIP(hipEventRecord(static_cast<hipEvent_t>(out->step_end), st));
     SBT_HIP(sbt::launch_energy(n, M, q->a, q->row_ptr, q->col, q->b, xfinal, epart,
                                out->agent_energy, st));
+    if (gang_run) SBT_HIP(sbt::launch_mfma_gang_verdict(M, prow, out->agent_energy, st));
     SBT_HIP(sbt::launch_select_best(n, M, out->agent_energy, xfinal, out->best_energy,
                                     out->best_agent, out->T, st));
     if (out->trace) SBT_HIP(sbt::launch_trace_reduce(L.n_ckpt, M, etrace, out->trace, st));
