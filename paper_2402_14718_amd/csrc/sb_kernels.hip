@@ -42,11 +42,13 @@ bool lds_attribute_needed(const void *fn, size_t lds) {
 // ------------------------------------------------------------ Ising prep
 
 // J = -b/4 in FP32, h_i = -(a_i/2 + 1/4 sum_j b_ij), and per-block partial
-// sums {sum J, sum J^2, sum_{j>i} b, sum a} in FP64.  A thread sums a row,
-// in order; the block's couplings come through LDS in tiles, since a thread
-// that reads its row from memory touches a line per coupling and lane
-// (208710 rows: 0.60 -> 0.33 ms).
-constexpr int kPrepTile = 2048;
+// sums {sum J, sum J^2, sum_{j>i} b, sum a} in FP64.  A lane sums a row, in
+// order; the rows' couplings come through LDS, kPrepCols columns of the
+// wave's 64 rows at a time, so that 16 lanes read a run of memory.  Lanes
+// that read their own rows touch a line each and coupling (208710 rows:
+// 0.60 -> @P1@ ms; runs of the workgroup's couplings instead of columns leave
+// most lanes without a row in the run, 0.33).
+constexpr int kPrepCols = 16;
 __global__ __launch_bounds__(256) void prep_ising_rows(int n, const double *__restrict__ a,
                                                        const int *__restrict__ row_ptr,
                                                        const int *__restrict__ col,
@@ -55,38 +57,48 @@ __global__ __launch_bounds__(256) void prep_ising_rows(int n, const double *__re
                                                        float *__restrict__ h,
                                                        double *__restrict__ part) {
     __shared__ double red[4];
-    __shared__ double tb[kPrepTile];
-    __shared__ int tc[kPrepTile];
-    const int i0 = blockIdx.x * 256, i = i0 + threadIdx.x;
-    const int p0 = i < n ? row_ptr[i] : 0, p1 = i < n ? row_ptr[i + 1] : 0;
-    const int q1 = row_ptr[min(n, i0 + 256)];
+    __shared__ double tb[4][64][kPrepCols + 1];
+    __shared__ int8_t upper[4][64][kPrepCols + 4];
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, sub = lane / kPrepCols, e = lane % kPrepCols;
+    const int p0 = i < n ? row_ptr[i] : 0, len = i < n ? row_ptr[i + 1] - p0 : 0;
+    const int longest = wave_max_int(len);
     double sj = 0.0, sj2 = 0.0, sup = 0.0, sa = 0.0, rs = 0.0;
-    for (int q = row_ptr[i0]; q < q1; q += kPrepTile) {
-        double bv[kPrepTile / 256];
-        int cv[kPrepTile / 256];
+    for (int q = 0; q < longest; q += kPrepCols) {
+        double bv[kPrepCols];
+        int cv[kPrepCols], at[kPrepCols];
 #pragma unroll
-        for (int u = 0; u < kPrepTile / 256; ++u) {
-            const int p = min(q + u * 256 + static_cast<int>(threadIdx.x), q1 - 1);
-            bv[u] = b[p];
-            cv[u] = col[p];
+        for (int s = 0; s < kPrepCols; ++s) {
+            const int row = s * (64 / kPrepCols) + sub;
+            const int first = __shfl(p0, row, 64), size = __shfl(len, row, 64);
+            at[s] = q + e < size ? first + q + e : -1;
+            bv[s] = 0.0;
+            cv[s] = -1;
+            if (at[s] >= 0) {
+                bv[s] = b[at[s]];
+                cv[s] = col[at[s]];
+            }
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();  // the sums of the columns before are taken
 #pragma unroll
-        for (int u = 0; u < kPrepTile / 256; ++u) {
-            const int k = u * 256 + threadIdx.x;
-            tb[k] = bv[u];
-            tc[k] = cv[u];
-            if (q + k < q1) J[q + k] = static_cast<float>(-0.25 * bv[u]);
+        for (int s = 0; s < kPrepCols; ++s) {
+            const int row = s * (64 / kPrepCols) + sub;
+            tb[wave][row][e] = bv[s];
+            upper[wave][row][e] = cv[s] > (i - lane) + row;
+            if (at[s] >= 0) J[at[s]] = static_cast<float>(-0.25 * bv[s]);
         }
-        __syncthreads();
-        const int e1 = min(p1, q + kPrepTile);
-        for (int p = max(p0, q); p < e1; ++p) {
-            const double v = tb[p - q], jv = -0.25 * v;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // (past the row's end: zeros)
+#pragma unroll
+        for (int u = 0; u < kPrepCols; ++u) {
+            const double v = tb[wave][lane][u], jv = -0.25 * v;
             rs += v;
             sj += jv;
             sj2 += jv * jv;
-            if (tc[p - q] > i) sup += v;
+            sup += upper[wave][lane][u] ? v : 0.0;
         }
-        __syncthreads();
     }
     if (i < n) {
         h[i] = static_cast<float>(-(0.5 * a[i] + 0.25 * rs));

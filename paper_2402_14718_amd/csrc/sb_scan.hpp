@@ -53,9 +53,9 @@ __device__ __forceinline__ void scan_lengths(int n, int range, Len len, int *off
     const int t = threadIdx.x;
     const int lo = min(n, static_cast<int>(blockIdx.x) * range), hi = min(n, lo + range);
     int v = 0, base;
-    for (int i = t; i < lo; i += 8 * kScanThreads) {
+    for (int i = t; i < lo; i += 16 * kScanThreads) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v += i + u * kScanThreads < lo ? len(i + u * kScanThreads) : 0;
+        for (int u = 0; u < 16; ++u) v += i + u * kScanThreads < lo ? len(i + u * kScanThreads) : 0;
     }
     (void)scan_threads(v, wsum, base);
     for (int i0 = lo; i0 < hi; i0 += kScanTile) {

@@ -64,10 +64,11 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void mfma_count(int n, int nb, const int *__restrict__ prow,
+__global__ __launch_bounds__(kWalkThreads) void mfma_count(int n, int nb, const int *__restrict__ prow,
                                                   const int *__restrict__ pcol, int *__restrict__ cnt) {
-    const int i = blockIdx.x * 256 + threadIdx.x, b = i / kBR;
-    const int d = union_size<kBR>(RowWalk(n, prow, pcol, i));
+    __shared__ int words[kWalkWords];
+    const int i = blockIdx.x * kWalkThreads + threadIdx.x, b = i / kBR;
+    const int d = union_size<kBR>(RowWalk(n, prow, pcol, i, words));
     if (i % kBR == 0 && b < nb) cnt[b] = (d + kBK - 1) / kBK;
 }
 
@@ -100,11 +101,12 @@ __device__ __forceinline__ void bf16_triple(float v, uint32_t (&t)[3]) {
 // last listed one.  A lane is a row of the block: it assembles its words over
 // 8 consecutive listed columns and stores them whole, next to the 15 others'.
 template <int JP>
-__global__ __launch_bounds__(256) void mfma_fill(int nb, StreamArgs A, const int *__restrict__ koff,
+__global__ __launch_bounds__(kWalkThreads) void mfma_fill(int nb, StreamArgs A, const int *__restrict__ koff,
                                                  int *__restrict__ kcol, uint64_t *__restrict__ kA) {
     constexpr int W = mfma_words(JP);
-    const int i = blockIdx.x * 256 + threadIdx.x, b = i / kBR, r = i % kBR;
-    RowWalk walk(A.n, A.row_ptr, A.col, i);
+    __shared__ int words[kWalkWords];
+    const int i = blockIdx.x * kWalkThreads + threadIdx.x, b = i / kBR, r = i % kBR;
+    RowWalk walk(A.n, A.row_ptr, A.col, i, words);
     const int ks0 = b < nb ? koff[b] : 0, u1 = b < nb ? (koff[b + 1] - ks0) * kBK : 0;
     int last = 0;
     for (int u = 0; __any(u < u1); u += 8) {
@@ -178,26 +180,39 @@ __device__ __forceinline__ bool mfma_block(int ngb, int nab, int &gb, int &ab) {
     return true;
 }
 
-// Sign records from the current positions (layout of mfma_sign_bytes).
-__global__ __launch_bounds__(256) void mfma_signs(int n, int M, const float *__restrict__ x,
-                                                  uint8_t *__restrict__ S) {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;  // (row, group, c)
-    const int R = mfma_groups(M);
-    if (idx >= static_cast<int64_t>(n) * R * 16) return;
-    const int i = static_cast<int>(idx / (R * 16));
-    const int grp = static_cast<int>(idx / 16 % R), c = static_cast<int>(idx % 16);
-    uint32_t byte = 0;
+// The start state (init_state's draws) in the step's tiles, and its sign
+// records; a wave per tile.
+__global__ __launch_bounds__(256) void mfma_init(int n, int M, uint32_t k0, uint32_t k1, uint32_t event,
+                                                 float *__restrict__ x, float *__restrict__ y,
+                                                 uint8_t *__restrict__ S) {
+    const int R = mfma_groups(M), nb = (n + kBR - 1) / kBR;
+    const int64_t id = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (id >= static_cast<int64_t>(nb) * R) return;
+    const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+    const int b = static_cast<int>(id / R), ab = static_cast<int>(id % R), i = b * kBR + c;
+    const size_t tile = static_cast<size_t>(id) * (kBR * kMfmaGroup) + 4 * lane;
+    uint32_t word = 0;  // byte r, bit t: agent 16 t + 4 g + r
+    for (int t = 0; t < kMfmaGroup / 16; ++t) {
+        f32x4 xv = {0.0f, 0.0f, 0.0f, 0.0f}, yv = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        const int m = kMfmaGroup * grp + 16 * t + c;
-        if (m < M && x[static_cast<size_t>(i) * M + m] >= 0.0f) byte |= 1u << t;
+        for (int r = 0; r < 4; ++r) {
+            const int m = kMfmaGroup * ab + 16 * t + 4 * g + r;
+            if (i < n && m < M) {
+                const Philox4 d = philox4x32_10(static_cast<uint32_t>(i), static_cast<uint32_t>(m), event, 0u, k0, k1);
+                xv[r] = philox_word_to_unit(d.v[0]);
+                yv[r] = philox_word_to_unit(d.v[1]);
+                word |= xv[r] >= 0.0f ? 1u << (8 * r + t) : 0u;
+            }
+        }
+        *reinterpret_cast<f32x4 *>(x + tile + 256 * t) = xv;
+        *reinterpret_cast<f32x4 *>(y + tile + 256 * t) = yv;
     }
-    S[idx] = static_cast<uint8_t>(byte);
+    if (i < n) reinterpret_cast<uint32_t *>(S)[(static_cast<size_t>(i) * R + ab) * 4 + g] = word;
 }
 
-// Spin-major x[i M + m] <-> the step's tiles (layout of mfma_state_floats);
-// one thread per 16-byte run of a tile.
-__global__ __launch_bounds__(256) void mfma_state(int n, int M, bool to_tiles, const float *__restrict__ src,
+// The step's tiles (layout of mfma_state_floats) -> spin-major x[i M + m]; one
+// thread per 16-byte run of a tile.
+__global__ __launch_bounds__(256) void mfma_state(int n, int M, const float *__restrict__ src,
                                                   float *__restrict__ dst) {
     const int R = mfma_groups(M);
     const int64_t q = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
@@ -207,18 +222,11 @@ __global__ __launch_bounds__(256) void mfma_state(int n, int M, bool to_tiles, c
     const int b = static_cast<int>(tile / R), ab = static_cast<int>(tile % R);
     const int i = b * kBR + (lane & 15), m = kMfmaGroup * ab + 16 * t + 4 * (lane >> 4);
     const size_t row = static_cast<size_t>(i) * M;
-    if (to_tiles) {
-        f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (i >= n) return;
+    const f32x4 v = *reinterpret_cast<const f32x4 *>(src + 4 * q);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (i < n && m + r < M) v[r] = src[row + m + r];
-        *reinterpret_cast<f32x4 *>(dst + 4 * q) = v;
-    } else if (i < n) {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(src + 4 * q);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (m + r < M) dst[row + m + r] = v[r];
-    }
+    for (int r = 0; r < 4; ++r)
+        if (m + r < M) dst[row + m + r] = v[r];
 }
 
 // One K-step of a tile: acc[t] += (-sgn of 8 columns, agents of tile t) x
@@ -727,31 +735,33 @@ size_t mfma_ksteps_bound(int n, int64_t nnz) {
 
 hipError_t launch_mfma_plan(int jprec, const StreamArgs &A, const MfmaArgs &P, hipStream_t st) {
     const int nb = (A.n + kBR - 1) / kBR;
-    const unsigned gr = static_cast<unsigned>((nb * static_cast<int64_t>(kBR) + 255) / 256);
-    mfma_count<<<gr, 256, 0, st>>>(A.n, nb, A.row_ptr, A.col, P.kcnt);
+    const unsigned gr = static_cast<unsigned>((nb * static_cast<int64_t>(kBR) + kWalkThreads - 1) / kWalkThreads);
+    mfma_count<<<gr, kWalkThreads, 0, st>>>(A.n, nb, A.row_ptr, A.col, P.kcnt);
     mfma_scan<<<scan_grid(nb), kScanThreads, 0, st>>>(nb, scan_range(nb), P.kcnt, P.koff);
     switch (jprec) {
-        case kJFp8: mfma_fill<kJFp8><<<gr, 256, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
-        case kJBf16x2: mfma_fill<kJBf16x2><<<gr, 256, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
-        case kJFp32: mfma_fill<kJFp32><<<gr, 256, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
-        case kJFp8Blk: mfma_fill<kJFp8Blk><<<gr, 256, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
-        case kJBf16: mfma_fill<kJBf16><<<gr, 256, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
-        case kJFp16: mfma_fill<kJFp16><<<gr, 256, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
+        case kJFp8: mfma_fill<kJFp8><<<gr, kWalkThreads, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
+        case kJBf16x2: mfma_fill<kJBf16x2><<<gr, kWalkThreads, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
+        case kJFp32: mfma_fill<kJFp32><<<gr, kWalkThreads, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
+        case kJFp8Blk: mfma_fill<kJFp8Blk><<<gr, kWalkThreads, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
+        case kJBf16: mfma_fill<kJBf16><<<gr, kWalkThreads, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
+        case kJFp16: mfma_fill<kJFp16><<<gr, kWalkThreads, 0, st>>>(nb, A, P.koff, P.kcol, P.kA); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_mfma_state(int n, int M, bool to_tiles, const float *src, float *dst, hipStream_t st) {
-    const int64_t runs = static_cast<int64_t>(mfma_state_floats(n, M) / 4);
-    if (runs > 0)
-        mfma_state<<<static_cast<unsigned>((runs + 255) / 256), 256, 0, st>>>(n, M, to_tiles, src, dst);
+hipError_t launch_mfma_init(int n, int M, uint64_t seed, uint32_t event, float *x, float *y, uint8_t *S,
+                            hipStream_t st) {
+    const int64_t tiles = static_cast<int64_t>((n + kBR - 1) / kBR) * mfma_groups(M);
+    mfma_init<<<static_cast<unsigned>((tiles + 3) / 4), 256, 0, st>>>(
+        n, M, static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), event, x, y, S);
     return hipGetLastError();
 }
 
-hipError_t launch_mfma_signs(int n, int M, const float *x, uint8_t *S, hipStream_t st) {
-    const int64_t total = static_cast<int64_t>(n) * mfma_groups(M) * 16;
-    if (total > 0) mfma_signs<<<static_cast<unsigned>((total + 255) / 256), 256, 0, st>>>(n, M, x, S);
+hipError_t launch_mfma_state(int n, int M, const float *src, float *dst, hipStream_t st) {
+    const int64_t runs = static_cast<int64_t>(mfma_state_floats(n, M) / 4);
+    if (runs > 0)
+        mfma_state<<<static_cast<unsigned>((runs + 255) / 256), 256, 0, st>>>(n, M, src, dst);
     return hipGetLastError();
 }
 

@@ -64,7 +64,6 @@ __host__ __device__ constexpr int mfma_groups(int M) { return (M + kMfmaGroup - 
 __host__ __device__ constexpr size_t mfma_sign_bytes(int n, int M) {
     return static_cast<size_t>(n) * mfma_groups(M) * 16;
 }
-hipError_t launch_mfma_signs(int n, int M, const float *x, uint8_t *S, hipStream_t st);
 
 // The step's own layout of x and y: each (block of kMfmaRows rows, group of
 // kMfmaGroup agents) is one contiguous tile of 2048 floats, in the order the
@@ -72,14 +71,17 @@ hipError_t launch_mfma_signs(int n, int M, const float *x, uint8_t *S, hipStream
 // + r) at (b R + a) 2048 + 256 t + 4 (16 g + c) + r, R = mfma_groups(M) --
 // so every 16-byte access of a wave falls in one 1 KB run.  Rows are padded
 // to whole blocks and agents to whole groups (the padding is zero and never
-// read back).  Converted from and to the spin-major layout (x[i M + m]) of
-// the other kernels at the start, at energy checkpoints and at the end.
+// read back).  Drawn in this layout (launch_mfma_init) and converted to the
+// spin-major layout (x[i M + m]) of the other kernels at energy checkpoints and
+// at the end.
 __host__ __device__ constexpr size_t mfma_state_floats(int n, int M) {
     return static_cast<size_t>((n + kMfmaRows - 1) / kMfmaRows) * mfma_groups(M) * kMfmaRows * kMfmaGroup;
 }
-// to_tiles: spin-major src -> tiled dst (padding zeroed); else tiled src ->
-// spin-major dst.
-hipError_t launch_mfma_state(int n, int M, bool to_tiles, const float *src, float *dst, hipStream_t st);
+// The start state and its sign records.
+hipError_t launch_mfma_init(int n, int M, uint64_t seed, uint32_t event, float *x, float *y, uint8_t *S,
+                            hipStream_t st);
+// Tiled src -> spin-major dst.
+hipError_t launch_mfma_state(int n, int M, const float *src, float *dst, hipStream_t st);
 
 // Upper bound on the K-steps of all blocks: a block lists at most its own
 // couplings, padded by fewer than kMfmaK.

@@ -45,10 +45,11 @@ __device__ __forceinline__ float stored_coupling(const StreamArgs &A, int p, int
         return A.J[p];
 }
 
-__global__ __launch_bounds__(256) void quad_count(int n, int nq, const int *__restrict__ prow,
+__global__ __launch_bounds__(kWalkThreads) void quad_count(int n, int nq, const int *__restrict__ prow,
                                                   const int *__restrict__ pcol, int *__restrict__ cnt) {
-    const int i = blockIdx.x * 256 + threadIdx.x, q = i / kR;
-    const int d = union_size<kR>(RowWalk(n, prow, pcol, i));
+    __shared__ int words[kWalkWords];
+    const int i = blockIdx.x * kWalkThreads + threadIdx.x, q = i / kR;
+    const int d = union_size<kR>(RowWalk(n, prow, pcol, i, words));
     if (i % kR == 0 && q < nq) cnt[q] = (d + kChunk - 1) / kChunk * kChunk;
 }
 
@@ -60,10 +61,11 @@ __global__ __launch_bounds__(kScanThreads) void quad_scan(int nq, int range, con
 // Lists a quad's columns, eight at a time (the padding to whole chunks: a
 // listed column, no coupling).
 template <int JP>
-__global__ __launch_bounds__(256) void quad_fill(int nq, StreamArgs A, const int *__restrict__ qoff,
+__global__ __launch_bounds__(kWalkThreads) void quad_fill(int nq, StreamArgs A, const int *__restrict__ qoff,
                                                  int *__restrict__ qcol, float *__restrict__ qJ) {
-    const int i = blockIdx.x * 256 + threadIdx.x, q = i / kR, r = i % kR;
-    RowWalk w(A.n, A.row_ptr, A.col, i);
+    __shared__ int words[kWalkWords];
+    const int i = blockIdx.x * kWalkThreads + threadIdx.x, q = i / kR, r = i % kR;
+    RowWalk w(A.n, A.row_ptr, A.col, i, words);
     int u = q < nq ? qoff[q] : 0;
     const int u1 = q < nq ? qoff[q + 1] : 0;
     int last = 0;
@@ -186,14 +188,14 @@ size_t quad_cols_bound(int n, int64_t nnz) {
 
 hipError_t launch_quad_plan(int jprec, const StreamArgs &A, const QuadArgs &Q, hipStream_t st) {
     const int nq = (A.n + kR - 1) / kR;
-    const unsigned g = static_cast<unsigned>((nq * static_cast<int64_t>(kR) + 255) / 256);
-    quad_count<<<g, 256, 0, st>>>(A.n, nq, A.row_ptr, A.col, Q.qcnt);
+    const unsigned g = static_cast<unsigned>((nq * static_cast<int64_t>(kR) + kWalkThreads - 1) / kWalkThreads);
+    quad_count<<<g, kWalkThreads, 0, st>>>(A.n, nq, A.row_ptr, A.col, Q.qcnt);
     quad_scan<<<scan_grid(nq), kScanThreads, 0, st>>>(nq, scan_range(nq), Q.qcnt, Q.qoff);
     switch (jprec) {
-        case kJFp8: quad_fill<kJFp8><<<g, 256, 0, st>>>(nq, A, Q.qoff, Q.qcol, Q.qJ); break;
-        case kJFp8Blk: quad_fill<kJFp8Blk><<<g, 256, 0, st>>>(nq, A, Q.qoff, Q.qcol, Q.qJ); break;
-        case kJBf16x2: quad_fill<kJBf16x2><<<g, 256, 0, st>>>(nq, A, Q.qoff, Q.qcol, Q.qJ); break;
-        case kJFp32: quad_fill<kJFp32><<<g, 256, 0, st>>>(nq, A, Q.qoff, Q.qcol, Q.qJ); break;
+        case kJFp8: quad_fill<kJFp8><<<g, kWalkThreads, 0, st>>>(nq, A, Q.qoff, Q.qcol, Q.qJ); break;
+        case kJFp8Blk: quad_fill<kJFp8Blk><<<g, kWalkThreads, 0, st>>>(nq, A, Q.qoff, Q.qcol, Q.qJ); break;
+        case kJBf16x2: quad_fill<kJBf16x2><<<g, kWalkThreads, 0, st>>>(nq, A, Q.qoff, Q.qcol, Q.qJ); break;
+        case kJFp32: quad_fill<kJFp32><<<g, kWalkThreads, 0, st>>>(nq, A, Q.qoff, Q.qcol, Q.qJ); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

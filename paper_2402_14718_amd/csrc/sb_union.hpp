@@ -3,9 +3,11 @@
 //
 // The walk is a chain (smallest next column, advance the rows that hold it),
 // so it is bound by latency and wants many groups in flight: with a lane per
-// row and the next entry of every row loaded a step ahead, 208710 rows make
-// 3261 waves.  One thread per group, 204 waves in blocks of 16 rows, took
-// 5.2 ms at 208710 rows for the matrix-core lists and 2.6 ms for the quads.
+// row, 208710 rows make 3261 waves, and the rows of a wave (consecutive, so
+// one run of memory) come through LDS, where they fit.  The matrix-core lists
+// of 208710 rows of 55 couplings took 5.2 ms with a thread per block, 0.82
+// with a lane per row and the entries from memory, and take @U1@; the quads'
+// 2.6, 0.53 and @U2@.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -36,28 +38,52 @@ __device__ __forceinline__ int group_min(int v) {
     return v;
 }
 
-// A row (padded CSR; its own column marks the padding) in column order.
-struct RowWalk {
-    const int *col;
-    int pos, end, head, next;  // head: column at pos, next: the one after it
+// Columns of a wave's rows in LDS, at most kWalkWords of them: the 64 rows of
+// a workgroup of one wave.
+constexpr int kWalkThreads = 64;
+constexpr int kWalkWords = 5120;
 
-    __device__ __forceinline__ RowWalk(int n, const int *prow, const int *pcol, int i) : col(pcol) {
+// A row (padded CSR; its own column marks the padding) in column order, read
+// from LDS where the wave's rows fit there.
+struct RowWalk {
+    const int *col, *lds;
+    int pos, end, head, next, base;  // head: column at pos; next: the one after it; base: the wave's first entry
+    bool staged;
+
+    // every lane of the wave; i: this lane's row, consecutive over the wave
+    __device__ __forceinline__ RowWalk(int n, const int *prow, const int *pcol, int i, int *words)
+        : col(pcol), lds(words) {
+        const int i0 = __builtin_amdgcn_readfirstlane(i);
+        base = prow[min(i0, n)];
+        const int size = prow[min(i0 + 64, n)] - base;
+        staged = size <= kWalkWords;
+        if (staged)
+            for (int p = threadIdx.x; p < size; p += 4 * kWalkThreads) {
+                int v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = pcol[base + min(p + u * kWalkThreads, size - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (p + u * kWalkThreads < size) words[p + u * kWalkThreads] = v[u];
+            }
+        __syncthreads();
         pos = i < n ? prow[i] : 0;
         end = i < n ? prow[i + 1] : 0;
-        while (pos < end && pcol[end - 1] == i) --end;  // drop the padding
-        head = pos < end ? pcol[pos] : kNoColumn;
-        next = pos + 1 < end ? pcol[pos + 1] : kNoColumn;
+        while (pos < end && at(end - 1) == i) --end;  // drop the padding
+        head = pos < end ? at(pos) : kNoColumn;
+        next = pos + 1 < end ? at(pos + 1) : kNoColumn;
     }
+    __device__ __forceinline__ int at(int p) const { return staged ? lds[p - base] : col[p]; }
     // The row's entry for column c, the smallest head of the group, or -1.
     __device__ __forceinline__ int take(int c) {
         const bool mine = head == c && c != kNoColumn;
-        const int at = mine ? pos : -1;
+        const int entry = mine ? pos : -1;
         if (mine) {
             ++pos;
             head = next;
-            next = pos + 1 < end ? col[pos + 1] : kNoColumn;
+            next = pos + 1 < end ? at(pos + 1) : kNoColumn;
         }
-        return at;
+        return entry;
     }
 };
 
