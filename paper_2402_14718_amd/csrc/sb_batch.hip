@@ -84,6 +84,7 @@ __global__ __launch_bounds__(256) void batch_prep(BatchArgs B, int jprec) {
     const BatchEvent E = B.ev[e];
     const int t = threadIdx.x;
     double sj = 0.0, sj2 = 0.0, sup = 0.0, sa = 0.0;
+    int other = 0;  // a BF16 coupling that is no normal FP16 value
     for (int i = t; i < E.n; i += 256) {
         const int r0 = B.row_ptr[E.rp_off + i], r1 = B.row_ptr[E.rp_off + i + 1];
         double rs = 0.0;
@@ -96,6 +97,9 @@ __global__ __launch_bounds__(256) void batch_prep(BatchArgs B, int jprec) {
             } else {  // BF16: FP32 first, then round to nearest even on the upper half
                 const uint32_t u = __float_as_uint(static_cast<float>(jv));
                 bits = static_cast<uint16_t>((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+                const float f = __uint_as_float(static_cast<uint32_t>(bits) << 16);
+                const bool normal = f == 0.0f || (__builtin_fabsf(f) >= 0x1p-14f && __builtin_fabsf(f) < 65536.0f);
+                other |= normal && __half2float(__float2half_rn(f)) == f ? 0 : 1;
             }
             B.J16[E.nz_off + p] = bits;
             rs += bv;
@@ -106,11 +110,13 @@ __global__ __launch_bounds__(256) void batch_prep(BatchArgs B, int jprec) {
         B.h[E.row_off + i] = static_cast<float>(-(0.5 * B.a[E.row_off + i] + 0.25 * rs));
         sa += B.a[E.row_off + i];
     }
+    other = __syncthreads_or(other);
     const double t0 = block_sum(sj, red);
     const double t1 = block_sum(sj2, red);
     const double t2 = block_sum(sup, red);
     const double t3 = block_sum(sa, red);
     if (t == 0) {
+        B.halves[e] = other == 0;
         const double n2 = static_cast<double>(E.n) * E.n;
         const double mean = t0 / n2;
         const double var = t1 / n2 - mean * mean;

@@ -56,7 +56,8 @@ constexpr int kBatchTailCap = 8192;                 // default LDS words for cou
 // coupling formats: 16-bit (batch), FP32, FP8 e4m3 with a per-row scale,
 // FP8 e4m3 with a per-block scale (blocks of 8 padded couplings of a row),
 // BF16 hi + lo pairs (streaming kernels, sb_stream_kernels.hpp)
-enum : int { kJFp16 = 0, kJBf16 = 1, kJFp32 = 2, kJFp8 = 3, kJFp8Blk = 4, kJBf16x2 = 5 };
+enum : int { kJFp16 = 0, kJBf16 = 1, kJFp32 = 2, kJFp8 = 3, kJFp8Blk = 4, kJBf16x2 = 5,
+              kJBf16Half = 6 };  // BF16 couplings of an event where all are FP16 values too
 
 struct BatchEvent {
     int n, nnz;
@@ -98,6 +99,7 @@ struct BatchArgs {
     void *trash;                 // 64 bytes that absorb stores of lanes without work
     int *counter;                // this launch's work queue counter
     double *etrace;              // [E * n_ckpt * M]
+    int *halves;                 // [E] BF16 couplings: all of the event are FP16 values
     double *energy;              // [E * M] final O(T)
     double *epart;               // [E * n_chunks * M] its parts by kEnergyChunk rows
     int n_chunks;                // of the largest event without gangs

@@ -1,6 +1,6 @@
 // The resident single-event kernel (gfx950): all steps of one event in one
 // launch, FP32 couplings, a workgroup per one or two agents.  The solve is
-// rows_solve (sb_rows_step.hpp), the step loop of the batched kernel.
+// rows_item (sb_rows_step.hpp), the step loop of the batched kernel.
 //
 // Paper section "Simulated Bifurcation" (bSB Eq. 5-8, dSB Eq. 9-12, aSB
 // Eq. 1-4).  Built once per mode (SBT_RESIDENT_MODE), in parallel.
@@ -15,7 +15,7 @@ namespace sbt {
 template <int MODE, int TPB, int S, int W>
 __global__ __launch_bounds__(TPB) void sb_resident_rows(BatchArgs B) {
     extern __shared__ __align__(16) unsigned char smem[];
-    rows_solve<MODE, kJFp32, TPB, S, W, true>(B, smem);
+    rows_item<MODE, kJFp32, TPB, S, W, true>(B, smem, 0);
 }
 
 namespace {
@@ -45,9 +45,13 @@ hipError_t launch_threads(const BatchArgs &B, const RowsShape &R, hipStream_t st
     if (R.slots == kBatchSPT && R.agents == 1) return launch_shape<MODE, TPB, kBatchSPT, 1>(B, st);
     if constexpr (TPB > 64)
         if (R.slots == 2 && R.agents == 2) return launch_shape<MODE, TPB, 2, 2>(B, st);
-    if constexpr (TPB == 1024)
+    if constexpr (TPB == 1024) {
         if (R.slots == 4)
             return R.agents == 2 ? launch_shape<MODE, TPB, 4, 2>(B, st) : launch_shape<MODE, TPB, 4, 1>(B, st);
+        if (R.slots == kBatchSPT && R.agents == 2) return launch_shape<MODE, TPB, kBatchSPT, 2>(B, st);
+        if (R.slots == 6)
+            return R.agents == 2 ? launch_shape<MODE, TPB, 6, 2>(B, st) : launch_shape<MODE, TPB, 6, 1>(B, st);
+    }
     return hipErrorInvalidValue;
 }
 

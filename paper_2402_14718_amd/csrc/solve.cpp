@@ -205,10 +205,16 @@ int device_lds_limit() {
 
 // Shape of the resident kernel that holds rows in registers (slots = 0: it
 // does not fit): two spins per thread on the smallest workgroup that holds
-// them, then four and nine on the largest; a hinted size wherever it holds
-// the event.  Two agents per workgroup once one per CU does not hold them
-// all (two or four spins per thread, where the registers allow it).
-sbt::RowsShape rows_shape(int32_t n, int32_t M, int tpb_hint) {
+// them, then four, six and nine on the largest (5458 spins x 250, dSB: 1.35 us
+// a step with nine slots, 1.16 with six); a hinted size wherever it holds the
+// event.  Two agents per workgroup once one per CU does not hold them all: a
+// coupling is then read and held once for both (us per step, one against two:
+// 5458 x 600 bSB 3.73 / 2.76, dSB 3.82 / 2.66; 8484 x 1024 bSB 6.9 / 5.3, x 900
+// dSB 8.6 / 4.2).  Nine slots of two agents hold fewer couplings, so past 3.5
+// per spin one agent is the better again (random rows, bSB: 3 per spin 7.1 /
+// 4.8, 3.5 9.8 / 16.1 -- track events, of longer first rows and shorter last
+// ones, have 3.4 at the largest size).
+sbt::RowsShape rows_shape(int32_t n, int64_t nnz, int32_t M, int tpb_hint) {
     sbt::RowsShape R{0, 0, 0};
     if (n > sbt::kBatchSPT * 1024) return R;
     if (tpb_hint != 0 && n <= sbt::kBatchSPT * tpb_hint) {
@@ -216,17 +222,18 @@ sbt::RowsShape rows_shape(int32_t n, int32_t M, int tpb_hint) {
         R.slots = n <= 2 * tpb_hint ? 2 : sbt::kBatchSPT;
     } else {
         R.threads = n <= 128 ? 64 : (n <= 512 ? 256 : (n <= 1024 ? 512 : 1024));
-        R.slots = n <= 2048 ? 2 : (n <= 4096 ? 4 : sbt::kBatchSPT);
+        R.slots = n <= 2048 ? 2 : (n <= 4096 ? 4 : (n <= 6144 ? 6 : sbt::kBatchSPT));
     }
-    R.agents = R.slots <= 4 && R.threads > 64 && M > kCUs ? 2 : 1;
+    const bool two = R.slots <= 6 || (R.threads == 1024 && 2 * nnz <= 7 * int64_t(n));
+    R.agents = two && R.threads > 64 && M > kCUs ? 2 : 1;
     return R;
 }
 
-// LDS words that the tails of an event can take (two per coupling), at most
-// what the step loop's buffers leave of 160 KB in any mode.
-int rows_tail_words(int64_t nnz, const sbt::RowsShape &R) {
-    const int64_t left = (163840 - 1024 - 12 * int64_t(R.slots) * R.threads * R.agents) / 4;
-    return static_cast<int>(std::min(2 * nnz, left));
+// LDS words that the step loop's buffers leave for tails in any mode.
+int64_t rows_tail_words(const sbt::RowsShape &R) {
+    const int64_t words = int64_t(R.slots) * R.threads;
+    const int64_t used = R.slots < sbt::kBatchSPT ? 8 * words * R.agents : (R.agents == 1 ? 12 : 16) * words;
+    return (163840 - 1024 - 16 * int64_t(R.threads) - used) / 4;
 }
 
 // Whether AUTO takes the resident step loop: while a row's couplings stay in
@@ -238,12 +245,12 @@ int rows_tail_words(int64_t nnz, const sbt::RowsShape &R) {
 // 31 against 5; 8000 of 8 25 against 13 / 102 against 41).  Only n and the
 // number of couplings are known here: either all couplings fit the tail
 // list, or there are few enough per spin for the registers of a shape (33
-// to 43 couplings per 4 to 9 slots, longest rows first).  The LDS-row kernel
+// to 43 couplings for 4 to 9 spins, longest rows first).  The LDS-row kernel
 // loses to the streaming step at every size past these shapes.
 bool rows_fit(int32_t n, int64_t nnz, const sbt::RowsShape &R) {
     if (R.slots == 0) return false;
-    const int per_spin = R.slots == 2 ? 16 : (R.slots == 4 ? 8 : 4);
-    return rows_tail_words(nnz, R) == 2 * nnz || nnz <= per_spin * int64_t(n);
+    const int per_spin = R.slots == 2 ? 16 : (R.slots == 4 ? 8 : (R.slots == 6 ? 5 : 4));
+    return 2 * nnz <= rows_tail_words(R) || nnz <= per_spin * int64_t(n);
 }
 
 // Shape of the LDS-row resident kernel, or tpb = 0 if it does not fit.
@@ -271,7 +278,7 @@ sbt::ResidentShape resident_shape(int32_t n, int64_t nnz, int lds_limit) {
 
 int pick_kernel(int32_t n, int64_t nnz, sbt_mode mode, const sbt_solve_params &p, int lds_limit,
                 sbt::RowsShape *rows, sbt::ResidentShape *shape) {
-    const sbt::RowsShape R = rows_shape(n, p.agents, p.tpb);
+    const sbt::RowsShape R = rows_shape(n, nnz, p.agents, p.tpb);
     const sbt::ResidentShape S = resident_shape(n, nnz, lds_limit);
     if (rows) *rows = R;
     if (shape) *shape = S;
@@ -476,7 +483,7 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
         xfinal = out->x_final ? out->x_final : xa;
         B.x_out = xfinal;
         B.y_out = out->y_final;
-        B.tail_cap = rows_tail_words(nnz, rows);
+        B.tail_cap = static_cast<int>(std::min<int64_t>(2 * nnz, 163840 / 4));  // (two words per coupling)
         B.one.n = n;
         B.one.nnz = nnz;
         B.one.event_id = p->event;

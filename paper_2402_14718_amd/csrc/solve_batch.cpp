@@ -197,7 +197,7 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
 }
 
 struct BatchLayout {
-    size_t ev, item_e, item_a, item_lg, J16, colr, h, c0, offset, perm, rank, sched, counter, trash, etrace, energy, epart, T;
+    size_t ev, item_e, item_a, item_lg, J16, colr, h, c0, offset, perm, rank, sched, counter, trash, etrace, energy, epart, halves, T;
     size_t gangs, gitem_g, gitem_b, xg, gints, gpart, gclock, done;
     size_t total;
     int n_ckpt;
@@ -228,6 +228,7 @@ BatchLayout make_layout(const Schedule &S, const sbt_solve_params &p) {
     L.counter = take(2 * sizeof(int32_t));  // one per launch
     L.trash = take(64);
     L.etrace = take(sizeof(double) * E * static_cast<size_t>(L.n_ckpt) * M);
+    L.halves = take(sizeof(int) * E);
     L.energy = take(sizeof(double) * E * M);
     L.epart = take(sizeof(double) * E * static_cast<size_t>(S.n_chunks) * M);
     L.T = take(static_cast<size_t>(S.sum_n) * M);
@@ -421,6 +422,7 @@ extern "C" int sbt_batch_run_tuned(const sbt_dev_batch *batch, sbt_mode mode, sb
     B.etrace = reinterpret_cast<double *>(ws + L.etrace);
     B.energy = out->agent_energy ? out->agent_energy : reinterpret_cast<double *>(ws + L.energy);
     B.epart = reinterpret_cast<double *>(ws + L.epart);
+    B.halves = reinterpret_cast<int *>(ws + L.halves);
     B.n_chunks = S.n_chunks;
     B.trace = out->trace;
     B.best_energy = out->best_energy;

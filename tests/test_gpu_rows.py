@@ -45,7 +45,8 @@ def _qubo(n, hubs, seed):
 SHAPES = [(1, 3, []), (20, 32, []), (64, 1, [1, 2, 3]), (65, 100, [4, 5]), (128, 33, [8, 9]),
           (129, 257, [12, 13]), (512, 300, [16, 17, 3]), (513, 31, [2]), (1024, 257, [5, 4, 16]),
           (1025, 258, [14, 9, 5]), (2048, 3, [15, 15, 15]), (2049, 257, [18, 6]), (4096, 10, [48, 7]),
-          (4097, 9, [12] * 40), (9216, 5, [70, 25] + [9] * 30)]
+          (4097, 9, [12] * 40), (4097, 257, [12] * 40), (6144, 300, [22, 9]), (6145, 259, [30, 13, 7]),
+          (8484, 300, [24, 12] + [7] * 90), (9216, 5, [70, 25] + [9] * 30), (9216, 257, [50] * 3)]
 
 
 @pytest.mark.parametrize("mode", ["bsb", "dsb", "asb"])
