@@ -53,8 +53,11 @@ namespace {
 
 // Couplings held per slot, by slot: slot 0 holds the longest rows.  On the
 // 1000-particle event (n = 8484, 9 slots of 1024) the longest rows by slot
-// are 19-26, 6-7, 4, 3, 2, 2, 2, 2, 1.  FEW: nine slots with FP32 couplings of
-// two agents, or for dSB, whose state leaves room for fewer.
+// are 19-26, 6-7, 4, 3, 2, 2, 2, 2, 1.  FEW: nine slots, whose state leaves
+// room for fewer (all but FP32 bSB of one agent).  With the larger set the
+// step spilled: two agents, FP32, 8484 spins x 1024, bSB 8.4 against 5.3 us a
+// step; batch of 96 events of 20-400 particles, bSB, FP16, 6.19 against
+// 5.95 ms; 128 of 20-1000, dSB, FP16, 31.8 against 31.2.
 template <bool FEW>
 struct Held {
     static constexpr int kCaps[2][kBatchSPT] = {{16, 8, 5, 4, 3, 2, 2, 2, 1}, {12, 6, 4, 3, 2, 2, 2, 2, 1}};
@@ -219,7 +222,7 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
     // first buffer has one, else the position
     constexpr bool kBytesHeld = L::kBuf <= 65536;
     constexpr uint32_t kScale = kBytesHeld ? kB : 1;
-    using H = Held<kWide && S == kBatchSPT && (W == 2 || MODE == kDSB)>;
+    using H = Held<S == kBatchSPT && (!kWide || W == 2 || MODE == kDSB)>;
     constexpr int kHeld = H::before(S);
     // FP32 couplings: their addresses two to a register, or one, where the
     // registers allow it (an instruction less per coupling; with the finer
