@@ -18,7 +18,7 @@ if not torch.cuda.is_available():
 import paper_2402_14718_amd as sbt  # noqa: E402
 
 
-def _qubo(n, hubs, seed):
+def _qubo(n, hubs, seed, scale=1.0):
     """A path of n spins (rows of one or two couplings) and, per entry of
     `hubs`, one spin coupled to about that many others; couplings and biases
     are multiples of 1/8 up to 2, exact in every form."""
@@ -38,8 +38,8 @@ def _qubo(n, hubs, seed):
     b = sp.csr_matrix(sp.triu(b + b.T, 1))
     b = sp.csr_matrix(b + b.T)
     b.sort_indices()
-    return sbt.Qubo(n, rng.integers(-8, 9, n) / 8.0, b.indptr.astype(np.int64),
-                    b.indices.astype(np.int32), b.data.copy(), np.zeros((n, 3), np.int64))
+    return sbt.Qubo(n, scale * (rng.integers(-8, 9, n) / 8.0), b.indptr.astype(np.int64),
+                    b.indices.astype(np.int32), scale * b.data, np.zeros((n, 3), np.int64))
 
 
 SHAPES = [(1, 3, []), (20, 32, []), (64, 1, [1, 2, 3]), (65, 100, [4, 5]), (128, 33, [8, 9]),
@@ -105,3 +105,37 @@ def test_auto_takes_the_loop_while_couplings_fit_and_equals_the_row_step(n, per_
     assert got["kernel"] == kernel, q.nnz / n
     for k in ("x", "y", "T", "agent_energy", "best_agent"):
         assert np.array_equal(got[k], ref[k]), k
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -18, 2.0 ** 20])
+@pytest.mark.parametrize("mode", ["bsb", "dsb"])
+def test_batch_bf16_couplings_that_are_no_fp16_values(mode, scale):
+    # BF16 values below or above the range of FP16, beside an event within it
+    qs = [_qubo(300, [20], 1, scale), _qubo(300, [20], 1), _qubo(5000, [18, 6], 2, scale)]
+    M, kw = 24, dict(steps=64, dt=0.5, seed=5)
+    for k, q in enumerate(qs):
+        c0 = 0.15 / (1.0 if k == 1 else scale)
+        s = sbt.DeviceBatchSolver(qs, mode, "bf16", sbt.solve_params(agents=M, c0=c0, **kw),
+                                  want_agent_energy=True, want_agent_state=True)
+        s.run()
+        got = s.result()["agent_x"][k]
+        ref = sbt.solve(q, mode, kernel="stream_rows", agents=M, event=k, c0=c0, want_state=True, **kw)
+        assert np.array_equal(got, ref["x"])
+
+
+@pytest.mark.parametrize("kernel,mode,steps", [("stream", "bsb", 20), ("stream", "bsb", 21), ("stream", "dsb", 20),
+                                               ("stream_mfma", "dsb", 20), ("resident", "bsb", 20)])
+def test_final_state_in_arrays_aligned_to_four_bytes(kernel, mode, steps):
+    q = _qubo(513, [9], 3)
+    s = sbt.DeviceSolver(q, mode, sbt.solve_params(agents=72, steps=steps, kernel=kernel, seed=2), want_state=True)
+    s.run()
+    torch.cuda.synchronize()
+    x, y = s.x.clone(), s.y.clone()
+    n = x.numel()
+    bx, by = torch.zeros(n + 2, device="cuda"), torch.zeros(n + 2, device="cuda")
+    s._dr.x_final, s._dr.y_final = bx.data_ptr() + 4, by.data_ptr() + 4
+    s.run()
+    torch.cuda.synchronize()
+    for base, want in ((bx, x), (by, y)):
+        assert torch.equal(base[1:n + 1], want.reshape(-1))
+        assert base[0] == 0 and base[n + 1] == 0
