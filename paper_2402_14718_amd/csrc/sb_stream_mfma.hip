@@ -490,13 +490,15 @@ __global__ __launch_bounds__(256) void sb_stream_mfma(StreamArgs A, int k, const
 // would cost it the operands in the L2), only that a workgroup's stores are
 // done before it arrives.  Gangs are queued one after the other and taken
 // band by band by running workgroups, so a gang that has been started gets
-// all its bands as long as `bands` workgroups fit the device beside what else
-// runs there (an eighth of it for M = 1024).  Waits are
+// all its bands as long as `bands` workgroups of this launch run at once.  A
+// gang takes an eighth of the device at most, so of up to eight such launches
+// side by side (streams, processes) one always has that many; with a gang over
+// the whole device two could each hold what the other waits for.  Waits are
 // bounded: past kGangWait ticks of the 100 MHz clock the run is given up
 // and ctl[1] set (the solve's energies are then NaN).
 //
 // A step of 8484 x 1024: FP32 24.3 -> 10.2 us, FP8 23.6 -> 8.1; 1480 x 256
-// 5.2 -> 4.6, 4.9 -> 4.8.  What is left is the meeting (2.3 us), the latency
+// 5.2 -> 4.0, 4.9 -> 3.4.  What is left is the meeting (2.3 us), the latency
 // of the records (1.7) and the update of 16 or 17 tiles per CU.  Two
 // workgroups of four waves per CU, of different gangs, do not hide one
 // another's meeting (13.5 us): a gang of 64 meets more slowly.
@@ -811,7 +813,7 @@ hipError_t launch_stream_mfma(int jprec, const StreamArgs &A, const MfmaArgs &P,
 
 int mfma_gang_bands(int n, int M, int cus) {
     const int nb = (n + kBR - 1) / kBR, R = mfma_groups(M);
-    const int bands = std::min(cus / std::min(R, 8), nb);
+    const int bands = std::min(cus / 8, nb);
     if (bands < 1 || n < kGangHead + gang_words(bands) * R) return 0;
     return (nb + bands - 1) / bands <= kGangTiles * kGangWaves ? bands : 0;
 }

@@ -96,7 +96,8 @@ hipError_t launch_stream_mfma(int jprec, const StreamArgs &A, const MfmaArgs &P,
 // Steps k0 .. k1 - 1 with the state on the chip (one launch): x, y in and out
 // as above, the signs of step k0 in Sin, those after step k1 - 1 in Sin or
 // Sout as after k1 - k0 single steps.  A gang (one group of kMfmaGroup
-// agents) runs on mfma_gang_bands workgroups, 0 where the state does not
+// agents) runs on mfma_gang_bands workgroups (at most an eighth of the
+// device), 0 where the state does not
 // fit: a workgroup takes up to kGangTiles tiles in each of its waves.  ctl: n
 // ints that nothing else uses until the verdict.
 constexpr int kGangWaves = 8;

@@ -39,3 +39,19 @@ def test_run_on_the_chip_equals_single_steps(n, M, degree, precision):
         got = sbt.solve(q, "dsb", energy_every=every, want_trace=every > 0, **kw)
         for k in ("x", "y", "T", "agent_energy", "best_agent"):
             assert np.array_equal(got[k], ref[k]), (every, k)
+
+
+def test_runs_on_several_streams_at_once():
+    q = _qubo(8493, 3, 4)
+    kw = dict(agents=300, steps=40, kernel="stream_mfma")
+    want = [sbt.solve(q, "dsb", seed=s, want_state=True, **kw) for s in range(4)]
+    solvers = [sbt.DeviceSolver(q, "dsb", sbt.solve_params(seed=s, **kw), want_state=True) for s in range(4)]
+    streams = [torch.cuda.Stream() for _ in solvers]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for s, st in zip(solvers, streams):
+            s.run(st)
+    torch.cuda.synchronize()
+    for s, w in zip(solvers, want):
+        assert np.array_equal(s.x.cpu().numpy(), w["x"])
+        assert np.array_equal(s.agent_energy.cpu().numpy(), w["agent_energy"])
