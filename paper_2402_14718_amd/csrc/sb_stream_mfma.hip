@@ -637,7 +637,14 @@ __global__ __launch_bounds__(64 * kGangWaves, 2) void sb_mfma_gang(
 #pragma unroll
                 for (int w = 0; w < W; ++w) an[w] = kA[(static_cast<size_t>(ks) * 64 + lane) * W + w];
             };
-            if (nk[0] > 0) load_operand(ks0[0]);
+            // the first operand of the next tile with couplings (a block may have none)
+            auto load_next_tile = [&](int i) {
+                int ks = -1;
+#pragma unroll
+                for (int u = kTiles - 1; u > i; --u) ks = nk[u] > 0 ? ks0[u] : ks;
+                if (ks >= 0) load_operand(ks);
+            };
+            load_next_tile(-1);
 #pragma unroll
             for (int i = 0; i < kTiles; ++i) {
                 if (!has[i]) continue;
@@ -673,8 +680,8 @@ __global__ __launch_bounds__(64 * kGangWaves, 2) void sb_mfma_gang(
                         for (int w = 0; w < W; ++w) a8[w] = an[w];
                         if (ks + 1 < ks0[i] + nk[i])
                             load_operand(ks + 1);
-                        else if (i + 1 < kTiles && nk[i + 1 < kTiles ? i + 1 : i] > 0)
-                            load_operand(ks0[i + 1 < kTiles ? i + 1 : i]);
+                        else
+                            load_next_tile(i);
                         mfma_kstep<JP>(s8, a8, acc);
                     }
                 }
