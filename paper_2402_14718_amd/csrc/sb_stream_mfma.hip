@@ -180,17 +180,13 @@ __device__ __forceinline__ bool mfma_block(int ngb, int nab, int &gb, int &ab) {
     return true;
 }
 
-// The start state (init_state's draws) in the step's tiles, and its sign
-// records; a wave per tile.
-__global__ __launch_bounds__(256) void mfma_init(int n, int M, uint32_t k0, uint32_t k1, uint32_t event,
-                                                 float *__restrict__ x, float *__restrict__ y,
-                                                 uint8_t *__restrict__ S) {
-    const int R = mfma_groups(M), nb = (n + kBR - 1) / kBR;
-    const int64_t id = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (id >= static_cast<int64_t>(nb) * R) return;
-    const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
-    const int b = static_cast<int>(id / R), ab = static_cast<int>(id % R), i = b * kBR + c;
-    const size_t tile = static_cast<size_t>(id) * (kBR * kMfmaGroup) + 4 * lane;
+// The start state (init_state's draws) of one tile, by a wave; put(at, word)
+// takes its sign words.
+template <class Put>
+__device__ __forceinline__ void mfma_draw(int n, int M, uint32_t k0, uint32_t k1, uint32_t event, int b, int ab, int R,
+                                          int lane, float *x, float *y, Put put) {
+    const int g = lane >> 4, c = lane & 15, i = b * kBR + c;
+    const size_t tile = (static_cast<size_t>(b) * R + ab) * (kBR * kMfmaGroup) + 4 * lane;
     uint32_t word = 0;  // byte r, bit t: agent 16 t + 4 g + r
     for (int t = 0; t < kMfmaGroup / 16; ++t) {
         f32x4 xv = {0.0f, 0.0f, 0.0f, 0.0f}, yv = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -207,29 +203,39 @@ __global__ __launch_bounds__(256) void mfma_init(int n, int M, uint32_t k0, uint
         *reinterpret_cast<f32x4 *>(x + tile + 256 * t) = xv;
         *reinterpret_cast<f32x4 *>(y + tile + 256 * t) = yv;
     }
-    if (i < n) reinterpret_cast<uint32_t *>(S)[(static_cast<size_t>(i) * R + ab) * 4 + g] = word;
+    if (i < n) put((static_cast<size_t>(i) * R + ab) * 4 + g, word);
 }
 
-// The step's tiles (layout of mfma_state_floats) -> spin-major x[i M + m]; a
-// workgroup per tile.  A tile's runs of 16 bytes go round the rows, so they
-// pass through LDS and a row is written as one run of 512 bytes (208710 x 512,
+// The start state in the step's tiles and its sign records; a wave per tile.
+__global__ __launch_bounds__(256) void mfma_init(int n, int M, uint32_t k0, uint32_t k1, uint32_t event,
+                                                 float *__restrict__ x, float *__restrict__ y,
+                                                 uint8_t *__restrict__ S) {
+    const int R = mfma_groups(M), nb = (n + kBR - 1) / kBR;
+    const int64_t id = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (id >= static_cast<int64_t>(nb) * R) return;
+    mfma_draw(n, M, k0, k1, event, static_cast<int>(id / R), static_cast<int>(id % R), R, threadIdx.x & 63, x, y,
+              [&](size_t at, uint32_t word) { reinterpret_cast<uint32_t *>(S)[at] = word; });
+}
+
+// A tile (layout of mfma_state_floats) -> spin-major x[i M + m], by a
+// workgroup.  The tile's runs of 16 bytes go round the rows, so they pass
+// through LDS and a row is written as one run of 512 bytes (208710 x 512,
 // 0.33 -> 0.16 ms against a thread per run).
-__global__ __launch_bounds__(256) void mfma_state(int n, int M, const float *__restrict__ src,
-                                                  float *__restrict__ dst) {
-    constexpr int kRuns = kMfmaGroup / 4;  // of a row
-    __shared__ f32x4 rows[kBR][kRuns + 1];
-    const int R = mfma_groups(M);
-    const int b = blockIdx.x / R, ab = blockIdx.x % R;
-    const f32x4 *tile = reinterpret_cast<const f32x4 *>(src) + static_cast<size_t>(blockIdx.x) * (kBR * kRuns);
+constexpr int kStateThreads = 256;
+constexpr int kRuns = kMfmaGroup / 4;  // of a row
+typedef f32x4 StateRows[kBR][kRuns + 1];
+__device__ __forceinline__ void tile_state(int n, int M, int b, int ab, const float *src, float *dst, StateRows &rows) {
+    const size_t at = static_cast<size_t>(b) * mfma_groups(M) + ab;
+    const f32x4 *tile = reinterpret_cast<const f32x4 *>(src) + at * (kBR * kRuns);
 #pragma unroll
-    for (int u = 0; u < kBR * kRuns / 256; ++u) {
-        const int q = u * 256 + threadIdx.x, lane = q % 64;
+    for (int u = 0; u < kBR * kRuns / kStateThreads; ++u) {
+        const int q = u * kStateThreads + threadIdx.x, lane = q % 64;
         rows[lane & 15][4 * (q / 64) + (lane >> 4)] = tile[q];
     }
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < kBR * kRuns / 256; ++u) {
-        const int q = u * 256 + threadIdx.x, c = q / kRuns, i = b * kBR + c;
+    for (int u = 0; u < kBR * kRuns / kStateThreads; ++u) {
+        const int q = u * kStateThreads + threadIdx.x, c = q / kRuns, i = b * kBR + c;
         const int m = kMfmaGroup * ab + 4 * (q % kRuns);
         if (i >= n) continue;
         const f32x4 v = rows[c][q % kRuns];
@@ -237,6 +243,13 @@ __global__ __launch_bounds__(256) void mfma_state(int n, int M, const float *__r
         for (int r = 0; r < 4; ++r)
             if (m + r < M) dst[static_cast<size_t>(i) * M + m + r] = v[r];
     }
+}
+
+__global__ __launch_bounds__(kStateThreads) void mfma_state(int n, int M, const float *__restrict__ src,
+                                                            float *__restrict__ dst) {
+    __shared__ StateRows rows;
+    const int R = mfma_groups(M);
+    tile_state(n, M, blockIdx.x / R, blockIdx.x % R, src, dst, rows);
 }
 
 // One K-step of a tile: acc[t] += (-sgn of 8 columns, agents of tile t) x
@@ -493,17 +506,20 @@ __global__ __launch_bounds__(256) void sb_stream_mfma(StreamArgs A, int k, const
 // all its bands as long as `bands` workgroups of this launch run at once.  A
 // gang takes an eighth of the device at most, so of up to eight such launches
 // side by side (streams, processes) one always has that many; with a gang over
-// the whole device two could each hold what the other waits for.  Waits are
-// bounded: past kGangWait ticks of the 100 MHz clock the run is given up
-// and ctl[1] set (the solve's energies are then NaN).
+// the whole device two could each hold what the other waits for.  Where fewer
+// compute units are left than that (a long launch beside this one, a captured
+// solve replayed on a stream with a mask), a wait ends after kGangWait ticks of
+// the 100 MHz clock: ctl[1] is set, the launch ends, later runs of the solve do
+// nothing, and alone_steps takes the steps that are missing.
 //
 // A step of 8484 x 1024: FP32 24.3 -> 10.2 us, FP8 23.6 -> 8.1; 1480 x 256
 // 5.2 -> 4.0, 4.9 -> 3.4.  What is left is the meeting (2.3 us), the latency
 // of the records (1.7) and the update of 16 or 17 tiles per CU.  Two
 // workgroups of four waves per CU, of different gangs, do not hide one
 // another's meeting (13.5 us): a gang of 64 meets more slowly.
-constexpr long long kGangWait = 1000000000LL;
-constexpr int kGangHead = 32;  // control words before the gangs' flags: work counter, verdict
+constexpr long long kGangWait = 100000000LL;  // 1 s, where a step takes microseconds
+// control words before the gangs' flags: work counter, 1 + k0 of the run that was given up (0: none)
+constexpr int kGangHead = 32;
 // flags of a gang, in cache lines of their own
 __host__ __device__ constexpr int gang_words(int bands) { return (bands + 31) / 32 * 32; }
 constexpr int kGangSlots = kChunkSteps * kBK;
@@ -513,7 +529,8 @@ constexpr int kGangRec = kGangSlots + kGangSlots / 8;  // records of a chunk, pa
 // own and waits until all have done as many: 32 additions to one counter
 // took longer (8 gangs of 32 workgroups: 2.65 against 2.35 us,
 // and 8.6 with the counters in one cache line).
-__device__ __forceinline__ bool gang_meet(int *flags, int bands, int band, int done, int *fault, int *stop) {
+__device__ __forceinline__ bool gang_meet(int *flags, int bands, int band, int done, int *fault, int given_up,
+                                          int *stop) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's records are out
     __syncthreads();
     if (threadIdx.x < 64) {
@@ -527,7 +544,7 @@ __device__ __forceinline__ bool gang_meet(int *flags, int bands, int band, int d
                 if (tries % 64 == 0) {
                     bad = __hip_atomic_load(fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
                     if (!bad && wall_clock64() - t0 > kGangWait) {
-                        __hip_atomic_store(fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_store(fault, given_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         bad = true;
                     }
                     if (__any(bad)) break;
@@ -540,6 +557,15 @@ __device__ __forceinline__ bool gang_meet(int *flags, int bands, int band, int d
     }
     __syncthreads();
     return *stop != 0;
+}
+
+// The sign record of a column, as other workgroups wrote it.
+__device__ __forceinline__ uint4 load_record(const uint8_t *S, int col, int R, int ab) {
+    const uint64_t *p = reinterpret_cast<const uint64_t *>(S + (static_cast<size_t>(col) * R + ab) * 16);
+    const uint64_t a = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t b = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return uint4{static_cast<uint32_t>(a), static_cast<uint32_t>(a >> 32), static_cast<uint32_t>(b),
+                 static_cast<uint32_t>(b >> 32)};
 }
 
 // (w << 1) | (x >= 0): the comparison's carry added in.
@@ -563,8 +589,12 @@ __global__ __launch_bounds__(64 * kGangWaves, 2) void sb_mfma_gang(
     f32x4 *spare = reinterpret_cast<f32x4 *>(smem + kGangWaves * kGangRec * 16) + wave * 2 * T * 64 + lane;
     const int M = A.M, R = mfma_groups(M), nb = (A.n + kBR - 1) / kBR;
     const float c0 = static_cast<float>(A.scal[0]);
-    for (;;) {
-        if (threadIdx.x == 0) item_s = atomicAdd(ctl, 1);
+    for (bool first = true;; first = false) {
+        if (threadIdx.x == 0) {  // (nothing where a run was given up before)
+            const int given_up = first ? __hip_atomic_load(ctl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+            const int next = atomicAdd(ctl, 1);
+            item_s = given_up ? items : next;
+        }
         __syncthreads();
         const int item = __builtin_amdgcn_readfirstlane(item_s);
         __syncthreads();
@@ -618,13 +648,7 @@ __global__ __launch_bounds__(64 * kGangWaves, 2) void sb_mfma_gang(
             const uint8_t *Sin = ((k - k0) & 1) ? S1 : S0;
             uint8_t *Sout = ((k - k0) & 1) ? S0 : S1;
             const float gk = A.sched[k];
-            auto load_rec = [&](int col) -> uint4 {
-                const uint64_t *p = reinterpret_cast<const uint64_t *>(Sin + (static_cast<size_t>(col) * R + ab) * 16);
-                const uint64_t a = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint64_t b = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return uint4{static_cast<uint32_t>(a), static_cast<uint32_t>(a >> 32), static_cast<uint32_t>(b),
-                             static_cast<uint32_t>(b >> 32)};
-            };
+            auto load_rec = [&](int col) { return load_record(Sin, col, R, ab); };
             uint4 rn[kTiles][2];
 #pragma unroll
             for (int i = 0; i < kTiles; ++i)
@@ -718,7 +742,7 @@ __global__ __launch_bounds__(64 * kGangWaves, 2) void sb_mfma_gang(
                     __hip_atomic_store(reinterpret_cast<uint32_t *>(Sout) + (static_cast<size_t>(row) * R + ab) * 4 + g,
                                        word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (k + 1 < k1) stop = gang_meet(flags, bands, band, k + 1 - k0, ctl + 1, &stop_s);
+            if (k + 1 < k1) stop = gang_meet(flags, bands, band, k + 1 - k0, ctl + 1, k0 + 1, &stop_s);
         }
 #pragma unroll
         for (int i = 0; i < kTiles; ++i) {
@@ -737,14 +761,130 @@ __global__ __launch_bounds__(64 * kGangWaves, 2) void sb_mfma_gang(
                 *reinterpret_cast<f32x4 *>(y + tile_of(i) + 256 * t) = yv;
             }
         }
+        if (stop) return;
+        if (threadIdx.x == 0) __hip_atomic_store(flags + band, k1 - k0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
     }
 }
 
-// Energies of a run that was given up are NaN.
-__global__ void mfma_gang_verdict(int M, const int *__restrict__ ctl, double *__restrict__ energy) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m < M && ctl[1] != 0) energy[m] = NAN;
+// One group's steps that a given-up run of sb_mfma_gang leaves, by one
+// workgroup that waits for nobody, its blocks in turn.  Bands of a gang stop at
+// different steps, so a gang of which a band did not finish is taken again from
+// the start draw; the runs after it go on from the state.  Arithmetic and order
+// are sb_mfma_gang's.
+template <int JP, int WAVES>
+__device__ __forceinline__ void alone_steps(const StreamArgs &A, const MfmaArgs &P, const GangRun &G, float *x, float *y,
+                                         int ab, int bands, uint4 (&rec_lds)[WAVES][kGangRec], int &short_s) {
+    constexpr int T = kMfmaGroup / 16, W = mfma_words(JP);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int g = lane >> 4, c = lane & 15, k0 = G.k0, k1 = G.k1;
+    const int M = A.M, R = mfma_groups(M), nb = (A.n + kBR - 1) / kBR;
+    const int *__restrict__ koff = P.koff, *__restrict__ kcol = P.kcol;
+    const uint64_t *__restrict__ kA = P.kA;
+    auto signs = [&](int k) { return ((k - k0) & 1) ? G.S1 : G.S0; };  // that step k reads
+    int kb = k0;
+    if (G.ctl[1] == k0 + 1) {
+        const int *flags = G.ctl + gang_words(bands) * ab + kGangHead;
+        if (threadIdx.x == 0) short_s = 0;
+        __syncthreads();
+        for (int b = threadIdx.x; b < bands; b += 64 * WAVES)
+            if (flags[b] != k1 - k0) short_s = 1;
+        __syncthreads();
+        if (short_s == 0) return;
+        kb = 0;
+        for (int b = wave; b < nb; b += WAVES)
+            mfma_draw(A.n, M, G.seed_lo, G.seed_hi, G.event, b, ab, R, lane, x, y, [&](size_t at, uint32_t word) {
+                __hip_atomic_store(reinterpret_cast<uint32_t *>(signs(0)) + at, word, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            });
+    }
+    const float c0 = static_cast<float>(A.scal[0]);
+    uint4 *rec = rec_lds[wave];
+    for (int k = kb; k < k1; ++k) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's records are out
+        __syncthreads();
+        const uint8_t *Sin = signs(k);
+        uint8_t *Sout = signs(k + 1);
+        const float gk = A.sched[k];
+        for (int b = wave; b < nb; b += WAVES) {
+            const int ks0 = koff[b], nk = koff[b + 1] - ks0;
+            f32x4 acc[T];
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int j = 0; j * kChunkSteps < nk; ++j) {
+                uint4 rn[2];
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) {
+                    const int u = min(j * kGangSlots + lane + 64 * hh, nk * kBK - 1);
+                    rn[hh] = load_record(Sin, kcol[static_cast<size_t>(ks0) * kBK + u], R, ab);
+                }
+                __builtin_amdgcn_wave_barrier();  // the LDS reads of the chunk before come first
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) {
+                    const int sl = lane + 64 * hh;
+                    rec[sl + sl / 8] = rn[hh];
+                }
+                __builtin_amdgcn_wave_barrier();
+                for (int kk = 0; kk < min(kChunkSteps, nk - j * kChunkSteps); ++kk) {
+                    uint32_t s8[8];
+                    uint64_t a8[W];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int sl = kk * kBK + 8 * g + e;
+                        s8[e] = reinterpret_cast<const uint8_t *>(rec + sl + sl / 8)[c];
+                    }
+#pragma unroll
+                    for (int w = 0; w < W; ++w)
+                        a8[w] = kA[(static_cast<size_t>(ks0 + j * kChunkSteps + kk) * 64 + lane) * W + w];
+                    mfma_kstep<JP>(s8, a8, acc);
+                }
+            }
+            const int row = b * kBR + c, rc = min(row, A.n - 1);
+            const float hv = A.h[rc], sc = JP == kJFp8 ? A.rowscale[rc] : 1.0f;
+            const size_t tile = (static_cast<size_t>(b) * R + ab) * (kBR * kMfmaGroup) + 4 * lane;
+            uint32_t word = 0;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                f32x4 xv = *reinterpret_cast<const f32x4 *>(x + tile + 256 * t);
+                f32x4 yv = *reinterpret_cast<const f32x4 *>(y + tile + 256 * t);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float xr = xv[r], yr = yv[r];
+                    sb_update(xr, yr, __builtin_fmaf(-sc, acc[t][r], hv), c0, gk, A.dt, A.dta0);
+                    xv[r] = xr;
+                    yv[r] = yr;
+                    if (kMfmaGroup * ab + 16 * t + 4 * g + r < M && xr >= 0.0f) word |= 1u << (8 * r + t);
+                }
+                *reinterpret_cast<f32x4 *>(x + tile + 256 * t) = xv;
+                *reinterpret_cast<f32x4 *>(y + tile + 256 * t) = yv;
+            }
+            if (row < A.n)
+                __hip_atomic_store(reinterpret_cast<uint32_t *>(Sout) + (static_cast<size_t>(row) * R + ab) * 4 + g, word,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
+// mfma_state of x after a run of sb_mfma_gang.  Where the run was given up, the
+// first workgroup of each group of agents takes the missing steps and converts
+// the group's tiles: no launch more for the runs that need none of this.
+template <int JP>
+__global__ __launch_bounds__(kStateThreads) void mfma_gang_state(StreamArgs A, MfmaArgs P, GangRun G, float *x, float *y,
+                                                                 int bands, float *__restrict__ dst) {
+    constexpr int kWaves = kStateThreads / 64;
+    __shared__ StateRows rows;
+    __shared__ uint4 rec[kWaves][kGangRec];
+    __shared__ int short_s;
+    const int R = mfma_groups(A.M), b0 = blockIdx.x / R, ab = blockIdx.x % R;
+    if (G.ctl[1] == 0) {
+        tile_state(A.n, A.M, b0, ab, x, dst, rows);
+    } else if (b0 == 0) {
+        alone_steps<JP, kWaves>(A, P, G, x, y, ab, bands, rec, short_s);
+        for (int b = 0; b * kBR < A.n; ++b) {
+            __syncthreads();  // the steps' stores are done, and the rows of the block before
+            tile_state(A.n, A.M, b, ab, x, dst, rows);
+        }
+    }
 }
 
 size_t mfma_ksteps_bound(int n, int64_t nnz) {
@@ -779,7 +919,7 @@ hipError_t launch_mfma_init(int n, int M, uint64_t seed, uint32_t event, float *
 
 hipError_t launch_mfma_state(int n, int M, const float *src, float *dst, hipStream_t st) {
     const unsigned tiles = static_cast<unsigned>((n + kBR - 1) / kBR) * mfma_groups(M);
-    if (tiles > 0) mfma_state<<<tiles, 256, 0, st>>>(n, M, src, dst);
+    if (tiles > 0) mfma_state<<<tiles, kStateThreads, 0, st>>>(n, M, src, dst);
     return hipGetLastError();
 }
 
@@ -828,43 +968,58 @@ int mfma_gang_bands(int n, int M, int cus) {
 namespace {
 
 template <int JP>
-hipError_t launch_gang_form(const StreamArgs &A, const MfmaArgs &P, int k0, int k1, float *x, float *y,
-                            uint8_t *S0, uint8_t *S1, int cus, int *ctl,
+hipError_t launch_gang_form(const StreamArgs &A, const MfmaArgs &P, const GangRun &G, float *x, float *y, int cus,
                             hipStream_t st) {
     const int R = mfma_groups(A.M), nb = (A.n + kBR - 1) / kBR;
     const int bands = mfma_gang_bands(A.n, A.M, cus);
-    if (bands == 0) return hipErrorInvalidValue;
     const bool spare = (nb + bands - 1) / bands > kGangRegTiles * kGangWaves;
     const size_t lds = kGangWaves * (kGangRec * sizeof(uint4) + (spare ? 2 * kMfmaGroup / 16 * 64 * 16 : 0));
-    return launch_with_lds(sb_mfma_gang<JP>, dim3(std::min(cus, R * bands)), dim3(64 * kGangWaves), lds, st, A,
-                           k0, k1, P.koff, P.kcol, P.kA, A.h, A.rowscale, x, y, S0, S1, bands, R * bands, ctl);
+    return launch_with_lds(sb_mfma_gang<JP>, dim3(std::min(cus, R * bands)), dim3(64 * kGangWaves), lds, st, A, G.k0,
+                           G.k1, P.koff, P.kcol, P.kA, A.h, A.rowscale, x, y, G.S0, G.S1, bands, R * bands, G.ctl);
+}
+
+template <int JP>
+hipError_t launch_gang_state_form(const StreamArgs &A, const MfmaArgs &P, const GangRun &G, float *x, float *y, int cus,
+                                  float *dst, hipStream_t st) {
+    const unsigned tiles = static_cast<unsigned>((A.n + kBR - 1) / kBR) * mfma_groups(A.M);
+    mfma_gang_state<JP><<<tiles, kStateThreads, 0, st>>>(A, P, G, x, y, mfma_gang_bands(A.n, A.M, cus), dst);
+    return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_mfma_gang(int jprec, const StreamArgs &A, const MfmaArgs &P, int k0, int k1, float *x,
-                            float *y, uint8_t *Sin, uint8_t *Sout, int cus, int *ctl, hipStream_t st) {
+hipError_t launch_mfma_gang(int jprec, const StreamArgs &A, const MfmaArgs &P, const GangRun &G, float *x, float *y,
+                            int cus, hipStream_t st) {
     const int bands = mfma_gang_bands(A.n, A.M, cus);
     if (bands == 0) return hipErrorInvalidValue;
-    // (work counter and flags; the verdict of earlier runs of the solve stays)
-    hipError_t e = launch_zero_ints(ctl, k0 == 0 ? 2 : 1, st);
+    // (work counter and flags; a run given up stays noted for the solve)
+    hipError_t e = launch_zero_ints(G.ctl, G.k0 == 0 ? 2 : 1, st);
     if (e == hipSuccess)
-        e = launch_zero_ints(ctl + kGangHead, gang_words(bands) * mfma_groups(A.M), st);
+        e = launch_zero_ints(G.ctl + kGangHead, gang_words(bands) * mfma_groups(A.M), st);
     if (e != hipSuccess) return e;
     switch (jprec) {
-        case kJFp8: return launch_gang_form<kJFp8>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
-        case kJBf16x2: return launch_gang_form<kJBf16x2>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
-        case kJFp32: return launch_gang_form<kJFp32>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
-        case kJFp8Blk: return launch_gang_form<kJFp8Blk>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
-        case kJBf16: return launch_gang_form<kJBf16>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
-        case kJFp16: return launch_gang_form<kJFp16>(A, P, k0, k1, x, y, Sin, Sout, cus, ctl, st);
+        case kJFp8: return launch_gang_form<kJFp8>(A, P, G, x, y, cus, st);
+        case kJBf16x2: return launch_gang_form<kJBf16x2>(A, P, G, x, y, cus, st);
+        case kJFp32: return launch_gang_form<kJFp32>(A, P, G, x, y, cus, st);
+        case kJFp8Blk: return launch_gang_form<kJFp8Blk>(A, P, G, x, y, cus, st);
+        case kJBf16: return launch_gang_form<kJBf16>(A, P, G, x, y, cus, st);
+        case kJFp16: return launch_gang_form<kJFp16>(A, P, G, x, y, cus, st);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_mfma_gang_verdict(int M, const int *ctl, double *energy, hipStream_t st) {
-    mfma_gang_verdict<<<(M + 255) / 256, 256, 0, st>>>(M, ctl, energy);
-    return hipGetLastError();
+hipError_t launch_mfma_gang_state(int jprec, const StreamArgs &A, const MfmaArgs &P, const GangRun &G, float *x,
+                                  float *y, int cus, float *dst, hipStream_t st) {
+    if (mfma_gang_bands(A.n, A.M, cus) == 0) return hipErrorInvalidValue;
+    switch (jprec) {
+        case kJFp8: return launch_gang_state_form<kJFp8>(A, P, G, x, y, cus, dst, st);
+        case kJBf16x2: return launch_gang_state_form<kJBf16x2>(A, P, G, x, y, cus, dst, st);
+        case kJFp32: return launch_gang_state_form<kJFp32>(A, P, G, x, y, cus, dst, st);
+        case kJFp8Blk: return launch_gang_state_form<kJFp8Blk>(A, P, G, x, y, cus, dst, st);
+        case kJBf16: return launch_gang_state_form<kJBf16>(A, P, G, x, y, cus, dst, st);
+        case kJFp16: return launch_gang_state_form<kJFp16>(A, P, G, x, y, cus, dst, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace sbt

@@ -94,19 +94,27 @@ hipError_t launch_stream_mfma(int jprec, const StreamArgs &A, const MfmaArgs &P,
                               const uint8_t *Sin, uint8_t *Sout, hipStream_t st);
 
 // Steps k0 .. k1 - 1 with the state on the chip (one launch): x, y in and out
-// as above, the signs of step k0 in Sin, those after step k1 - 1 in Sin or
-// Sout as after k1 - k0 single steps.  A gang (one group of kMfmaGroup
-// agents) runs on mfma_gang_bands workgroups (at most an eighth of the
-// device), 0 where the state does not
-// fit: a workgroup takes up to kGangTiles tiles in each of its waves.  ctl: n
-// ints that nothing else uses until the verdict.
+// as above, the signs of step k0 in S0, those after step k1 - 1 in S0 or S1 as
+// after k1 - k0 single steps.  A gang (one group of kMfmaGroup agents) runs on
+// mfma_gang_bands workgroups (at most an eighth of the device), 0 where the
+// state does not fit: a workgroup takes up to kGangTiles tiles in each of its
+// waves.  launch_mfma_gang_state (x to the spin-major layout) has to follow
+// each run: it takes the steps of a run that was given up, its workgroups
+// having never run at once.
+struct GangRun {
+    int k0, k1;
+    uint8_t *S0, *S1;
+    int *ctl;                          // n ints that nothing else uses until the end of the solve
+    uint32_t seed_lo, seed_hi, event;  // the solve's start draw
+};
 constexpr int kGangWaves = 8;
 constexpr int kGangRegTiles = 2;
 constexpr int kGangTiles = 3;
 // cus: compute units that the launch's stream may use.
 int mfma_gang_bands(int n, int M, int cus);
-hipError_t launch_mfma_gang(int jprec, const StreamArgs &A, const MfmaArgs &P, int k0, int k1, float *x,
-                            float *y, uint8_t *Sin, uint8_t *Sout, int cus, int *ctl, hipStream_t st);
-hipError_t launch_mfma_gang_verdict(int M, const int *ctl, double *energy, hipStream_t st);
+hipError_t launch_mfma_gang(int jprec, const StreamArgs &A, const MfmaArgs &P, const GangRun &G, float *x, float *y,
+                            int cus, hipStream_t st);
+hipError_t launch_mfma_gang_state(int jprec, const StreamArgs &A, const MfmaArgs &P, const GangRun &G, float *x,
+                                  float *y, int cus, float *dst, hipStream_t st);
 
 }  // namespace sbt

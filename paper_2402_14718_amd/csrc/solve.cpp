@@ -56,8 +56,10 @@ constexpr int32_t kCUs = 256;
 constexpr size_t kMfmaAutoPairs = size_t(1) << 23;
 
 // Matrix-core steps between two checkpoints are one launch from this many on:
-// it reads and writes the state once (70 us at 8484 x 1024) and saves half of
-// a step or more.
+// it reads and writes the state once.  us a step with energies after every 4
+// steps, in one launch / in four: 8484 x 1024, FP32 31.7 / 39.4; 3000 x 2800
+// 38.5 / 39; 512 x 16384 36.0 / 36.6; 1480 x 256 12.3 / 11.7; after every 6,
+// 10.1 / 10.2 there and 25.5 / 35 at 8484 x 1024.
 constexpr int32_t kGangSteps = 4;
 bool mfma_auto(sbt_mode mode, int32_t prec, int32_t n, int32_t M) {
     return mode == SBT_DSB && static_cast<size_t>(n) * static_cast<size_t>(M) >= kMfmaAutoPairs;
@@ -432,7 +434,6 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
     SBT_HIP(sbt::launch_prep(n, q->a, q->row_ptr, q->col, q->b, dJ, dh, prep, scal, c0_fixed, st));
     SBT_HIP(sbt::launch_schedule(K, p->a0, sched, st));
     const bool in_rows = kernel == SBT_KERNEL_RESIDENT && rows.slots > 0;
-    bool gang_run = false;
     // the final state is made in the caller's arrays where they are aligned
     // for the kernels' 16-byte accesses (copies of both: 0.4 ms at 208710 x 512)
     auto usable = [](const void *v) { return v != nullptr && reinterpret_cast<uintptr_t>(v) % 16 == 0; };
@@ -595,14 +596,23 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
         const int run = p->energy_every > 0 ? std::min(K, p->energy_every) : K;
         const int cus = mfma ? stream_cus(st) : 0;
         const bool gang = mfma && run >= kGangSteps && sbt::mfma_gang_bands(n, M, cus) > 0;
+        sbt::GangRun G{0, 0, nullptr, nullptr, prow, static_cast<uint32_t>(p->seed & 0xffffffffu),
+                       static_cast<uint32_t>(p->seed >> 32), static_cast<uint32_t>(p->event)};
+        // (xin == xa: dSB)
+        auto mfma_positions = [&]() {
+            return gang ? sbt::launch_mfma_gang_state(jprec, A, P, G, xt, yt, cus, xin, st)
+                        : sbt::launch_mfma_state(n, M, xt, xin, st);
+        };
         int ck = 0;
         for (int k = 0; k < K; ++k) {
             if (gang) {
-                const int k1 = std::min(K, k + run);
-                SBT_HIP(sbt::launch_mfma_gang(jprec, A, P, k, k1, xt, yt, reinterpret_cast<uint8_t *>(Sin),
-                                              reinterpret_cast<uint8_t *>(Sout), cus, prow, st));
-                if ((k1 - k) % 2 == 0) std::swap(Sin, Sout);  // (swapped back below)
-                k = k1 - 1;
+                G.k0 = k;
+                G.k1 = std::min(K, k + run);
+                G.S0 = reinterpret_cast<uint8_t *>(Sin);
+                G.S1 = reinterpret_cast<uint8_t *>(Sout);
+                SBT_HIP(sbt::launch_mfma_gang(jprec, A, P, G, xt, yt, cus, st));
+                if ((G.k1 - k) % 2 == 0) std::swap(Sin, Sout);  // (swapped back below)
+                k = G.k1 - 1;
             } else if (tiled)
                 SBT_HIP(sbt::launch_stream_tile(static_cast<int>(mode), jprec, A, T, k, xin, xout, st));
             else if (mfma)
@@ -615,23 +625,21 @@ extern "C" int sbt_solve_dev(const sbt_dev_qubo *q, int32_t max_row_nnz, sbt_mod
             std::swap(xin, xout);
             std::swap(Sin, Sout);
             if (p->energy_every > 0 && (k + 1) % p->energy_every == 0) {
-                if (mfma) SBT_HIP(sbt::launch_mfma_state(n, M, xt, xin, st));  // xin == xa (dSB)
+                if (mfma) SBT_HIP(mfma_positions());
                 SBT_HIP(sbt::launch_energy(n, M, q->a, q->row_ptr, q->col, q->b, xin, epart,
                                            etrace + static_cast<size_t>(ck) * M, st));
                 ++ck;
             }
         }
         if (mfma) {
-            SBT_HIP(sbt::launch_mfma_state(n, M, xt, xin, st));
+            if (p->energy_every <= 0 || K % p->energy_every != 0) SBT_HIP(mfma_positions());
             if (out->y_final) SBT_HIP(sbt::launch_mfma_state(n, M, yt, dy, st));
         }
-        gang_run = gang;
         xfinal = xin;
     }
     if (out->step_end) SBT_HIP(hipEventRecord(static_cast<hipEvent_t>(out->step_end), st));
     SBT_HIP(sbt::launch_energy(n, M, q->a, q->row_ptr, q->col, q->b, xfinal, epart,
                                out->agent_energy, st));
-    if (gang_run) SBT_HIP(sbt::launch_mfma_gang_verdict(M, prow, out->agent_energy, st));
     SBT_HIP(sbt::launch_select_best(n, M, out->agent_energy, xfinal, out->best_energy,
                                     out->best_agent, out->T, st));
     if (out->trace) SBT_HIP(sbt::launch_trace_reduce(L.n_ckpt, M, etrace, out->trace, st));
