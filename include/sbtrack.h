@@ -468,9 +468,8 @@ typedef struct {
 /* How a batch is scheduled: which events run on which step-kernel shape
  * and how many agents a work item holds.  Scheduling only: every agent
  * performs the same step arithmetic in the same order under any tuning, so
- * positions, assignments and final energies are bit-identical; checkpoint
- * energies are summed in an order that follows the schedule and agree to
- * rounding.
+ * positions, assignments and energies are bit-identical (those of events that
+ * run as gangs of row bands: positions and assignments, energies to rounding).
  * Shapes: 1024 threads per workgroup, one workgroup per CU (any n up to
  * 9216), and 512 threads, two workgroups per CU (n up to 4608), each with 9
  * position slots per thread.  The 1024-thread items run first, then the

@@ -74,6 +74,19 @@ __device__ __forceinline__ uint16_t column_rank(const int *rank, int row, int co
     return static_cast<uint16_t>(rank[col] | (col > row ? 0x8000 : 0));
 }
 
+// The largest of the workgroup's values (each at least 0), in thread 0; red:
+// one double per wave.
+__device__ __forceinline__ double block_max(double v, double *red) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (unsigned w = 1; w < blockDim.x >> 6; ++w) v = fmax(v, red[w]);
+    __syncthreads();
+    return v;
+}
+
 // Per-event preparation, one workgroup per event: FP32 field h, 16-bit
 // couplings J = -b/4, c0 and the Ising offset C (FP64, fixed order), and
 // the spin order by decreasing row length.
@@ -83,11 +96,11 @@ __global__ __launch_bounds__(256) void batch_prep(BatchArgs B, int jprec) {
     const int e = blockIdx.x;
     const BatchEvent E = B.ev[e];
     const int t = threadIdx.x;
-    double sj = 0.0, sj2 = 0.0, sup = 0.0, sa = 0.0;
+    double sj = 0.0, sj2 = 0.0, sup = 0.0, sa = 0.0, top = 0.0;
     int other = 0;  // a BF16 coupling that is no normal FP16 value
     for (int i = t; i < E.n; i += 256) {
         const int r0 = B.row_ptr[E.rp_off + i], r1 = B.row_ptr[E.rp_off + i + 1];
-        double rs = 0.0;
+        double rs = 0.0, most = __builtin_fabs(B.a[E.row_off + i]);
         for (int p = r0; p < r1; ++p) {
             const double bv = B.b[E.nz_off + p];
             const double jv = -0.25 * bv;
@@ -103,13 +116,16 @@ __global__ __launch_bounds__(256) void batch_prep(BatchArgs B, int jprec) {
             }
             B.J16[E.nz_off + p] = bits;
             rs += bv;
+            most += __builtin_fabs(bv);
             sj += jv;
             sj2 += jv * jv;
             if (B.col[E.nz_off + p] > i) sup += bv;
         }
         B.h[E.row_off + i] = static_cast<float>(-(0.5 * B.a[E.row_off + i] + 0.25 * rs));
         sa += B.a[E.row_off + i];
+        top = most < INFINITY ? fmax(top, most) : top;
     }
+    top = block_max(top, red);
     other = __syncthreads_or(other);
     const double t0 = block_sum(sj, red);
     const double t1 = block_sum(sj2, red);
@@ -117,6 +133,9 @@ __global__ __launch_bounds__(256) void batch_prep(BatchArgs B, int jprec) {
     const double t3 = block_sum(sa, red);
     if (t == 0) {
         B.halves[e] = other == 0;
+        // at most 2^14 spins of terms below 2^at: see rows_item's agent_energy
+        const int at = top > 0.0 ? min(max(ilogb(top) + 1, -900), 1000) : 0;
+        B.split_at[e] = ldexp(1.5, at + 14);
         const double n2 = static_cast<double>(E.n) * E.n;
         const double mean = t0 / n2;
         const double var = t1 / n2 - mean * mean;
@@ -154,66 +173,6 @@ __global__ void batch_reset(int *counters, int n) {
     if (static_cast<int>(threadIdx.x) < n) counters[threadIdx.x] = 0;
 }
 
-// Final FP64 O(T) of every agent (Eq. 13), from the assignments: a workgroup
-// sums kEnergyChunk rows of one event for 64 agents, one lane each.  Its order
-// depends on nothing but the event, so agents with the same T have the same
-// energy under every schedule (the best agent is the lowest of a tie).
-// Four rows of a wave are in flight together: each is a chain of loads.
-__global__ __launch_bounds__(1024) void batch_energy(BatchArgs B) {
-    constexpr int kWaves = 16, kPer = kEnergyChunk / kWaves, R = 4;
-    __shared__ double sum[kWaves][64];
-    const int e = blockIdx.z;
-    const BatchEvent E = B.ev[e];
-    const int lo = blockIdx.x * kEnergyChunk;
-    if (E.gang || lo >= E.n) return;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int m = blockIdx.y * 64 + lane, mc = min(m, B.M - 1);
-    const int8_t *T = B.T + static_cast<size_t>(E.row_off) * B.M + mc;
-    const int *rp = B.row_ptr + E.rp_off, *col = B.col + E.nz_off;
-    const double *a = B.a + E.row_off, *b = B.b + E.nz_off;
-    double tot = 0.0;
-    for (int u = 0; u < kPer; u += R) {
-        double er[R];
-        int p[R], q[R];
-        bool on[R];
-        int most = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = lo + wave * kPer + u + r, ic = min(i, E.n - 1);
-            p[r] = rp[ic];
-            q[r] = i < E.n ? rp[ic + 1] : p[r];
-            er[r] = a[ic];
-            on[r] = i < E.n && T[static_cast<size_t>(ic) * B.M] != 0;
-            most = max(most, q[r] - p[r]);
-        }
-        for (int k = 0; k < most; ++k) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                if (k >= q[r] - p[r]) continue;  // (uniform: a row is a wave's)
-                const int i = lo + wave * kPer + u + r, c = col[p[r] + k];
-                const double bv = b[p[r] + k];
-                if (c > i && T[static_cast<size_t>(c) * B.M] != 0) er[r] += bv;
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) tot += on[r] ? er[r] : 0.0;
-    }
-    sum[wave][lane] = tot;
-    __syncthreads();
-    if (wave == 0 && m < B.M) {
-        double v = 0.0;
-        for (int w = 0; w < kWaves; ++w) v += sum[w][lane];
-        B.epart[(static_cast<size_t>(e) * B.n_chunks + blockIdx.x) * B.M + m] = v;
-    }
-}
-
-// The parts of an agent's energy, in order.
-__device__ __forceinline__ double agent_total(const BatchArgs &B, const BatchEvent &E, int e, int m) {
-    double v = 0.0;
-    for (int c = 0; c * kEnergyChunk < E.n; ++c) v += B.epart[(static_cast<size_t>(e) * B.n_chunks + c) * B.M + m];
-    return v;
-}
-
 constexpr int kSelect = 256;
 
 // Per event: best agent (minimum energy, lowest index on ties), its T,
@@ -226,7 +185,6 @@ __global__ __launch_bounds__(kSelect) void batch_select(BatchArgs B) {
     double be = INFINITY;
     int bm = 0x7fffffff;
     for (int m = t; m < B.M; m += kSelect) {
-        if (!E.gang) B.energy[static_cast<size_t>(e) * B.M + m] = agent_total(B, E, e, m);
         const double v = B.energy[static_cast<size_t>(e) * B.M + m];
         if (v < be || (v == be && m < bm)) {
             be = v;
@@ -309,12 +267,6 @@ hipError_t launch_batch_steps(int mode, int jprec, int tpb, const BatchArgs &B, 
     if (tpb == kBatchTPBSmall) return steps_of_shape<kBatchTPBSmall>(mode, jprec, B, st);
     if (tpb == kBatchTPB) return steps_of_shape<kBatchTPB>(mode, jprec, B, st);
     return hipErrorInvalidValue;
-}
-
-hipError_t launch_batch_energy(const BatchArgs &B, hipStream_t st) {
-    if (B.n_chunks > 0)
-        batch_energy<<<dim3(B.n_chunks, (B.M + 63) / 64, B.E), 1024, 0, st>>>(B);
-    return hipGetLastError();
 }
 
 hipError_t launch_batch_select(const BatchArgs &B, hipStream_t st) {

@@ -69,8 +69,6 @@ struct BatchEvent {
     int gang;                    // solved as gangs of row bands
 };
 
-constexpr int kEnergyChunk = 512;  // rows per workgroup of batch_energy
-
 struct BatchArgs {
     int E, M, K, ckpt_every, n_ckpt;
     int n_items, item_begin;     // this launch's items: [item_begin, item_begin + n_items)
@@ -100,9 +98,8 @@ struct BatchArgs {
     int *counter;                // this launch's work queue counter
     double *etrace;              // [E * n_ckpt * M]
     int *halves;                 // [E] BF16 couplings: all of the event are FP16 values
+    double *split_at;            // [E] where rows_item splits an event's energy terms (prep output)
     double *energy;              // [E * M] final O(T)
-    double *epart;               // [E * n_chunks * M] its parts by kEnergyChunk rows
-    int n_chunks;                // of the largest event without gangs
     double *trace;               // [E * n_ckpt] best so far, or null
     double *best_energy;         // [E]
     int *best_agent;             // [E]
@@ -150,8 +147,6 @@ hipError_t launch_batch_steps(int mode, int jprec, int tpb, const BatchArgs &B, 
 template <int MODE, int JP, int TPB>
 hipError_t launch_batch_steps_tu(const BatchArgs &B, hipStream_t st);
 
-// final energies of every event without gangs, from its agents' T
-hipError_t launch_batch_energy(const BatchArgs &B, hipStream_t st);
 hipError_t launch_batch_select(const BatchArgs &B, hipStream_t st);
 // the gang launch (persistent grid of `B.grid` 1024-thread workgroups) and
 // the reduction of its partial energies and stamps; n_gangs gangs

@@ -506,11 +506,21 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
     // FP64 energy of the current state per agent (Eq. 13): out[w] is
     // agent (agent0 + t * W + w)'s in threads t < G.  The sums run
     // through the buffer that this step does not read.
+    //
+    // In a batch each spin's term (its row in CSR order) is split into a
+    // multiple of 2^-38 and one of 2^-77 of the largest term, whose sums over
+    // at most 2^14 spins are exact.  So an agent's energy does not depend on
+    // which thread holds a spin: agents with equal spins have equal energies
+    // under any schedule (the best of a tie is the lowest), a checkpoint's
+    // energy is the final one of that state, and a target taken from either
+    // is reached.  What is dropped is below 2^-64 of the largest term.
+    constexpr int kParts = SINGLE ? 1 : 2;
     auto agent_energy = [&](int buf, double (&out)[W]) {
         const Place P = fresh();
         const int lane = static_cast<int>(P.even & 63u);
         double *red = L::kRedInBuf ? reinterpret_cast<double *>(smem + (buf ^ 1) * L::kBuf) : red_own;
-        double v[W] = {};
+        double v[kParts][W] = {};
+        const double at = SINGLE ? 0.0 : B.split_at[e];
         unrolled<S>([&](auto sc) {
             constexpr int s = decltype(sc)::value;
             if (s >= n_act) return;
@@ -536,25 +546,39 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
             }
             float x[W];
             state(sc, P, buf, x);
-            for (int w = 0; w < W; ++w) v[w] += (there & (x[w] >= 0.0f)) ? er[w] : 0.0;
+            for (int w = 0; w < W; ++w) {
+                const double term = (there & (x[w] >= 0.0f)) ? er[w] : 0.0;
+                if constexpr (SINGLE) {
+                    v[0][w] += term;
+                } else {
+                    const double high = (term + at) - at, rest = high == term ? 0.0 : term - high;
+                    v[0][w] += high;
+                    v[kParts - 1][w] += (rest + at * 0x1p-39) - at * 0x1p-39;
+                }
+            }
         });
-        for (int w = 0; w < W; ++w) {
-            // lanes with equal t % G hold the same agents
-            for (int off = 32; off >= G; off >>= 1) v[w] += lane_xor(v[w], lane, off);
-            red[w * T + t] = v[w];
+        double tot[W] = {};
+        for (int part = 0; part < kParts; ++part) {
+            for (int w = 0; w < W; ++w) {
+                // lanes with equal t % G hold the same agents
+                double sum = v[part][w];
+                for (int off = 32; off >= G; off >>= 1) sum += lane_xor(sum, lane, off);
+                red[w * T + t] = sum;
+            }
+            __syncthreads();
+            for (int w = 0; w < W; ++w) {
+                // group t: lane t of every wave when G <= 64; otherwise lane
+                // t % 64 of the waves whose first group is t rounded down to 64
+                double sum = 0.0;
+                if (wave_reports)
+                    for (int v2 = 0; v2 < nwaves; ++v2)
+                        if (G <= 64 || ((v2 * 64) & (G - 1)) == wave * 64)
+                            sum += red[w * T + v2 * 64 + (t & 63)];
+                tot[w] += sum;  // (of exact sums: one rounding)
+            }
+            __syncthreads();
         }
-        __syncthreads();
-        for (int w = 0; w < W; ++w) {
-            // group t: lane t of every wave when G <= 64; otherwise lane
-            // t % 64 of the waves whose first group is t rounded down to 64
-            double tot = 0.0;
-            if (wave_reports)
-                for (int v2 = 0; v2 < nwaves; ++v2)
-                    if (G <= 64 || ((v2 * 64) & (G - 1)) == wave * 64)
-                        tot += red[w * T + v2 * 64 + (t & 63)];
-            out[w] = tot;
-        }
-        __syncthreads();
+        for (int w = 0; w < W; ++w) out[w] = tot[w];
     };
 
     auto held_value = [&](auto oc) __attribute__((always_inline)) -> float {
@@ -937,9 +961,14 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
             }
             if (k < kend) step(std::integral_constant<int, 0>{}, k++);
         }
-        if (B.ckpt_every > 0 && k % B.ckpt_every == 0) {
+        const bool checkpoint = B.ckpt_every > 0 && k % B.ckpt_every == 0;
+        if (checkpoint || (!SINGLE && k == B.K)) {
             double en[W];
             agent_energy(k & 1, en);
+            if (!SINGLE && wave_reports)
+                for (int w = 0; w < W; ++w)
+                    put(reports(w), B.energy + static_cast<size_t>(e) * B.M + agent0 + t * W + w, en[w], B.trash);
+            if (!checkpoint) break;
             if (wave_reports)
                 for (int w = 0; w < W; ++w)
                     put(reports(w), B.etrace + (static_cast<size_t>(e) * B.n_ckpt + ck) * B.M + agent0 + t * W + w,

@@ -32,7 +32,6 @@ struct Schedule {
     std::vector<int32_t> gitem_gang, gitem_band;
     int64_t xg_floats = 0, part_entries = 0;
     int max_bands = 0;
-    int n_chunks = 0;  // of the largest event without gangs (batch_energy)
     int items() const { return static_cast<int>(item_event.size() + gitem_gang.size()); }
 };
 
@@ -103,7 +102,7 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
     const int n_ckpt = p.energy_every > 0 ? p.steps / p.energy_every : 0;
     S.gangs.clear();
     S.xg_floats = S.part_entries = 0;
-    S.max_bands = S.n_chunks = 0;
+    S.max_bands = 0;
     std::vector<int64_t> gang_cost;
     int64_t row_off = 0, nz_off = 0;
     for (int32_t e = 0; e < E; ++e) {
@@ -119,7 +118,6 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
         d.event_id = same_start ? p.event : p.event + e;
         d.c0_scale = c0_scale ? static_cast<float>(c0_scale[e]) : 1.0f;
         d.gang = n[e] > band_limit;
-        if (!d.gang) S.n_chunks = std::max(S.n_chunks, (n[e] + sbt::kEnergyChunk - 1) / sbt::kEnergyChunk);
         if (n[e] > band_limit) {
             // row bands of balanced size, one gang per agent
             const int bands = (n[e] + band_limit - 1) / band_limit;
@@ -197,7 +195,7 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
 }
 
 struct BatchLayout {
-    size_t ev, item_e, item_a, item_lg, J16, colr, h, c0, offset, perm, rank, sched, counter, trash, etrace, energy, epart, halves, T;
+    size_t ev, item_e, item_a, item_lg, J16, colr, h, c0, offset, perm, rank, sched, counter, trash, etrace, split_at, energy, halves, T;
     size_t gangs, gitem_g, gitem_b, xg, gints, gpart, gclock, done;
     size_t total;
     int n_ckpt;
@@ -229,8 +227,8 @@ BatchLayout make_layout(const Schedule &S, const sbt_solve_params &p) {
     L.trash = take(64);
     L.etrace = take(sizeof(double) * E * static_cast<size_t>(L.n_ckpt) * M);
     L.halves = take(sizeof(int) * E);
+    L.split_at = take(sizeof(double) * E);
     L.energy = take(sizeof(double) * E * M);
-    L.epart = take(sizeof(double) * E * static_cast<size_t>(S.n_chunks) * M);
     L.T = take(static_cast<size_t>(S.sum_n) * M);
     const size_t G = S.gangs.size(), GI = S.gitem_gang.size();
     L.gangs = take(sizeof(sbt::GangDesc) * G);
@@ -421,9 +419,8 @@ extern "C" int sbt_batch_run_tuned(const sbt_dev_batch *batch, sbt_mode mode, sb
     B.trash = ws + L.trash;
     B.etrace = reinterpret_cast<double *>(ws + L.etrace);
     B.energy = out->agent_energy ? out->agent_energy : reinterpret_cast<double *>(ws + L.energy);
-    B.epart = reinterpret_cast<double *>(ws + L.epart);
+    B.split_at = reinterpret_cast<double *>(ws + L.split_at);
     B.halves = reinterpret_cast<int *>(ws + L.halves);
-    B.n_chunks = S.n_chunks;
     B.trace = out->trace;
     B.best_energy = out->best_energy;
     B.best_agent = out->best_agent;
@@ -498,8 +495,6 @@ extern "C" int sbt_batch_run_tuned(const sbt_dev_batch *batch, sbt_mode mode, sb
         e = sbt::launch_batch_gang_reduce(B, n_gangs, st);
         if (e != hipSuccess) return fail(SBT_EDEVICE, "%s: gang reduce: %s", who, hipGetErrorString(e));
     }
-    e = sbt::launch_batch_energy(B, st);
-    if (e != hipSuccess) return fail(SBT_EDEVICE, "%s: batch energy: %s", who, hipGetErrorString(e));
     e = sbt::launch_batch_select(B, st);
     if (e != hipSuccess) return fail(SBT_EDEVICE, "%s: batch select: %s", who, hipGetErrorString(e));
     if (out->agent_trace)
