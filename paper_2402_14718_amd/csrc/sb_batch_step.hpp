@@ -43,14 +43,24 @@ __global__ __launch_bounds__(TPB, 4) void sb_batch(BatchArgs B) {
         // multiply-add takes those as they are, where a BF16 value costs an
         // instruction to mask (couplings of track events lie in 0.23..0.25:
         // 128 events of 20-1000 particles, dSB: 94.3 -> 90.8 ms)
-        if constexpr (JP == kJBf16) {
-            if (__builtin_amdgcn_readfirstlane(B.halves[B.item_event[item]]) != 0)
-                rows_item<MODE, kJBf16Half, TPB, kBatchSPT, kBatchAgents, false>(B, smem, item);
+        const int e = B.item_event[item];
+        // an item of at most two slots runs without a branch in its steps
+        const int lg_groups = max(0, __builtin_amdgcn_readfirstlane(B.item_lg[item]) - (kBatchAgents - 1));
+        const bool small = (__builtin_amdgcn_readfirstlane(B.ev[e].n) << lg_groups) <= 2 * TPB;
+        auto solve = [&](auto jc) __attribute__((always_inline)) {
+            constexpr int J = decltype(jc)::value;
+            if (small)
+                rows_item<MODE, J, TPB, 2, kBatchAgents, false>(B, smem, item);
             else
-                rows_item<MODE, JP, TPB, kBatchSPT, kBatchAgents, false>(B, smem, item);
-        } else {
-            rows_item<MODE, JP, TPB, kBatchSPT, kBatchAgents, false>(B, smem, item);
+                rows_item<MODE, J, TPB, kBatchSPT, kBatchAgents, false>(B, smem, item);
+        };
+        if constexpr (JP == kJBf16) {
+            if (__builtin_amdgcn_readfirstlane(B.halves[e]) != 0) {
+                solve(std::integral_constant<int, kJBf16Half>{});
+                continue;
+            }
         }
+        solve(std::integral_constant<int, JP>{});
     }
 }
 
@@ -60,7 +70,7 @@ template <int MODE, int JP, int TPB>
 hipError_t launch_batch_steps_tu(const BatchArgs &B, hipStream_t st) {
     using L = RowsLds<MODE, TPB, kBatchSPT, kBatchAgents>;
     BatchArgs A = B;
-    A.tail_cap = L::tail_words(B.tail_cap);
+    A.lds = static_cast<int>(L::bytes(L::tail_words(B.tail_cap)));
     // the 16-bit LDS addresses assume the dynamic LDS starts at address 0,
     // which holds when the kernel has no static LDS
     static const bool base_zero = [] {
@@ -70,7 +80,7 @@ hipError_t launch_batch_steps_tu(const BatchArgs &B, hipStream_t st) {
                fa.sharedSizeBytes == 0;
     }();
     if (!base_zero) return hipErrorInvalidConfiguration;
-    return launch_with_lds(sb_batch<MODE, JP, TPB>, dim3(A.grid), dim3(TPB), L::bytes(A.tail_cap), st, A);
+    return launch_with_lds(sb_batch<MODE, JP, TPB>, dim3(A.grid), dim3(TPB), A.lds, st, A);
 }
 
 }  // namespace sbt

@@ -73,6 +73,7 @@ struct BatchArgs {
     int E, M, K, ckpt_every, n_ckpt;
     int n_items, item_begin;     // this launch's items: [item_begin, item_begin + n_items)
     int grid, tail_cap;          // persistent workgroups; LDS words for staged couplings
+    int lds;                     // batch: LDS bytes of a workgroup
     uint32_t seed_lo, seed_hi;
     float dt, dta0;
     double c0_fixed;             // > 0: fixed c0 for every event

@@ -431,10 +431,11 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
     // memory.  The scan's scratch is the buffer no wave reads yet.
     int *scan = reinterpret_cast<int *>(L::kRedInBuf ? smem + L::kBuf : smem + 2 * L::kBuf);
     int t_total = 0, big_total = 0;
+    const int tail_cap = SINGLE ? B.tail_cap : min(B.tail_cap, (B.lds - static_cast<int>(L::kTails)) / 4);
     const int t_base = block_exclusive_scan(tsum, scan, t_total);
     (void)block_exclusive_scan(tbig, scan, big_total);
     constexpr int kTW = kWide ? 2 : 1;  // words per tail entry
-    const bool lds_tails = __builtin_amdgcn_readfirstlane(t_total) * kTW <= B.tail_cap &&
+    const bool lds_tails = __builtin_amdgcn_readfirstlane(t_total) * kTW <= tail_cap &&
                            __builtin_amdgcn_readfirstlane(big_total) == 0;
     if (lds_tails && any_tail > 0) {
         int o = t_base;

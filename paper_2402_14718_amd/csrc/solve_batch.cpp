@@ -145,6 +145,13 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
                    static_cast<double>(n[e]) * (1 << (lg - 1)) >
                        kLeastFill * tpb_of(small) * sbt::kBatchSPT * sbt::kBatchAgents)
                 --lg;
+            // (two slots or fewer take the branch-free steps: on to there while
+            // an item is more than a workgroup's share of the launch)
+            int few = lg;
+            while (few > 1 && static_cast<double>(cost) * (1 << few) > kItemsPerGroup * share[small ? 1 : 0] &&
+                   (static_cast<int64_t>(n[e]) << (few - 1)) > 2 * tpb_of(small))
+                --few;
+            if (few > 0 && (static_cast<int64_t>(n[e]) << (few - 1)) <= 2 * tpb_of(small)) lg = few;
             for (int a0 = 0; a0 < p.agents;) {
                 // (the last items of an odd number of agents are smaller)
                 while (lg > 1 && (1 << lg) > p.agents - a0) --lg;
