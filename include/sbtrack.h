@@ -473,7 +473,9 @@ typedef struct {
  * Shapes: 1024 threads per workgroup, one workgroup per CU (any n up to
  * 9216), and 512 threads, two workgroups per CU (n up to 4608), each with 9
  * position slots per thread.  The 1024-thread items run first, then the
- * 512-thread items, each as one persistent launch over its own queue. */
+ * 512-thread items, each as one persistent launch over its own queue.  Events
+ * whose rows are longer than registers and LDS of a shape hold run on the
+ * 1024-thread shape, with one agent per LDS word where two do not fit. */
 typedef struct {
     int32_t split_n;     /* events with n <= split_n (and n <= 4608) run on the */
                          /*   512-thread shape; 0 = chosen: every event that    */

@@ -148,6 +148,19 @@ __global__ __launch_bounds__(256) void batch_prep(BatchArgs B, int jprec) {
     }
     if (E.n > kBatchSlots) return;  // (a gang: it needs no spin order)
     rank_rows(E.n, B.row_ptr + E.rp_off, B.perm + E.row_off, B.rank + E.row_off, bins);
+    if (E.n > kBatchSlotsSmall) {
+        // (a list entry's place has 5 bits for a row's length: see rows_item)
+        int rest = 0, longest = 0;
+        for (int q = t; q < E.n; q += 256) {
+            const int i = B.perm[E.row_off + q];
+            const int past = max(0, B.row_ptr[E.rp_off + i + 1] - B.row_ptr[E.rp_off + i] - kHeldCaps[1][q / kBatchTPB]);
+            rest += past;
+            longest = max(longest, past);
+        }
+        (void)block_exclusive_scan(rest, bins, rest);
+        const int list = __syncthreads_or(longest > 31) ? INT32_MAX : rest;
+        if (t == 0) B.long_rows[e] = list > B.list_room;
+    }
     // columns as ranks, for the step kernel's LDS addresses
     for (int i = t; i < E.n; i += 256)
         for (int p = B.row_ptr[E.rp_off + i]; p < B.row_ptr[E.rp_off + i + 1]; ++p)
@@ -251,21 +264,21 @@ hipError_t launch_batch_reset(int *counters, int n, hipStream_t st) {
 }
 
 template <int TPB>
-static hipError_t steps_of_shape(int mode, int jprec, const BatchArgs &B, hipStream_t st) {
+static hipError_t steps_of_shape(int mode, int jprec, bool long_rows, const BatchArgs &B, hipStream_t st) {
     const bool f16 = jprec == kJFp16;
     if (mode == kDSB)
-        return f16 ? launch_batch_steps_tu<kDSB, kJFp16, TPB>(B, st)
-                   : launch_batch_steps_tu<kDSB, kJBf16, TPB>(B, st);
+        return f16 ? launch_batch_steps_tu<kDSB, kJFp16, TPB>(B, long_rows, st)
+                   : launch_batch_steps_tu<kDSB, kJBf16, TPB>(B, long_rows, st);
     if (mode == kASB)
-        return f16 ? launch_batch_steps_tu<kASB, kJFp16, TPB>(B, st)
-                   : launch_batch_steps_tu<kASB, kJBf16, TPB>(B, st);
-    return f16 ? launch_batch_steps_tu<kBSB, kJFp16, TPB>(B, st)
-               : launch_batch_steps_tu<kBSB, kJBf16, TPB>(B, st);
+        return f16 ? launch_batch_steps_tu<kASB, kJFp16, TPB>(B, long_rows, st)
+                   : launch_batch_steps_tu<kASB, kJBf16, TPB>(B, long_rows, st);
+    return f16 ? launch_batch_steps_tu<kBSB, kJFp16, TPB>(B, long_rows, st)
+               : launch_batch_steps_tu<kBSB, kJBf16, TPB>(B, long_rows, st);
 }
 
-hipError_t launch_batch_steps(int mode, int jprec, int tpb, const BatchArgs &B, hipStream_t st) {
-    if (tpb == kBatchTPBSmall) return steps_of_shape<kBatchTPBSmall>(mode, jprec, B, st);
-    if (tpb == kBatchTPB) return steps_of_shape<kBatchTPB>(mode, jprec, B, st);
+hipError_t launch_batch_steps(int mode, int jprec, int tpb, bool long_rows, const BatchArgs &B, hipStream_t st) {
+    if (tpb == kBatchTPBSmall) return steps_of_shape<kBatchTPBSmall>(mode, jprec, long_rows, B, st);
+    if (tpb == kBatchTPB) return steps_of_shape<kBatchTPB>(mode, jprec, long_rows, B, st);
     return hipErrorInvalidValue;
 }
 

@@ -11,6 +11,6 @@
 namespace sbt {
 
 template hipError_t launch_batch_steps_tu<SBT_BATCH_MODE, SBT_BATCH_JP, SBT_BATCH_TPB>(
-    const BatchArgs &B, hipStream_t st);
+    const BatchArgs &B, bool long_rows, hipStream_t st);
 
 }  // namespace sbt

@@ -53,6 +53,12 @@ constexpr int kBatchSlots = kBatchTPB * kBatchSPT;  // largest n * agents / 2 pe
 constexpr int kBatchSlotsSmall = kBatchTPBSmall * kBatchSPT;
 constexpr int kBatchTailCap = 8192;                 // default LDS words for couplings past the
                                                     //   slots' register capacity (32 KB)
+// Couplings of a row that the step loop holds in registers, by slot (slot 0 has
+// the longest rows); [1]: nine slots whose state leaves room for fewer.
+constexpr int kHeldCaps[2][kBatchSPT] = {{16, 8, 5, 4, 3, 2, 2, 2, 1}, {12, 6, 4, 3, 2, 2, 2, 2, 1}};
+// LDS words left for other couplings by nine slots of two agents on 1024
+// threads, by mode.
+constexpr int kBatchListWords[3] = {4080, 7152, 4080};
 // coupling formats: 16-bit (batch), FP32, FP8 e4m3 with a per-row scale,
 // FP8 e4m3 with a per-block scale (blocks of 8 padded couplings of a row),
 // BF16 hi + lo pairs (streaming kernels, sb_stream_kernels.hpp)
@@ -99,6 +105,10 @@ struct BatchArgs {
     int *counter;                // this launch's work queue counter
     double *etrace;              // [E * n_ckpt * M]
     int *halves;                 // [E] BF16 couplings: all of the event are FP16 values
+    int *long_rows;              // [E] events of more than kBatchSlotsSmall spins whose couplings past the
+                                 //   registers of two agents are more than list_room (prep output)
+    int list_room;
+    int over_items;              // first items of the launch for long rows that belong to the one of two agents
     double *split_at;            // [E] where rows_item splits an event's energy terms (prep output)
     double *energy;              // [E * M] final O(T)
     double *trace;               // [E * n_ckpt] best so far, or null
@@ -142,11 +152,12 @@ struct GangDesc {
 hipError_t launch_batch_prep(int jprec, const BatchArgs &B, hipStream_t st);
 // resets the launch counters (kernels, so the reset can be graph-captured)
 hipError_t launch_batch_reset(int *counters, int n, hipStream_t st);
-hipError_t launch_batch_steps(int mode, int jprec, int tpb, const BatchArgs &B, hipStream_t st);
+// (long_rows: the items of one agent per word, 1024 threads)
+hipError_t launch_batch_steps(int mode, int jprec, int tpb, bool long_rows, const BatchArgs &B, hipStream_t st);
 // the step kernel of one mode, coupling format and shape, instantiated in
 // its own translation unit (sb_batch_mode.hip, built once per triple)
 template <int MODE, int JP, int TPB>
-hipError_t launch_batch_steps_tu(const BatchArgs &B, hipStream_t st);
+hipError_t launch_batch_steps_tu(const BatchArgs &B, bool long_rows, hipStream_t st);
 
 hipError_t launch_batch_select(const BatchArgs &B, hipStream_t st);
 // the gang launch (persistent grid of `B.grid` 1024-thread workgroups) and

@@ -15,7 +15,7 @@ namespace sbt {
 template <int MODE, int TPB, int S, int W>
 __global__ __launch_bounds__(TPB) void sb_resident_rows(BatchArgs B) {
     extern __shared__ __align__(16) unsigned char smem[];
-    rows_item<MODE, kJFp32, TPB, S, W, true>(B, smem, 0);
+    rows_item<MODE, kJFp32, TPB, S, W, true>(B, smem, 0, static_cast<int>(blockIdx.x) * W, 0);
 }
 
 namespace {

@@ -54,14 +54,13 @@ namespace {
 // Couplings held per slot, by slot: slot 0 holds the longest rows.  On the
 // 1000-particle event (n = 8484, 9 slots of 1024) the longest rows by slot
 // are 19-26, 6-7, 4, 3, 2, 2, 2, 2, 1.  FEW: nine slots, whose state leaves
-// room for fewer (all but FP32 bSB of one agent).  With the larger set the
+// room for fewer (two agents, and one of FP32 dSB).  With the larger set the
 // step spilled: two agents, FP32, 8484 spins x 1024, bSB 8.4 against 5.3 us a
 // step; batch of 96 events of 20-400 particles, bSB, FP16, 6.19 against
 // 5.95 ms; 128 of 20-1000, dSB, FP16, 31.8 against 31.2.
 template <bool FEW>
 struct Held {
-    static constexpr int kCaps[2][kBatchSPT] = {{16, 8, 5, 4, 3, 2, 2, 2, 1}, {12, 6, 4, 3, 2, 2, 2, 2, 1}};
-    static __host__ __device__ constexpr int cap(int s) { return kCaps[FEW ? 1 : 0][s]; }
+    static __host__ __device__ constexpr int cap(int s) { return kHeldCaps[FEW ? 1 : 0][s]; }
     static __host__ __device__ constexpr int before(int s) {
         int o = 0;
         for (int i = 0; i < s; ++i) o += cap(i);
@@ -209,9 +208,10 @@ struct RowsLds {
     static size_t bytes(int tails) { return kTails + sizeof(uint32_t) * static_cast<size_t>(tails); }
 };
 
-// Solves one item; SINGLE: the one event, agents b * W .. in workgroup b.
+// Solves one item: agents agent0 .. of event e, 2^lg groups of W; SINGLE: the
+// one event, agents b * W .. in workgroup b.  (All three wave-uniform.)
 template <int MODE, int JP, int TPB, int S, int W, bool SINGLE>
-__device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *smem, int item) {
+__device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *smem, int e, int agent0, int lgG) {
     constexpr bool kHalf = JP == kJFp16 || JP == kJBf16Half;  // held as FP16
     using V = Shared<MODE, W>;
     using word = typename V::type;
@@ -222,7 +222,7 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
     // first buffer has one, else the position
     constexpr bool kBytesHeld = L::kBuf <= 65536;
     constexpr uint32_t kScale = kBytesHeld ? kB : 1;
-    using H = Held<S == kBatchSPT && (!kWide || W == 2 || MODE == kDSB)>;
+    using H = Held<S == kBatchSPT && (W == 2 || (kWide && MODE == kDSB))>;
     constexpr int kHeld = H::before(S);
     // FP32 couplings: their addresses two to a register, or one, where the
     // registers allow it (an instruction less per coupling; with the finer
@@ -246,14 +246,6 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
         }
     };
 
-    int e = 0, agent0, lgG = 0;
-    if constexpr (SINGLE) {
-        agent0 = static_cast<int>(blockIdx.x) * W;
-    } else {
-        e = __builtin_amdgcn_readfirstlane(B.item_event[item]);
-        agent0 = __builtin_amdgcn_readfirstlane(B.item_agent0[item]);
-        lgG = max(0, __builtin_amdgcn_readfirstlane(B.item_lg[item]) - (W - 1));
-    }
     const BatchEvent E = SINGLE ? B.one : B.ev[e];
     const int n = E.n;
     const int G = 1 << lgG;
@@ -342,14 +334,18 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
     auto address = [&](uint32_t colr) -> uint32_t {
         return ((colr & (kColUpper - 1)) * G + g) * kScale;
     };
+    auto coupling_of = [&](uint16_t j) -> uint32_t {
+        if constexpr (JP == kJBf16Half)
+            return static_cast<uint32_t>(
+                       __half_as_ushort(__float2half_rn(__uint_as_float(static_cast<uint32_t>(j) << 16)))) << 16;
+        else
+            return static_cast<uint32_t>(j) << 16;
+    };
     auto coupling = [&](int p) -> uint32_t {
         if constexpr (kWide)
             return __float_as_uint(B.J32[p]);
-        else if constexpr (JP == kJBf16Half)
-            return static_cast<uint32_t>(__half_as_ushort(
-                       __float2half_rn(__uint_as_float(static_cast<uint32_t>(B.J16[p]) << 16)))) << 16;
         else
-            return static_cast<uint32_t>(B.J16[p]) << 16;
+            return coupling_of(B.J16[p]);
     };
     auto self_of = [&](int s, const Place &P) -> uint32_t { return static_cast<uint32_t>(place(s, P)) * kScale; };
     if constexpr (kWide) {
@@ -811,18 +807,35 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
                     const int i = spin_at(s, P, there);
                     const int len = row_of(i, there, p0);
                     const int most = wave_max_at(len, static_cast<int>(P.even & 63u));
-                    // (eight in flight: one at a time they cost a memory
-                    // latency each)
+                    // eight at a time (one at a time they cost a memory
+                    // latency each), as runs of memory: lanes hold rows of
+                    // their own, so an access costs a cache line per lane
+                    // whatever its width (entries past the row's end are
+                    // read, at most seven past the last row's, and not used:
+                    // the arrays lie in the workspace with others after them)
                     constexpr int U = 8;
                     for (int u0 = CAP; u0 < most; u0 += U) {
                         uint32_t v[U], a[U];
                         word x[U];
+                        const int at = u0 < len ? E.nz_off + p0 + u0 : 0;
+                        struct __attribute__((packed, aligned(2))) Half8 {
+                            uint16_t v[U];
+                        };
+                        const Half8 cols = *reinterpret_cast<const Half8 *>(B.colr + at);
+                        if constexpr (kWide) {
+                            struct __attribute__((packed, aligned(4))) Float8 {
+                                float v[U];
+                            };
+                            const Float8 js = *reinterpret_cast<const Float8 *>(B.J32 + at);
 #pragma unroll
-                        for (int u = 0; u < U; ++u) {
-                            const int p = u0 + u < len ? E.nz_off + p0 + u0 + u : 0;
-                            v[u] = coupling(p);
-                            a[u] = B.colr[p];
+                            for (int u = 0; u < U; ++u) v[u] = __float_as_uint(js.v[u]);
+                        } else {
+                            const Half8 js = *reinterpret_cast<const Half8 *>(B.J16 + at);
+#pragma unroll
+                            for (int u = 0; u < U; ++u) v[u] = coupling_of(js.v[u]);
                         }
+#pragma unroll
+                        for (int u = 0; u < U; ++u) a[u] = cols.v[u];
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
                             launder(v[u]);

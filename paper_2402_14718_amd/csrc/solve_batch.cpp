@@ -22,10 +22,12 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Schedule {
     std::vector<sbt::BatchEvent> ev;
-    // items of the 1024-thread launch first, then those of the 512-thread
-    // launch, each group in decreasing-cost order
+    // items of the 512-thread launch first, then those of the 1024-thread
+    // launch, which the launch for long rows goes through too, and its own;
+    // each group in decreasing-cost order
     std::vector<int32_t> item_event, item_agent0, item_lg;
-    int n_large = 0, n_small = 0;  // items per launch
+    int n_small = 0, n_large = 0, n_long = 0;  // items per group
+    bool maybe_long = false;                   // an event of the second group may have long rows
     int64_t sum_n = 0, sum_nnz = 0;
     // events above the band limit: one gang of row bands per agent
     std::vector<sbt::GangDesc> gangs;
@@ -37,15 +39,60 @@ struct Schedule {
 
 int tpb_of(bool small) { return small ? sbt::kBatchTPBSmall : sbt::kBatchTPB; }
 
-// Agents per work item: the largest power of two A with n * A / 2 (two
-// agents share a slot) within `fill` of the shape's slots (and A <= agents,
-// A / 2 <= its threads); at least one agent, two where the event has them.
-int lg_agents_for(int32_t n, int32_t M, int tpb, double fill) {
-    const double cap = fill * tpb * sbt::kBatchSPT * sbt::kBatchAgents;
-    int lg = M >= sbt::kBatchAgents ? 1 : 0;
-    static_assert(sbt::kBatchAgents == 2, "lg counts pairs");
-    while ((2 << lg) <= M && (1 << lg) <= tpb && static_cast<double>(n) * (2 << lg) <= cap) ++lg;
+// Agents per work item: the largest power of two A with n * A / W (W agents
+// share a slot: two, or one) within `fill` of the shape's slots (and A <= agents,
+// A / W <= its threads); at least one agent, W where the event has them.
+int lg_agents_for(int32_t n, int32_t M, int tpb, int W, double fill) {
+    const double cap = fill * tpb * sbt::kBatchSPT * W;
+    int lg = M >= W ? W - 1 : 0;
+    while ((2 << lg) <= M && (2 << lg) <= W * tpb && static_cast<double>(n) * (2 << lg) <= cap) ++lg;
     return lg;
+}
+
+// Long rows.  Couplings past those held in registers go to a list in LDS; an
+// item whose list does not fit reads them from memory in every step, which
+// costs more than any other choice here (us a step of 16 events, shape by size
+// alone / by the list: 64 spins of 8 couplings x 100 agents 4.9 / 0.5; 2000 of 8
+// x 1 8.7 / 2.1; 4000 of 4.5 x 100 26.5 / 10.2).  Only n and nnz are known when
+// a batch is planned, so the list is estimated for row lengths of mean r = nnz /
+// n and deviation sqrt(r), longest first.  Rows of at most kShortRows couplings
+// on average are taken to fit: track events of up to 4608 spins have 2 to 3.2, a
+// few rows of them long, and their lists are empty.
+constexpr double kShortRows = 3.5;
+// Nine slots of two agents hold 34 couplings for nine spins, and a list beside
+// them: events of at most this many per spin are not asked for long rows.
+constexpr int64_t kFewCouplings = 3;
+
+double tail_words(double n, double r, int G, int tpb, int W) {
+    const double used = n * G;
+    const bool two = W == 2 && used <= 2.0 * tpb;
+    double sum = 0.0;
+    for (int s = 0; s < sbt::kBatchSPT && s * tpb < used; ++s) {
+        const double here = std::min<double>(tpb, used - s * tpb);
+        for (int u = 0; u < 4; ++u) {
+            const double q = (s * tpb + (u + 0.5) / 4 * here) / used;
+            const double z = 4.91 * (std::pow(1.0 - q, 0.14) - std::pow(q, 0.14));  // normal quantile
+            const double len = std::min(n - 1, r + std::sqrt(r) * z);
+            sum += here / 4 * std::max(0.0, len - sbt::kHeldCaps[W == 2 && !two ? 1 : 0][s]);
+        }
+    }
+    return 1.1 * sum;
+}
+
+// Words of the list, in the mode that leaves the fewest (bSB), of a shape's
+// workgroups with nine slots of W agents (W = 2: or with two in the same LDS).
+double list_words(int tpb, int slots, int W, int asked) {
+    auto tails = [&](int S) { return 8 * S * tpb * W + 64; };
+    const int most = tpb == sbt::kBatchTPBSmall ? 81920 : 163840;
+    const int lds = tails(sbt::kBatchSPT) + 4 * std::min(asked, (most - tails(sbt::kBatchSPT)) / 4);
+    return std::min(asked, (lds - tails(slots)) / 4);
+}
+
+bool list_fits(int32_t n, int64_t nnz, int G, int tpb, int W, int asked) {
+    const double r = static_cast<double>(nnz) / n;
+    if (r <= kShortRows) return true;
+    const bool two = W == 2 && static_cast<int64_t>(n) * G <= 2 * tpb;
+    return tail_words(n, r, G, tpb, W) <= list_words(tpb, two ? 2 : sbt::kBatchSPT, W, asked);
 }
 
 // A shape's workgroups run side by side (one per CU, or two of the small
@@ -86,18 +133,26 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
         int64_t cost;
         int32_t e, a0, lg;
     };
-    std::vector<Item> items[2];  // [0]: 1024-thread shape, [1]: 512-thread shape
+    enum { kSmall, kLarge, kLong };  // 512 threads, 1024 threads, 1024 threads with one agent per word
+    std::vector<Item> items[3];
     // split_n = 0: every event that fits it on the 512-thread shape, whose
     // two workgroups per CU hide each other's barriers (512 events x 128
     // agents, dSB BF16: VALU busy 0.79 against 0.66 on the 1024-thread shape)
     const int32_t split = tu.split_n > 0 ? tu.split_n : sbt::kBatchSlotsSmall;
-    double share[2] = {0.0, 0.0};  // largest cost of an item
+    // Long rows whose list fits the 512-thread shape in no item go to the 1024,
+    // and there to one agent per word where two do not fit either.  Of events
+    // past the 512-thread shape the device knows that itself, from their rows.
+    auto launch_of = [&](int32_t e) -> int {
+        if (n[e] > sbt::kBatchSlotsSmall) return kLarge;
+        auto fits = [&](int tpb) { return list_fits(n[e], nnz[e], 1, tpb, sbt::kBatchAgents, tu.tail_words); };
+        if (n[e] <= split && fits(sbt::kBatchTPBSmall)) return kSmall;
+        return fits(sbt::kBatchTPB) ? kLarge : kLong;
+    };
+    double share[3] = {0.0, 0.0, 0.0};  // largest cost of an item
     for (int32_t e = 0; e < E; ++e)
         if (n[e] > 0 && nnz[e] >= 0)
-            share[n[e] <= split && n[e] <= sbt::kBatchSlotsSmall ? 1 : 0] +=
-                (static_cast<double>(n[e]) + static_cast<double>(nnz[e])) * p.agents;
-    share[0] /= kItemsPerGroup * kCUs;
-    share[1] /= kItemsPerGroup * 2.0 * kCUs;
+            share[launch_of(e)] += (static_cast<double>(n[e]) + static_cast<double>(nnz[e])) * p.agents;
+    for (int l = kSmall; l <= kLong; ++l) share[l] /= kItemsPerGroup * kCUs * (l == kSmall ? 2.0 : 1.0);
     const int band_limit = tu.band_rows > 0 ? tu.band_rows : sbt::kBatchSlots;
     const int n_ckpt = p.energy_every > 0 ? p.steps / p.energy_every : 0;
     S.gangs.clear();
@@ -108,7 +163,7 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
     for (int32_t e = 0; e < E; ++e) {
         if (n[e] < 1) return fail(SBT_EINVAL, "%s: event %d has n = %d", who, e, n[e]);
         if (nnz[e] < 0) return fail(SBT_EINVAL, "%s: event %d has nnz < 0", who, e);
-        const bool small = n[e] <= split && n[e] <= sbt::kBatchSlotsSmall;
+        const int launch = launch_of(e), tpb = tpb_of(launch == kSmall);
         sbt::BatchEvent &d = S.ev[e];
         d.n = n[e];
         d.nnz = static_cast<int>(nnz[e]);
@@ -140,23 +195,36 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
                 return fail(SBT_EINVAL, "%s: too many row bands for 32-bit offsets", who);
         } else {
             const int64_t cost = static_cast<int64_t>(n[e]) + nnz[e];
-            int lg = lg_agents_for(n[e], p.agents, tpb_of(small), tu.fill);
-            while (lg > 1 && static_cast<double>(cost) * (1 << lg) > share[small ? 1 : 0] &&
-                   static_cast<double>(n[e]) * (1 << (lg - 1)) >
-                       kLeastFill * tpb_of(small) * sbt::kBatchSPT * sbt::kBatchAgents)
+            // (these items hold kBatchAgents agents at most: the launch for long rows takes them one by one)
+            S.maybe_long |= n[e] > sbt::kBatchSlotsSmall && nnz[e] > kFewCouplings * n[e];
+            const int W = launch == kLong ? 1 : sbt::kBatchAgents;
+            const int least = W - 1;  // (log2 of the fewest agents of an item)
+            int lg = lg_agents_for(n[e], p.agents, tpb, W, tu.fill);
+            while (lg > least && static_cast<double>(cost) * (1 << lg) > share[launch] &&
+                   static_cast<double>(n[e]) * (1 << (lg - 1)) > kLeastFill * tpb * sbt::kBatchSPT * W)
                 --lg;
             // (two slots or fewer take the branch-free steps: on to there while
             // an item is more than a workgroup's share of the launch)
-            int few = lg;
-            while (few > 1 && static_cast<double>(cost) * (1 << few) > kItemsPerGroup * share[small ? 1 : 0] &&
-                   (static_cast<int64_t>(n[e]) << (few - 1)) > 2 * tpb_of(small))
-                --few;
-            if (few > 0 && (static_cast<int64_t>(n[e]) << (few - 1)) <= 2 * tpb_of(small)) lg = few;
+            if (W == 2) {
+                int few = lg;
+                while (few > 1 && static_cast<double>(cost) * (1 << few) > kItemsPerGroup * share[launch] &&
+                       (static_cast<int64_t>(n[e]) << (few - 1)) > 2 * tpb)
+                    --few;
+                if (few > 0 && (static_cast<int64_t>(n[e]) << (few - 1)) <= 2 * tpb) lg = few;
+            }
+            if (n[e] <= sbt::kBatchSlotsSmall) {
+                auto fits = [&](int l) {
+                    return list_fits(n[e], nnz[e], 1 << std::max(0, l - least), tpb, W, tu.tail_words);
+                };
+                int fit = lg;
+                while (fit > least && !fits(fit)) --fit;
+                if (fits(fit)) lg = fit;
+            }
             for (int a0 = 0; a0 < p.agents;) {
                 // (the last items of an odd number of agents are smaller)
-                while (lg > 1 && (1 << lg) > p.agents - a0) --lg;
+                while (lg > least && (1 << lg) > p.agents - a0) --lg;
                 const int used = std::min(1 << lg, p.agents - a0);
-                items[small ? 1 : 0].push_back({cost * used, e, a0, lg});
+                items[launch].push_back({cost * used, e, a0, lg});
                 a0 += used;
             }
         }
@@ -178,8 +246,9 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
             S.item_lg.push_back(it.lg);
         }
     }
-    S.n_large = static_cast<int>(items[0].size());
-    S.n_small = static_cast<int>(items[1].size());
+    S.n_small = static_cast<int>(items[kSmall].size());
+    S.n_large = static_cast<int>(items[kLarge].size());
+    S.n_long = static_cast<int>(items[kLong].size());
     // gangs: largest events first, then agent order; items gang after gang
     std::vector<int> order(S.gangs.size());
     std::iota(order.begin(), order.end(), 0);
@@ -202,7 +271,7 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
 }
 
 struct BatchLayout {
-    size_t ev, item_e, item_a, item_lg, J16, colr, h, c0, offset, perm, rank, sched, counter, trash, etrace, split_at, energy, halves, T;
+    size_t ev, item_e, item_a, item_lg, J16, colr, h, c0, offset, perm, rank, sched, counter, trash, etrace, split_at, energy, halves, long_rows, T;
     size_t gangs, gitem_g, gitem_b, xg, gints, gpart, gclock, done;
     size_t total;
     int n_ckpt;
@@ -230,10 +299,11 @@ BatchLayout make_layout(const Schedule &S, const sbt_solve_params &p) {
     L.perm = take(sizeof(int32_t) * static_cast<size_t>(S.sum_n));
     L.rank = take(sizeof(int32_t) * static_cast<size_t>(S.sum_n));
     L.sched = take(sizeof(float) * static_cast<size_t>(p.steps));
-    L.counter = take(2 * sizeof(int32_t));  // one per launch
+    L.counter = take(3 * sizeof(int32_t));  // one per launch
     L.trash = take(64);
     L.etrace = take(sizeof(double) * E * static_cast<size_t>(L.n_ckpt) * M);
     L.halves = take(sizeof(int) * E);
+    L.long_rows = take(sizeof(int) * E);
     L.split_at = take(sizeof(double) * E);
     L.energy = take(sizeof(double) * E * M);
     L.T = take(static_cast<size_t>(S.sum_n) * M);
@@ -428,6 +498,9 @@ extern "C" int sbt_batch_run_tuned(const sbt_dev_batch *batch, sbt_mode mode, sb
     B.energy = out->agent_energy ? out->agent_energy : reinterpret_cast<double *>(ws + L.energy);
     B.split_at = reinterpret_cast<double *>(ws + L.split_at);
     B.halves = reinterpret_cast<int *>(ws + L.halves);
+    B.long_rows = reinterpret_cast<int *>(ws + L.long_rows);
+    // (without the launch for them no event has long rows)
+    B.list_room = S.maybe_long ? std::min(tu.tail_words, sbt::kBatchListWords[mode]) : INT32_MAX;
     B.trace = out->trace;
     B.best_energy = out->best_energy;
     B.best_agent = out->best_agent;
@@ -448,7 +521,7 @@ extern "C" int sbt_batch_run_tuned(const sbt_dev_batch *batch, sbt_mode mode, sb
     const int cus = cu_count();
     hipError_t e = sbt::launch_batch_prep(jprec, B, st);
     if (e != hipSuccess) return fail(SBT_EDEVICE, "%s: batch prep: %s", who, hipGetErrorString(e));
-    SBT_HIP(sbt::launch_batch_reset(counters, 2, st));
+    SBT_HIP(sbt::launch_batch_reset(counters, 3, st));
     if (B.done) SBT_HIP(sbt::launch_zero_ints(B.done, batch->n_events, st));
     const int n_gangs = static_cast<int>(S.gangs.size());
     if (n_gangs > 0) {
@@ -477,26 +550,24 @@ extern "C" int sbt_batch_run_tuned(const sbt_dev_batch *batch, sbt_mode mode, sb
         e = sbt::launch_batch_gang(static_cast<int>(mode), jprec, LG, st);
         if (e != hipSuccess) return fail(SBT_EDEVICE, "%s: gang kernel: %s", who, hipGetErrorString(e));
     }
-    // the 1024-thread items (one workgroup per CU), then the 512-thread items
-    // (two per CU), each launch a persistent grid over its own queue
-    if (S.n_large > 0) {
-        sbt::BatchArgs L0 = B;
-        L0.item_begin = 0;
-        L0.n_items = S.n_large;
-        L0.counter = counters;
-        L0.grid = std::min(S.n_large, cus);
-        e = sbt::launch_batch_steps(static_cast<int>(mode), jprec, sbt::kBatchTPB, L0, st);
-        if (e != hipSuccess) return fail(SBT_EDEVICE, "%s: batch kernel: %s", who, hipGetErrorString(e));
-    }
-    if (S.n_small > 0) {
-        sbt::BatchArgs L1 = B;
-        L1.item_begin = S.n_large;
-        L1.n_items = S.n_small;
-        L1.counter = counters + 1;
-        L1.grid = std::min(S.n_small, 2 * cus);
-        e = sbt::launch_batch_steps(static_cast<int>(mode), jprec, sbt::kBatchTPBSmall, L1, st);
-        if (e != hipSuccess) return fail(SBT_EDEVICE, "%s: batch kernel: %s", who, hipGetErrorString(e));
-    }
+    // the 1024-thread items (one workgroup per CU) and those of long rows, then
+    // the 512-thread items (two per CU), each launch a persistent grid over its
+    // own queue
+    auto steps = [&](int begin, int items, int queue, int tpb, bool long_rows, int per_cu) {
+        sbt::BatchArgs A = B;
+        A.item_begin = begin;
+        A.n_items = items;
+        A.counter = counters + queue;
+        A.grid = std::min(items, per_cu * cus);
+        return items > 0 ? sbt::launch_batch_steps(static_cast<int>(mode), jprec, tpb, long_rows, A, st) : hipSuccess;
+    };
+    B.over_items = S.maybe_long ? S.n_large : 0;
+    e = steps(S.n_small, S.n_large, 0, sbt::kBatchTPB, false, 1);
+    if (e == hipSuccess)
+        e = steps(S.n_small + S.n_large - B.over_items, sbt::kBatchAgents * B.over_items + S.n_long, 1, sbt::kBatchTPB,
+                  true, 1);
+    if (e == hipSuccess) e = steps(0, S.n_small, 2, sbt::kBatchTPBSmall, false, 2);
+    if (e != hipSuccess) return fail(SBT_EDEVICE, "%s: batch kernel: %s", who, hipGetErrorString(e));
     if (out->step_end) SBT_HIP(hipEventRecord(static_cast<hipEvent_t>(out->step_end), st));
     if (n_gangs > 0) {
         e = sbt::launch_batch_gang_reduce(B, n_gangs, st);
