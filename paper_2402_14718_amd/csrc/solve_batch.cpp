@@ -63,21 +63,35 @@ constexpr double kShortRows = 3.5;
 // them: events of at most this many per spin are not asked for long rows.
 constexpr int64_t kFewCouplings = 3;
 
-double tail_words(double n, double r, int G, int tpb, int W) {
-    const double used = n * G;
-    const bool two = W == 2 && used <= 2.0 * tpb;
-    double sum = 0.0;
-    for (int s = 0; s < sbt::kBatchSPT && s * tpb < used; ++s) {
-        const double here = std::min<double>(tpb, used - s * tpb);
-        for (int u = 0; u < 4; ++u) {
-            const double q = (s * tpb + (u + 0.5) / 4 * here) / used;
-            const double z = 4.91 * (std::pow(1.0 - q, 0.14) - std::pow(q, 0.14));  // normal quantile
-            const double len = std::min(n - 1, r + std::sqrt(r) * z);
-            sum += here / 4 * std::max(0.0, len - sbt::kHeldCaps[W == 2 && !two ? 1 : 0][s]);
-        }
+// Couplings past those held, per position of an item whose positions fill some
+// slots: a table over r, made once (a plan and a run ask it several times per
+// event).
+class PastHeld {
+  public:
+    PastHeld() {
+        for (int used = 1; used <= sbt::kBatchSPT; ++used)
+            for (int u = 0; u < kPer * used; ++u) {
+                const double q = (u + 0.5) / (kPer * used);
+                const double z = 4.91 * (std::pow(1.0 - q, 0.14) - std::pow(q, 0.14));  // normal quantile
+                for (int few = 0; few < 2; ++few)
+                    for (int k = 0; k < kSteps; ++k) {
+                        const double r = static_cast<double>(k) / kPer, len = r + std::sqrt(r) * z;
+                        mean_[few][used - 1][k] += std::max(0.0, len - sbt::kHeldCaps[few][u / kPer]) / (kPer * used);
+                    }
+            }
     }
-    return 1.1 * sum;
-}
+    double at(bool few, int used, double r) const {
+        const double *v = mean_[few ? 1 : 0][std::min(used, sbt::kBatchSPT) - 1];
+        const int k = static_cast<int>(std::min(r, kMost) * kPer + 0.5);
+        return v[k] + std::max(0.0, r - kMost);
+    }
+
+  private:
+    static constexpr int kPer = 4;  // samples of a slot, and of r from one to the next
+    static constexpr double kMost = 64.0;
+    static constexpr int kSteps = kPer * 64 + 1;
+    double mean_[2][sbt::kBatchSPT][kSteps] = {};
+};
 
 // Words of the list, in the mode that leaves the fewest (bSB), of a shape's
 // workgroups with nine slots of W agents (W = 2: or with two in the same LDS).
@@ -89,10 +103,13 @@ double list_words(int tpb, int slots, int W, int asked) {
 }
 
 bool list_fits(int32_t n, int64_t nnz, int G, int tpb, int W, int asked) {
+    static const PastHeld past;
     const double r = static_cast<double>(nnz) / n;
     if (r <= kShortRows) return true;
-    const bool two = W == 2 && static_cast<int64_t>(n) * G <= 2 * tpb;
-    return tail_words(n, r, G, tpb, W) <= list_words(tpb, two ? 2 : sbt::kBatchSPT, W, asked);
+    const int64_t used = static_cast<int64_t>(n) * G;
+    const bool two = W == 2 && used <= 2 * tpb;
+    return 1.1 * past.at(W == 2 && !two, static_cast<int>((used + tpb - 1) / tpb), r) * static_cast<double>(used) <=
+           list_words(tpb, two ? 2 : sbt::kBatchSPT, W, asked);
 }
 
 // A shape's workgroups run side by side (one per CU, or two of the small
@@ -149,9 +166,12 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
         return fits(sbt::kBatchTPB) ? kLarge : kLong;
     };
     double share[3] = {0.0, 0.0, 0.0};  // largest cost of an item
+    std::vector<int8_t> launches(E, kSmall);
     for (int32_t e = 0; e < E; ++e)
-        if (n[e] > 0 && nnz[e] >= 0)
-            share[launch_of(e)] += (static_cast<double>(n[e]) + static_cast<double>(nnz[e])) * p.agents;
+        if (n[e] > 0 && nnz[e] >= 0) {
+            launches[e] = static_cast<int8_t>(launch_of(e));
+            share[launches[e]] += (static_cast<double>(n[e]) + static_cast<double>(nnz[e])) * p.agents;
+        }
     for (int l = kSmall; l <= kLong; ++l) share[l] /= kItemsPerGroup * kCUs * (l == kSmall ? 2.0 : 1.0);
     const int band_limit = tu.band_rows > 0 ? tu.band_rows : sbt::kBatchSlots;
     const int n_ckpt = p.energy_every > 0 ? p.steps / p.energy_every : 0;
@@ -163,7 +183,7 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
     for (int32_t e = 0; e < E; ++e) {
         if (n[e] < 1) return fail(SBT_EINVAL, "%s: event %d has n = %d", who, e, n[e]);
         if (nnz[e] < 0) return fail(SBT_EINVAL, "%s: event %d has nnz < 0", who, e);
-        const int launch = launch_of(e), tpb = tpb_of(launch == kSmall);
+        const int launch = launches[e], tpb = tpb_of(launch == kSmall);
         sbt::BatchEvent &d = S.ev[e];
         d.n = n[e];
         d.nnz = static_cast<int>(nnz[e]);
