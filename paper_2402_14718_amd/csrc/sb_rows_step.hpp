@@ -554,25 +554,29 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
                 }
             }
         });
+        // (both parts at once where the buffer has room for them)
+        constexpr int kAtOnce = L::kRedInBuf && kParts * L::kRed <= L::kBuf ? kParts : 1;
         double tot[W] = {};
-        for (int part = 0; part < kParts; ++part) {
-            for (int w = 0; w < W; ++w) {
-                // lanes with equal t % G hold the same agents
-                double sum = v[part][w];
-                for (int off = 32; off >= G; off >>= 1) sum += lane_xor(sum, lane, off);
-                red[w * T + t] = sum;
-            }
+        for (int part = 0; part < kParts; part += kAtOnce) {
+            for (int h = 0; h < kAtOnce; ++h)
+                for (int w = 0; w < W; ++w) {
+                    // lanes with equal t % G hold the same agents
+                    double sum = v[part + h][w];
+                    for (int off = 32; off >= G; off >>= 1) sum += lane_xor(sum, lane, off);
+                    red[(h * W + w) * T + t] = sum;
+                }
             __syncthreads();
-            for (int w = 0; w < W; ++w) {
-                // group t: lane t of every wave when G <= 64; otherwise lane
-                // t % 64 of the waves whose first group is t rounded down to 64
-                double sum = 0.0;
-                if (wave_reports)
-                    for (int v2 = 0; v2 < nwaves; ++v2)
-                        if (G <= 64 || ((v2 * 64) & (G - 1)) == wave * 64)
-                            sum += red[w * T + v2 * 64 + (t & 63)];
-                tot[w] += sum;  // (of exact sums: one rounding)
-            }
+            for (int h = 0; h < kAtOnce; ++h)
+                for (int w = 0; w < W; ++w) {
+                    // group t: lane t of every wave when G <= 64; otherwise lane
+                    // t % 64 of the waves whose first group is t rounded down to 64
+                    double sum = 0.0;
+                    if (wave_reports)
+                        for (int v2 = 0; v2 < nwaves; ++v2)
+                            if (G <= 64 || ((v2 * 64) & (G - 1)) == wave * 64)
+                                sum += red[(h * W + w) * T + v2 * 64 + (t & 63)];
+                    tot[w] += sum;  // (of exact sums: one rounding)
+                }
             __syncthreads();
         }
         for (int w = 0; w < W; ++w) out[w] = tot[w];
