@@ -146,6 +146,8 @@ __global__ __launch_bounds__(256) void batch_prep(BatchArgs B, int jprec) {
         B.c0[e] = static_cast<float>(c0 * static_cast<double>(E.c0_scale));
         B.offset[e] = 0.5 * t3 + 0.25 * t2;
     }
+    if (B.energy_apart)
+        for (int m = t; m < 2 * B.M; m += 256) B.esum[static_cast<size_t>(e) * B.M * 2 + m] = 0.0;
     if (E.n > kBatchSlots) return;  // (a gang: it needs no spin order)
     rank_rows(E.n, B.row_ptr + E.rp_off, B.perm + E.row_off, B.rank + E.row_off, bins);
     if (E.n > kBatchSlotsSmall) {
@@ -186,6 +188,62 @@ __global__ void batch_reset(int *counters, int n) {
     if (static_cast<int>(threadIdx.x) < n) counters[threadIdx.x] = 0;
 }
 
+// Final FP64 O(T) of every agent (Eq. 13), from the assignments: a workgroup
+// sums kEnergyChunk rows of one event for 64 agents, one lane each, in the exact
+// parts of add_split, so the atomic sums are the step kernel's energies to the
+// bit.  Where a workgroup of the step kernel takes several items, their
+// energies there cost it a chain of loads per slot and item (40 events of 5000
+// spins x 128 agents, 1 step: 1.05 -> 0.84 ms); of few items this launch costs
+// more than it saves.
+// Four rows of a wave are in flight together: each is a chain of loads.
+__global__ __launch_bounds__(1024) void batch_energy(BatchArgs B) {
+    constexpr int kWaves = 16, kPer = kEnergyChunk / kWaves, R = 4;
+    __shared__ double sum[2][kWaves][64];
+    const int lanes = (B.M + 63) / 64, chunk = blockIdx.x / lanes, e = B.chunk_event[chunk];
+    const BatchEvent E = B.ev[e];
+    const int lo = (chunk - E.chunk0) * kEnergyChunk;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int m = (blockIdx.x % lanes) * 64 + lane, mc = min(m, B.M - 1);
+    const int8_t *T = B.T + static_cast<size_t>(E.row_off) * B.M + mc;
+    const int *rp = B.row_ptr + E.rp_off, *col = B.col + E.nz_off;
+    const double *a = B.a + E.row_off, *b = B.b + E.nz_off, at = B.split_at[e];
+    double v[2] = {0.0, 0.0};
+    for (int u = 0; u < kPer; u += R) {
+        double er[R];
+        int p[R], q[R];
+        bool on[R];
+        int most = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = lo + wave * kPer + u + r, ic = min(i, E.n - 1);
+            p[r] = rp[ic];
+            q[r] = i < E.n ? rp[ic + 1] : p[r];
+            er[r] = a[ic];
+            on[r] = i < E.n && T[static_cast<size_t>(ic) * B.M] != 0;
+            most = max(most, q[r] - p[r]);
+        }
+        for (int k = 0; k < most; ++k) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (k >= q[r] - p[r]) continue;  // (uniform: a row is a wave's)
+                const int i = lo + wave * kPer + u + r, c = col[p[r] + k];
+                const double bv = b[p[r] + k];
+                if (c > i && T[static_cast<size_t>(c) * B.M] != 0) er[r] += bv;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) add_split(on[r] ? er[r] : 0.0, at, v[0], v[1]);
+    }
+    sum[0][wave][lane] = v[0];
+    sum[1][wave][lane] = v[1];
+    __syncthreads();
+    if (wave < 2 && m < B.M) {
+        double tot = 0.0;
+        for (int w = 0; w < kWaves; ++w) tot += sum[wave][w][lane];
+        atomicAdd(B.esum + (static_cast<size_t>(e) * B.M + m) * 2 + wave, tot);
+    }
+}
+
 constexpr int kSelect = 256;
 
 // Per event: best agent (minimum energy, lowest index on ties), its T,
@@ -198,7 +256,9 @@ __global__ __launch_bounds__(kSelect) void batch_select(BatchArgs B) {
     double be = INFINITY;
     int bm = 0x7fffffff;
     for (int m = t; m < B.M; m += kSelect) {
-        const double v = B.energy[static_cast<size_t>(e) * B.M + m];
+        const size_t at = static_cast<size_t>(e) * B.M + m;
+        if (B.energy_apart && !E.gang) B.energy[at] = B.esum[2 * at] + B.esum[2 * at + 1];
+        const double v = B.energy[at];
         if (v < be || (v == be && m < bm)) {
             be = v;
             bm = m;
@@ -280,6 +340,11 @@ hipError_t launch_batch_steps(int mode, int jprec, int tpb, bool long_rows, cons
     if (tpb == kBatchTPBSmall) return steps_of_shape<kBatchTPBSmall>(mode, jprec, long_rows, B, st);
     if (tpb == kBatchTPB) return steps_of_shape<kBatchTPB>(mode, jprec, long_rows, B, st);
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_batch_energy(const BatchArgs &B, hipStream_t st) {
+    if (B.n_chunks > 0) batch_energy<<<static_cast<unsigned>(B.n_chunks) * ((B.M + 63) / 64), 1024, 0, st>>>(B);
+    return hipGetLastError();
 }
 
 hipError_t launch_batch_select(const BatchArgs &B, hipStream_t st) {

@@ -107,6 +107,15 @@ __device__ __forceinline__ float shared_value(float x) {
         return x;
 }
 
+// Adds a term below 2^E to two sums that are exact over 2^14 such terms, in any
+// order: a multiple of 2^(E - 38) and one of 2^(E - 77); at = 1.5 * 2^(E + 14).
+// What is dropped is below 2^(E - 78).
+__device__ __forceinline__ void add_split(double term, double at, double &high_sum, double &low_sum) {
+    const double high = (term + at) - at, rest = high == term ? 0.0 : term - high;
+    high_sum += high;
+    low_sum += (rest + at * 0x1p-39) - at * 0x1p-39;
+}
+
 // ------------------------------------------------------------ reductions
 
 __device__ __forceinline__ double wave_sum(double v) {

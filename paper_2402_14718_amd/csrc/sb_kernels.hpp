@@ -73,7 +73,10 @@ struct BatchEvent {
     int event_id;                // Philox counter word 2
     float c0_scale;              // c0 of the event = (fixed or auto c0) * c0_scale
     int gang;                    // solved as gangs of row bands
+    int chunk0;                  // first chunk of the event
 };
+
+constexpr int kEnergyChunk = 512;  // rows per workgroup of batch_energy
 
 struct BatchArgs {
     int E, M, K, ckpt_every, n_ckpt;
@@ -111,6 +114,10 @@ struct BatchArgs {
     int over_items;              // first items of the launch for long rows that belong to the one of two agents
     double *split_at;            // [E] where rows_item splits an event's energy terms (prep output)
     double *energy;              // [E * M] final O(T)
+    // batches of many items: final energies by batch_energy instead of the step kernel
+    int energy_apart, n_chunks;  // chunks of kEnergyChunk rows of all events without gangs
+    const int *chunk_event;      // [n_chunks]
+    double *esum;                // [E * M * 2] both parts' sums (zeroed by prep)
     double *trace;               // [E * n_ckpt] best so far, or null
     double *best_energy;         // [E]
     int *best_agent;             // [E]
@@ -159,6 +166,8 @@ hipError_t launch_batch_steps(int mode, int jprec, int tpb, bool long_rows, cons
 template <int MODE, int JP, int TPB>
 hipError_t launch_batch_steps_tu(const BatchArgs &B, bool long_rows, hipStream_t st);
 
+// final energies of every event without gangs, from its agents' T
+hipError_t launch_batch_energy(const BatchArgs &B, hipStream_t st);
 hipError_t launch_batch_select(const BatchArgs &B, hipStream_t st);
 // the gang launch (persistent grid of `B.grid` 1024-thread workgroups) and
 // the reduction of its partial energies and stamps; n_gangs gangs

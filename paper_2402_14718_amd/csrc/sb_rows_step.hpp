@@ -545,13 +545,10 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
             state(sc, P, buf, x);
             for (int w = 0; w < W; ++w) {
                 const double term = (there & (x[w] >= 0.0f)) ? er[w] : 0.0;
-                if constexpr (SINGLE) {
+                if constexpr (SINGLE)
                     v[0][w] += term;
-                } else {
-                    const double high = (term + at) - at, rest = high == term ? 0.0 : term - high;
-                    v[0][w] += high;
-                    v[kParts - 1][w] += (rest + at * 0x1p-39) - at * 0x1p-39;
-                }
+                else
+                    add_split(term, at, v[0][w], v[kParts - 1][w]);
             }
         });
         // (both parts at once where the buffer has room for them)
@@ -980,7 +977,7 @@ __device__ __forceinline__ void rows_item(const BatchArgs &B, unsigned char *sme
             if (k < kend) step(std::integral_constant<int, 0>{}, k++);
         }
         const bool checkpoint = B.ckpt_every > 0 && k % B.ckpt_every == 0;
-        if (checkpoint || (!SINGLE && k == B.K)) {
+        if (checkpoint || (!SINGLE && !B.energy_apart && k == B.K)) {
             double en[W];
             agent_energy(k & 1, en);
             if (!SINGLE && wave_reports)

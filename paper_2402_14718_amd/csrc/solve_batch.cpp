@@ -34,6 +34,8 @@ struct Schedule {
     std::vector<int32_t> gitem_gang, gitem_band;
     int64_t xg_floats = 0, part_entries = 0;
     int max_bands = 0;
+    std::vector<int32_t> chunk_event;  // of batch_energy
+    bool energy_apart = false;
     int items() const { return static_cast<int>(item_event.size() + gitem_gang.size()); }
 };
 
@@ -121,6 +123,7 @@ bool list_fits(int32_t n, int64_t nnz, int G, int tpb, int W, int asked) {
 constexpr double kCUs = 256;  // (a constant: plan and run must agree)
 constexpr int kItemsPerGroup = 6;
 constexpr double kLeastFill = 0.25;
+constexpr int kEnergyItems = 2;
 
 int check_tuning(const sbt_batch_tuning &t, const char *who) {
     if (t.split_n < 0) return fail(SBT_EINVAL, "%s: tuning split_n must be >= 0", who);
@@ -178,6 +181,7 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
     S.gangs.clear();
     S.xg_floats = S.part_entries = 0;
     S.max_bands = 0;
+    S.chunk_event.clear();
     std::vector<int64_t> gang_cost;
     int64_t row_off = 0, nz_off = 0;
     for (int32_t e = 0; e < E; ++e) {
@@ -193,6 +197,8 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
         d.event_id = same_start ? p.event : p.event + e;
         d.c0_scale = c0_scale ? static_cast<float>(c0_scale[e]) : 1.0f;
         d.gang = n[e] > band_limit;
+        d.chunk0 = static_cast<int>(S.chunk_event.size());
+        if (!d.gang) S.chunk_event.insert(S.chunk_event.end(), (n[e] + sbt::kEnergyChunk - 1) / sbt::kEnergyChunk, e);
         if (n[e] > band_limit) {
             // row bands of balanced size, one gang per agent
             const int bands = (n[e] + band_limit - 1) / band_limit;
@@ -269,6 +275,11 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
     S.n_small = static_cast<int>(items[kSmall].size());
     S.n_large = static_cast<int>(items[kLarge].size());
     S.n_long = static_cast<int>(items[kLong].size());
+    // final energies apart where the state is not a checkpoint's and a workgroup
+    // takes more than kEnergyItems items
+    const bool at_checkpoint = p.energy_every > 0 && p.steps % p.energy_every == 0;
+    S.energy_apart = !at_checkpoint && (S.n_small > kEnergyItems * 2 * kCUs || S.n_large + S.n_long > kEnergyItems * kCUs);
+    if (!S.energy_apart) S.chunk_event.clear();
     // gangs: largest events first, then agent order; items gang after gang
     std::vector<int> order(S.gangs.size());
     std::iota(order.begin(), order.end(), 0);
@@ -291,7 +302,7 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
 }
 
 struct BatchLayout {
-    size_t ev, item_e, item_a, item_lg, J16, colr, h, c0, offset, perm, rank, sched, counter, trash, etrace, split_at, energy, halves, long_rows, T;
+    size_t ev, item_e, item_a, item_lg, J16, colr, h, c0, offset, perm, rank, sched, counter, trash, etrace, split_at, energy, chunk_e, esum, halves, long_rows, T;
     size_t gangs, gitem_g, gitem_b, xg, gints, gpart, gclock, done;
     size_t total;
     int n_ckpt;
@@ -326,6 +337,8 @@ BatchLayout make_layout(const Schedule &S, const sbt_solve_params &p) {
     L.long_rows = take(sizeof(int) * E);
     L.split_at = take(sizeof(double) * E);
     L.energy = take(sizeof(double) * E * M);
+    L.chunk_e = take(sizeof(int32_t) * S.chunk_event.size());
+    L.esum = take(S.energy_apart ? 2 * sizeof(double) * E * M : 0);
     L.T = take(static_cast<size_t>(S.sum_n) * M);
     const size_t G = S.gangs.size(), GI = S.gitem_gang.size();
     L.gangs = take(sizeof(sbt::GangDesc) * G);
@@ -432,6 +445,9 @@ extern "C" int sbt_batch_plan_tuned(const int32_t *n, const int64_t *nnz, int32_
                            sizeof(int32_t) * S.item_agent0.size(), hipMemcpyHostToDevice, st));
     SBT_HIP(hipMemcpyAsync(ws + L.item_lg, S.item_lg.data(), sizeof(int32_t) * S.item_lg.size(),
                            hipMemcpyHostToDevice, st));
+    if (S.energy_apart)
+        SBT_HIP(hipMemcpyAsync(ws + L.chunk_e, S.chunk_event.data(), sizeof(int32_t) * S.chunk_event.size(),
+                               hipMemcpyHostToDevice, st));
     if (!S.gangs.empty()) {
         if (S.max_bands > cu_count())
             return fail(SBT_EUNSUPPORTED, "%s: an event needs %d row bands at once, more than the "
@@ -517,6 +533,10 @@ extern "C" int sbt_batch_run_tuned(const sbt_dev_batch *batch, sbt_mode mode, sb
     B.etrace = reinterpret_cast<double *>(ws + L.etrace);
     B.energy = out->agent_energy ? out->agent_energy : reinterpret_cast<double *>(ws + L.energy);
     B.split_at = reinterpret_cast<double *>(ws + L.split_at);
+    B.energy_apart = S.energy_apart;
+    B.n_chunks = static_cast<int>(S.chunk_event.size());
+    B.chunk_event = reinterpret_cast<const int *>(ws + L.chunk_e);
+    B.esum = reinterpret_cast<double *>(ws + L.esum);
     B.halves = reinterpret_cast<int *>(ws + L.halves);
     B.long_rows = reinterpret_cast<int *>(ws + L.long_rows);
     // (without the launch for them no event has long rows)
@@ -593,6 +613,7 @@ extern "C" int sbt_batch_run_tuned(const sbt_dev_batch *batch, sbt_mode mode, sb
         e = sbt::launch_batch_gang_reduce(B, n_gangs, st);
         if (e != hipSuccess) return fail(SBT_EDEVICE, "%s: gang reduce: %s", who, hipGetErrorString(e));
     }
+    if (S.energy_apart) SBT_HIP(sbt::launch_batch_energy(B, st));
     e = sbt::launch_batch_select(B, st);
     if (e != hipSuccess) return fail(SBT_EDEVICE, "%s: batch select: %s", who, hipGetErrorString(e));
     if (out->agent_trace)

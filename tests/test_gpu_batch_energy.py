@@ -82,3 +82,24 @@ def test_more_events_than_a_grid_dimension_holds():
     want = a[:, 0, None] * T[:, 0] + a[:, 1, None] * T[:, 1] + b[:, None] * T[:, 0] * T[:, 1]
     assert np.array_equal(r["agent_energy"], want)
     assert np.array_equal(r["energy"], want.min(axis=1))
+
+
+@pytest.mark.parametrize("M", [3, 70])
+def test_energies_apart_from_the_step_kernel_are_its_own(qubos, M):
+    """Batches of many items sum the final energies in a launch of their own;
+    a run that ends at a checkpoint has them from the step kernel."""
+    qs = (qubos + [sbt.build_qubo(tg.generate(tg.plain_spec(1200), 77).hits_struct())]) * (60 if M == 3 else 4)
+    kw = dict(want_agent_energy=True, want_agent_state=True, tuning=sbt.batch_tuning(split_n=1, fill=0.02))
+    runs = []
+    for every in (0, 20, 9):  # (9: the last checkpoint is not the end)
+        s = sbt.DeviceBatchSolver(qs, "dsb", "bf16", sbt.solve_params(agents=M, steps=20, seed=3, c0=0.3, energy_every=every),
+                                  **kw)
+        for _ in range(2):
+            s.run()
+        runs.append(s.result())
+    assert s.n_items > 1200  # more than two items per workgroup, those of gangs aside
+    for r in (runs[0], runs[2]):
+        for k in ("agent_energy", "energy", "best_agent"):
+            gang = np.array([q.n > 9216 for q in qs])
+            assert np.array_equal(r[k][~gang], runs[1][k][~gang]), k
+            assert np.allclose(r[k][gang], runs[1][k][gang], rtol=1e-12)
