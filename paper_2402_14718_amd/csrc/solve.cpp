@@ -211,11 +211,14 @@ int device_lds_limit() {
 // a step with nine slots, 1.16 with six); a hinted size wherever it holds the
 // event.  Two agents per workgroup once one per CU does not hold them all: a
 // coupling is then read and held once for both (us per step, one against two:
-// 5458 x 600 bSB 3.73 / 2.76, dSB 3.82 / 2.66; 8484 x 1024 bSB 6.9 / 5.3, x 900
-// dSB 8.6 / 4.2).  Nine slots of two agents hold fewer couplings, so past 3.5
-// per spin one agent is the better again (random rows, bSB: 3 per spin 7.1 /
-// 4.8, 3.5 9.8 / 16.1 -- track events, of longer first rows and shorter last
-// ones, have 3.4 at the largest size).
+// 5458 x 600 bSB 3.73 / 2.76, dSB 3.82 / 2.66; 8484 x 1024 bSB 6.9 / 4.4, x 900
+// dSB 8.6 / 4.2).  Nine slots of two agents hold fewer couplings and leave half
+// the list, so past 3.5 per spin one agent is the better again.  What decides is
+// how many couplings the list has to take, of which only the mean is known
+// here: the line is that of track events (the above: 3.4 per spin), whose few
+// long rows the registers hold.  Random rows of 8484 spins x 1024, one / two: dSB 3.5 per spin 11.0 / 6.5, 3.6 11.8 one; bSB 3.3 9.4
+// / 6.1, 3.4 9.5 / 12.2 (9216 spins: 3.1 9.8 / 6.3, 3.2 10.7 / 12.1); a launch per
+// step takes 29 and more there.
 sbt::RowsShape rows_shape(int32_t n, int64_t nnz, int32_t M, int tpb_hint) {
     sbt::RowsShape R{0, 0, 0};
     if (n > sbt::kBatchSPT * 1024) return R;
@@ -231,11 +234,13 @@ sbt::RowsShape rows_shape(int32_t n, int64_t nnz, int32_t M, int tpb_hint) {
     return R;
 }
 
-// LDS words that the step loop's buffers leave for tails in any mode.
+// LDS words that the step loop's buffers leave for tails in any mode (shapes of
+// nine slots and up to 512 threads take half of a CU's LDS).
 int64_t rows_tail_words(const sbt::RowsShape &R) {
     const int64_t words = int64_t(R.slots) * R.threads;
     const int64_t used = R.slots < sbt::kBatchSPT ? 8 * words * R.agents : (R.agents == 1 ? 12 : 16) * words;
-    return (163840 - 1024 - 16 * int64_t(R.threads) - used) / 4;
+    const int64_t lds = R.slots == sbt::kBatchSPT && R.threads <= 512 ? 81920 : 163840;
+    return (lds - 1024 - 16 * int64_t(R.threads) - used) / 4;
 }
 
 // Whether AUTO takes the resident step loop: while a row's couplings stay in
@@ -244,15 +249,21 @@ int64_t rows_tail_words(const sbt::RowsShape &R) {
 // spins of 16 couplings 1.9 against 9.4 / 3.8 against 10.4; 4000 of 8 2.6
 // against 9.3 / 5.5 against 16.8; 8000 of 3 1.9 against 9.9 / 7.4 against
 // 29.2); once the tails overflow the LDS it loses (2000 of 32 with 32 agents
-// 31 against 5; 8000 of 8 25 against 13 / 102 against 41).  Only n and the
+// 10.0 against 4.6; 8000 of 8 16.5 against 13.4 / 66 against 41).  Only n and the
 // number of couplings are known here: either all couplings fit the tail
 // list, or there are few enough per spin for the registers of a shape (33
-// to 43 couplings for 4 to 9 spins, longest rows first).  The LDS-row kernel
-// loses to the streaming step at every size past these shapes.
-bool rows_fit(int32_t n, int64_t nnz, const sbt::RowsShape &R) {
+// to 43 couplings for 4 to 9 spins, longest rows first).  On the hinted shapes
+// of half the LDS the list takes what the registers do not hold (1500 spins on
+// 256 threads x 32 agents, 10.0 / 13.9 couplings per spin: 3.1 against 4.2, 8.5
+// against 4.2).  The LDS-row kernel loses to the streaming step at every size
+// past these shapes.
+bool rows_fit(int32_t n, int64_t nnz, sbt_mode mode, const sbt::RowsShape &R) {
     if (R.slots == 0) return false;
     const int per_spin = R.slots == 2 ? 16 : (R.slots == 4 ? 8 : (R.slots == 6 ? 5 : 4));
-    return 2 * nnz <= rows_tail_words(R) || nnz <= per_spin * int64_t(n);
+    int64_t held = 0;
+    if (R.slots == sbt::kBatchSPT && R.threads <= 512)
+        for (int s = 0; s * R.threads < n; ++s) held += int64_t(R.threads) * sbt::kHeldCaps[mode == SBT_DSB ? 1 : 0][s];
+    return 2 * (nnz - held) <= rows_tail_words(R) || nnz <= per_spin * int64_t(n);
 }
 
 // Shape of the LDS-row resident kernel, or tpb = 0 if it does not fit.
@@ -321,7 +332,7 @@ int pick_kernel(int32_t n, int64_t nnz, sbt_mode mode, const sbt_solve_params &p
             return fail(SBT_EUNSUPPORTED, "resident kernel: n = %d does not fit in LDS", n);
         return SBT_KERNEL_RESIDENT;
     }
-    if (rows_fit(n, nnz, R)) return SBT_KERNEL_RESIDENT;
+    if (rows_fit(n, nnz, mode, R)) return SBT_KERNEL_RESIDENT;
     return stream_kind;
 }
 
