@@ -5,9 +5,9 @@ schedule -- which events run on the 512-thread step-kernel shape (two
 workgroups per CU) rather than the 1024-thread one, how full a work item is
 packed with agents, how many LDS words hold couplings past the register
 capacity -- is planned and run on the GPU through the C ABI and timed with
-HIP events on its stream.  A schedule changes no step arithmetic (only the
-order of the FP64 energy sums), so every candidate must return the same
-best energies to rounding (checked); the fastest is
+HIP events on its stream.  A schedule changes no step arithmetic, so every
+candidate must return the same best energies (checked to rounding: events run
+as gangs of row bands sum theirs by band); the fastest is
 written into the JSON tuning cache under the batch's key
 (sbt_batch_tuning_key), where sbt_batch_tuning_lookup -- and through it
 sbt_solve_batch, sbt_c0_scan and DeviceBatchSolver -- finds it.
@@ -33,7 +33,9 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 DEFAULT_CACHE = os.path.join(PKG, "tuning", "batch_tuning.json")
 FORMAT = "sbtrack batch tuning 1"
 
-SPLITS = (0, 1152, 2304, 4608)
+# 0: chosen by the library (every event that fits the 512-thread shape); 1: every
+# event of more than one spin on the 1024-thread shape
+SPLITS = (0, 1, 1152, 2304)
 FILLS = (1.0, 0.5)
 TAILS = (8192, 4096)
 

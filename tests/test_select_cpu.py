@@ -1,6 +1,7 @@
-"""AUTO's choice on shapes of half the LDS (a hint of 256 or 512 threads): the
-on-chip loop while registers and the list hold the couplings, as many words as
-the kernel's own LDS leaves."""
+"""Choices made on the host.  AUTO on shapes of half the LDS (a hint of 256 or
+512 threads): the on-chip loop while registers and the list hold the couplings,
+as many words as the kernel's own LDS leaves.  The tuner: splits that plan
+different items."""
 import pytest
 
 import paper_2402_14718_amd as sbt
@@ -15,3 +16,22 @@ def test_hinted_shapes_leave_the_chip_where_their_list_ends(n, tpb, mode, held, 
     assert kernel(held + words // 2) == "resident"
     assert kernel(held + words // 2 + 1) == "stream"
     assert kernel(4 * n) == "resident"
+
+
+def test_the_tuner_tries_schedules_that_differ():
+    """Each split of the shapes plans another number of items (seen in the
+    workspace that they take)."""
+    import ctypes as C
+
+    import numpy as np
+
+    from paper_2402_14718_amd import autotune
+    n = np.array([90, 300, 800, 1500, 3000, 6000] * 60, np.int32)
+    nnz = (2 * n).astype(np.int64)
+    p = sbt.solve_params(agents=128, steps=10)
+    sizes = []
+    for split in autotune.SPLITS:
+        t = sbt.batch_tuning(split_n=split)
+        sizes.append(sbt.load().sbt_batch_workspace_bytes_tuned(
+            n.ctypes.data_as(C.POINTER(C.c_int32)), nnz.ctypes.data_as(C.POINTER(C.c_int64)), n.size, C.byref(p), C.byref(t)))
+    assert len(set(sizes)) == len(autotune.SPLITS), dict(zip(autotune.SPLITS, sizes))
