@@ -8,8 +8,9 @@
 //                                     h = -(a/2 + rowsum(b)/4) (FP32),
 //                                     C, c0 (FP64, fixed-order reductions)
 //   init_state                        Philox4x32-10 start x0, y0
-//   sb_resident<MODE, TPB, SPT, JLDS> all K steps in one launch: one
-//                                     workgroup per agent, positions in LDS
+//   sb_resident<MODE, JLDS>           all K steps in one launch, events past
+//                                     the step loop's shapes: one workgroup
+//                                     per agent, positions in LDS
 //                                     (ping-pong), momenta in VGPRs, J in
 //                                     LDS when it fits
 //   (the streaming one-step kernel is in sb_stream.hip)
@@ -173,13 +174,14 @@ __global__ __launch_bounds__(256) void schedule_table(int K, double a0, float *_
 
 // ------------------------------------------------------ resident kernel
 
-// Workgroup = one agent, all n spins.  Thread t owns spins t, t+TPB, ...
+// Workgroup = one agent, all n spins.  Thread t owns spins t, t + TPB, ...
 // (SPT of them) and keeps their x, y, h and row bounds in registers; the
 // positions every thread gathers from live in LDS, double-buffered so one
 // barrier per step suffices.  LDS: [2][n] floats, then (JLDS) row_ptr,
 // col, J, then the reduction scratch.
-template <int MODE, int TPB, int SPT, bool JLDS>
-__global__ __launch_bounds__(TPB) void sb_resident(ResidentArgs A) {
+template <int MODE, bool JLDS>
+__global__ __launch_bounds__(kResidentThreads) void sb_resident(ResidentArgs A) {
+    constexpr int TPB = kResidentThreads, SPT = kResidentSlots;
     extern __shared__ __align__(16) unsigned char smem[];
     const int n = A.n;
     float *xs = reinterpret_cast<float *>(smem);
@@ -468,29 +470,15 @@ hipError_t launch_init(int n, int M, uint64_t seed, uint32_t event, float *x, fl
     return hipGetLastError();
 }
 
-template <int MODE, int TPB, bool JLDS>
-static hipError_t launch_lds_spt(const ResidentArgs &A, const ResidentShape &S, hipStream_t st) {
-    switch (S.spt) {
-        case 1: return launch_with_lds(sb_resident<MODE, TPB, 1, JLDS>, dim3(A.M), dim3(TPB), S.lds_bytes, st, A);
-        case 2: return launch_with_lds(sb_resident<MODE, TPB, 2, JLDS>, dim3(A.M), dim3(TPB), S.lds_bytes, st, A);
-        case 4: return launch_with_lds(sb_resident<MODE, TPB, 4, JLDS>, dim3(A.M), dim3(TPB), S.lds_bytes, st, A);
-        case 8: return launch_with_lds(sb_resident<MODE, TPB, 8, JLDS>, dim3(A.M), dim3(TPB), S.lds_bytes, st, A);
-        case 16: return launch_with_lds(sb_resident<MODE, TPB, 16, JLDS>, dim3(A.M), dim3(TPB), S.lds_bytes, st, A);
-        default: return hipErrorInvalidValue;
-    }
-}
-
 template <int MODE>
 static hipError_t launch_resident_m(const ResidentArgs &A, const ResidentShape &S, hipStream_t st) {
-    switch (S.tpb) {
-        case 64: return S.jlds ? launch_lds_spt<MODE, 64, true>(A, S, st) : launch_lds_spt<MODE, 64, false>(A, S, st);
-        case 256: return S.jlds ? launch_lds_spt<MODE, 256, true>(A, S, st) : launch_lds_spt<MODE, 256, false>(A, S, st);
-        case 1024: return S.jlds ? launch_lds_spt<MODE, 1024, true>(A, S, st) : launch_lds_spt<MODE, 1024, false>(A, S, st);
-        default: return hipErrorInvalidValue;
-    }
+    const dim3 grid(A.M), block(kResidentThreads);
+    return S.jlds ? launch_with_lds(sb_resident<MODE, true>, grid, block, S.lds_bytes, st, A)
+                  : launch_with_lds(sb_resident<MODE, false>, grid, block, S.lds_bytes, st, A);
 }
 
 hipError_t launch_resident(int mode, const ResidentArgs &A, const ResidentShape &S, hipStream_t st) {
+    if (A.n > kResidentSpins || S.lds_bytes == 0) return hipErrorInvalidValue;
     if (mode == kASB) return launch_resident_m<kASB>(A, S, st);
     return mode == kDSB ? launch_resident_m<kDSB>(A, S, st) : launch_resident_m<kBSB>(A, S, st);
 }

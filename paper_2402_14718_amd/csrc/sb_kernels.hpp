@@ -27,19 +27,20 @@ struct ResidentArgs {
     const float *sched;          // [K] a0 - a_k (schedule table)
 };
 
-// Shape of the LDS-row resident kernel.
+// The LDS-row resident kernel, for events past the step loop's shapes.
+constexpr int kResidentThreads = 1024;
+constexpr int kResidentSlots = 16;  // spins per thread
+constexpr int kResidentSpins = kResidentThreads * kResidentSlots;
 struct ResidentShape {
-    int tpb;                     // threads per workgroup
-    int spt;                     // spins per thread: a power of two up to 16
     bool jlds;                   // J held in LDS
-    size_t lds_bytes;
+    size_t lds_bytes;            // 0: the event does not fit
 };
 
 // Shape of the resident kernel whose rows are held in registers
 // (sb_resident_mode.hip); slots = 0: the event does not fit it.
 struct RowsShape {
     int threads;                 // 64, 256, 512 or 1024
-    int slots;                   // spins per thread: 2, 4 or 9
+    int slots;                   // spins per thread: 2, 4, 6 or 9
     int agents;                  // per workgroup: 1 or 2
 };
 

@@ -46,10 +46,13 @@ struct Layout {
 bool quad_step(sbt_mode mode, int32_t M) { return mode != SBT_DSB && M % 4 == 0 && M > 64; }
 
 // AUTO runs dSB on the matrix-core step from 2^23 spin-agent pairs on, for
-// every streaming coupling form (measured against the CSR step, FP8 /
-// BF16X2 / FP32 / FP8_BLOCK: 208710 x 512, 1.92x / 1.68x / 1.46x / 1.43x;
-// 8493 x 1024, cache-resident, 1.33x / 1.06x / 1.09x / 1.24x; 1480 x 256
-// is launch-bound and the matrix-core step 0.86x / 0.85x / 0.84x / 0.82x).
+// every streaming coupling form (measured against the CSR step, a launch per
+// step both, FP8 / BF16X2 / FP32 / FP8_BLOCK: 208710 x 512, 1.92x / 1.68x / 1.46x
+// / 1.43x; 8493 x 1024, cache-resident, 1.33x / 1.06x / 1.09x / 1.24x; 1480 x 256
+// is launch-bound and the matrix-core step 0.86x / 0.85x / 0.84x / 0.82x).  The
+// line is older than the on-chip loop of FP32 events, which is the faster where
+// it holds them (8484 spins, us a step: 4.2 x 900 agents, this step 10.2 x 1024);
+// its sums are in another order, so the line has stayed.
 // FP16 and BF16 single solves run only there (the CSR steps do not take
 // them; the batch functions do).
 constexpr int32_t kCUs = 256;
@@ -216,9 +219,10 @@ int device_lds_limit() {
 // the list, so past 3.5 per spin one agent is the better again.  What decides is
 // how many couplings the list has to take, of which only the mean is known
 // here: the line is that of track events (the above: 3.4 per spin), whose few
-// long rows the registers hold.  Random rows of 8484 spins x 1024, one / two: dSB 3.5 per spin 11.0 / 6.5, 3.6 11.8 one; bSB 3.3 9.4
-// / 6.1, 3.4 9.5 / 12.2 (9216 spins: 3.1 9.8 / 6.3, 3.2 10.7 / 12.1); a launch per
-// step takes 29 and more there.
+// long rows the registers hold.  Random rows of 8484 spins x 1024, one / two:
+// dSB 3.5 per spin 11.0 / 6.5, 3.6 11.8 with one; bSB 3.3 9.4 / 6.1, 3.4 9.5 /
+// 12.2 (9216 spins: 3.1 9.8 / 6.3, 3.2 10.7 / 12.1); a launch per step takes 29
+// and more there.
 sbt::RowsShape rows_shape(int32_t n, int64_t nnz, int32_t M, int tpb_hint) {
     sbt::RowsShape R{0, 0, 0};
     if (n > sbt::kBatchSPT * 1024) return R;
@@ -266,24 +270,16 @@ bool rows_fit(int32_t n, int64_t nnz, sbt_mode mode, const sbt::RowsShape &R) {
     return 2 * (nnz - held) <= rows_tail_words(R) || nnz <= per_spin * int64_t(n);
 }
 
-// Shape of the LDS-row resident kernel, or tpb = 0 if it does not fit.
+// Shape of the LDS-row resident kernel (events past the step loop's shapes), or
+// lds_bytes = 0 if it does not fit.
 sbt::ResidentShape resident_shape(int32_t n, int64_t nnz, int lds_limit) {
-    sbt::ResidentShape S{0, 0, false, 0};
-    auto pow2_at_least = [](int v) {
-        int p = 1;
-        while (p < v) p <<= 1;
-        return p;
-    };
-    const int tpb = n <= 64 ? 64 : (n <= 1024 ? 256 : 1024);
-    const int spt = pow2_at_least((n + tpb - 1) / tpb);
-    if (spt > 16) return S;
-    const size_t red = 16 + sizeof(double) * (tpb / 64);
+    sbt::ResidentShape S{false, 0};
+    if (n > sbt::kResidentSpins) return S;
+    const size_t red = 16 + sizeof(double) * (sbt::kResidentThreads / 64);
     const size_t base = sizeof(float) * 2 * static_cast<size_t>(n) + red;
     const size_t jbytes = sizeof(int) * (static_cast<size_t>(n) + 1) +
                           (sizeof(int) + sizeof(float)) * static_cast<size_t>(nnz);
     if (base > static_cast<size_t>(lds_limit)) return S;
-    S.tpb = tpb;
-    S.spt = spt;
     S.jlds = base + jbytes <= static_cast<size_t>(lds_limit);
     S.lds_bytes = S.jlds ? base + jbytes : base;
     return S;
@@ -328,7 +324,7 @@ int pick_kernel(int32_t n, int64_t nnz, sbt_mode mode, const sbt_solve_params &p
     if (p.kernel == SBT_KERNEL_AUTO && mfma_auto(mode, p.precision, n, p.agents))
         return SBT_KERNEL_STREAM_MFMA;
     if (p.kernel == SBT_KERNEL_RESIDENT) {
-        if (R.slots == 0 && S.tpb == 0)
+        if (R.slots == 0 && S.lds_bytes == 0)
             return fail(SBT_EUNSUPPORTED, "resident kernel: n = %d does not fit in LDS", n);
         return SBT_KERNEL_RESIDENT;
     }
