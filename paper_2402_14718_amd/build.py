@@ -36,7 +36,9 @@ HIP_VARIANTS = [("sb_batch_mode.hip", f"{m}_{j}_{tpb}",
                  [f"-DSBT_BATCH_MODE={mi}", f"-DSBT_BATCH_JP={ji}", f"-DSBT_BATCH_TPB={tpb}"])
                 for mi, m in enumerate(("bsb", "dsb", "asb")) for ji, j in enumerate(("fp16", "bf16"))
                 for tpb in (1024, 512)]
-HIP_VARIANTS += [("sb_resident_mode.hip", m, [f"-DSBT_RESIDENT_MODE={mi}"])
+# loops at whole cache lines: the smallest events' steps are one wave's, whose
+# instruction fetch shows (the same loop, 59.4 or 61.9 ns a step by its place)
+HIP_VARIANTS += [("sb_resident_mode.hip", m, [f"-DSBT_RESIDENT_MODE={mi}", "-Xarch_device", "-falign-loops=64"])
                  for mi, m in enumerate(("bsb", "dsb", "asb"))]
 # the GPU QUBO builder evaluates the host builder's cut expressions: no
 # floating-point contraction, like the host file

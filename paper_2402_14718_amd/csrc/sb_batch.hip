@@ -191,10 +191,10 @@ __global__ void batch_reset(int *counters, int n) {
 // Final FP64 O(T) of every agent (Eq. 13), from the assignments: a workgroup
 // sums kEnergyChunk rows of one event for 64 agents, one lane each, in the exact
 // parts of add_split, so the atomic sums are the step kernel's energies to the
-// bit.  Where a workgroup of the step kernel takes several items, their
-// energies there cost it a chain of loads per slot and item (40 events of 5000
-// spins x 128 agents, 1 step: 1.05 -> 0.84 ms); of few items this launch costs
-// more than it saves.
+// bit.  Where a workgroup of the step kernel takes many items, their energies
+// there cost it a chain of loads per slot and item (40 events of 5000 spins x
+// 128 agents, 1 step: 1.05 -> 0.88 ms); of few this launch costs more than it
+// saves.
 // Four rows of a wave are in flight together: each is a chain of loads.
 __global__ __launch_bounds__(1024) void batch_energy(BatchArgs B) {
     constexpr int kWaves = 16, kPer = kEnergyChunk / kWaves, R = 4;

@@ -123,7 +123,10 @@ bool list_fits(int32_t n, int64_t nnz, int G, int tpb, int W, int asked) {
 constexpr double kCUs = 256;  // (a constant: plan and run must agree)
 constexpr int kItemsPerGroup = 6;
 constexpr double kLeastFill = 0.25;
-constexpr int kEnergyItems = 2;
+// (ms, in the step kernel / apart: 96 events of 300-1000 particles x 128, 100 steps,
+// 12 items 4.77 / 4.61; 32 of 20-1000, 3 items 1.565 / 1.59; small events, whose
+// items share a CU, 64 of 100-300 x 64, 50 steps 0.397 / 0.416)
+constexpr int kEnergyItems = 8;
 
 int check_tuning(const sbt_batch_tuning &t, const char *who) {
     if (t.split_n < 0) return fail(SBT_EINVAL, "%s: tuning split_n must be >= 0", who);
@@ -275,10 +278,10 @@ int make_schedule(const int32_t *n, const int64_t *nnz, int32_t E, const double 
     S.n_small = static_cast<int>(items[kSmall].size());
     S.n_large = static_cast<int>(items[kLarge].size());
     S.n_long = static_cast<int>(items[kLong].size());
-    // final energies apart where the state is not a checkpoint's and a workgroup
-    // takes more than kEnergyItems items
+    // final energies apart where the state is not a checkpoint's and workgroups of
+    // 1024 threads take more than kEnergyItems items each
     const bool at_checkpoint = p.energy_every > 0 && p.steps % p.energy_every == 0;
-    S.energy_apart = !at_checkpoint && (S.n_small > kEnergyItems * 2 * kCUs || S.n_large + S.n_long > kEnergyItems * kCUs);
+    S.energy_apart = !at_checkpoint && S.n_large + S.n_long > kEnergyItems * kCUs;
     if (!S.energy_apart) S.chunk_event.clear();
     // gangs: largest events first, then agent order; items gang after gang
     std::vector<int> order(S.gangs.size());

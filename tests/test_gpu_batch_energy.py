@@ -88,7 +88,7 @@ def test_more_events_than_a_grid_dimension_holds():
 def test_energies_apart_from_the_step_kernel_are_its_own(qubos, M):
     """Batches of many items sum the final energies in a launch of their own;
     a run that ends at a checkpoint has them from the step kernel."""
-    qs = (qubos + [sbt.build_qubo(tg.generate(tg.plain_spec(1200), 77).hits_struct())]) * (60 if M == 3 else 4)
+    qs = (qubos + [sbt.build_qubo(tg.generate(tg.plain_spec(1200), 77).hits_struct())]) * (120 if M == 3 else 10)
     kw = dict(want_agent_energy=True, want_agent_state=True, tuning=sbt.batch_tuning(split_n=1, fill=0.02))
     runs = []
     for every in (0, 20, 9):  # (9: the last checkpoint is not the end)
@@ -97,7 +97,8 @@ def test_energies_apart_from_the_step_kernel_are_its_own(qubos, M):
         for _ in range(2):
             s.run()
         runs.append(s.result())
-    assert s.n_items > 1200  # more than two items per workgroup, those of gangs aside
+    # more than eight items per workgroup, beside the gangs' two bands per agent
+    assert s.n_items - 2 * M * sum(q.n > 9216 for q in qs) > 8 * 256
     for r in (runs[0], runs[2]):
         for k in ("agent_energy", "energy", "best_agent"):
             gang = np.array([q.n > 9216 for q in qs])
